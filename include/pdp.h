@@ -238,7 +238,8 @@ typedef struct pdp_params {
     uint64_t inc_capacity;   /* shared-k-mer records the scratch can hold, below 2^32: one per shared
                                 (k-mer, gene a, gene b) and requested direction (0: from the dictionary sizes) */
     uint32_t tile_rows;      /* query genes per accumulation tile, 1..256, rounded down to a power of two
-                                (0: 64; raised when a task would have more than 1024 tiles) */
+                                (0: 64; raised when a task would have more than 1024 tiles).  Tasks of a
+                                group (see pdp_plan_create) choose their own tiles and items */
     uint32_t join_entries;   /* index entries of the larger genome per join sub-range (1..1024) */
     uint32_t lds_budget;     /* LDS bytes of a tile work-group, at most 156 KiB (0 and anything below
                                 32 KiB: 32 KiB, the sorted path's 4096 records); more lets a tile whose
@@ -314,7 +315,14 @@ typedef struct pdp_plan_info {
  * pdp_plan_rows gives each task's first row in both outputs.  A task that
  * names a dictionary bound with PDP_DICT_LONG_GENES has no join items and no
  * tiles: its rows take the long-gene path (and PDP_PARAM_COLMAX does not apply
- * to it), with the same output layout.  Host only.
+ * to it), with the same output layout.  Tasks that compare most pairs of a set
+ * of dictionaries (a group, e.g. all pairs of eight genomes or more) are joined
+ * together: their shared k-mers are found in one pass over the group's indexes
+ * and kept with bounds known from the dictionaries, both directions of a task
+ * come from one (column maxima, whose candidates share the record capacity),
+ * and join_groups and tiles count the group's items and tiles.  A plan with
+ * PDP_PARAM_PERSISTENT or PDP_PARAM_TWO_PASS joins every pair on its own.
+ * Results are identical either way.  Host only.
  * Errors: PDP_E_INVAL (null, k or alphabet mismatch, BBH without AB|BA), PDP_E_LIMIT. */
 int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *params, pdp_plan **out);
 int32_t pdp_plan_info_get(const pdp_plan *plan, pdp_plan_info *info);

@@ -1,10 +1,13 @@
 // C-ABI entry points: argument validation, planning, workspace layout and
 // error reporting around the gfx950 kernels.
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include "internal.hpp"
@@ -48,6 +51,11 @@ struct pdp_plan {
     std::vector<DevTile> tiles;
     std::vector<DevItem> items;
     std::vector<DevLongSeg> long_segs;  // long-gene path: row segments by first row
+    std::vector<DevGroupDict> gdicts;   // group path
+    std::vector<DevGroupTgt> gtgts;
+    std::vector<DevGroupItem> gitems, gitems_wide;
+    std::vector<DevGroupTile> gtiles;
+    std::vector<uint8_t> tmap;
     std::vector<uint32_t> ab_row, ba_row, bbh_row;
     std::vector<uint32_t> order;  // order[t]: position of caller task t in the task table
     PlanShape shape;
@@ -262,6 +270,196 @@ static DevDict dev_dict(const pdp_dict *d) {
     return x;
 }
 
+// Code of the first k-mer of bucket b.
+static uint64_t bucket_code(const pdp_dict *d, uint64_t b) {
+    const AlphaSpec a = alpha_spec(d->alphabet);
+    uint64_t c = 0;
+    for (uint32_t i = 0; i < d->lead; ++i) {
+        c |= (b % a.sigma) << (a.bits * i);
+        b /= a.sigma;
+    }
+    return c << (a.bits * (d->k - d->lead));
+}
+
+// The group path's share of a plan: which tasks take it, and their tables (in_group[t] is set).  A
+// group is a connected component of the task graph, with at least a quarter of its pairs compared,
+// whose pair-by-pair join would search its entries kGroupGain times as often as the group path
+// reads them (all pairs of D genomes: (D - 1) / 2 times), and whose genes meet at most kGroupChance
+// genes of a target genome by chance.  Launch times without the builds, pair path against group
+// path: 5 x 3000 genes, k = 6: 144 / 167 us; 8 x 3000: 236 / 230; 12 x 3000: 445 / 405; chance
+// matches instead of family ones fill the tiles' tables: 12 x 1000 genes, k = 5 (36 by chance)
+// 336 / 428 us, k = 6 (2) 196 / 177.
+constexpr uint64_t kGroupGainNum = 7, kGroupGainDen = 2;
+constexpr double kGroupChance = 12.0;  // expected chance matches per gene and target genome, at most
+static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks, const std::vector<uint8_t> &is_long,
+                            std::vector<uint8_t> &in_group) {
+    std::vector<const pdp_dict *> dicts;
+    std::vector<uint32_t> ta(n_tasks, UINT32_MAX), tb(n_tasks, UINT32_MAX);
+    {
+        std::unordered_map<const void *, uint32_t> index;
+        auto id = [&](const pdp_dict *d) {
+            auto r = index.emplace(d->ix_dir, static_cast<uint32_t>(dicts.size()));
+            if (r.second) dicts.push_back(d);
+            return r.first->second;
+        };
+        for (uint32_t t = 0; t < n_tasks; ++t)
+            if (!is_long[t]) {
+                ta[t] = id(tasks[t].a);
+                tb[t] = id(tasks[t].b);
+            }
+    }
+    const uint32_t nd = static_cast<uint32_t>(dicts.size());
+    std::vector<uint32_t> root(nd);
+    for (uint32_t i = 0; i < nd; ++i) root[i] = i;
+    auto find = [&](uint32_t x) {
+        while (root[x] != x) x = root[x] = root[root[x]];
+        return x;
+    };
+    for (uint32_t t = 0; t < n_tasks; ++t)
+        if (ta[t] != UINT32_MAX) root[find(ta[t])] = find(tb[t]);
+    std::vector<uint32_t> comp(nd), local(nd);  // component of each dictionary and its place there
+    std::vector<std::vector<uint32_t>> members, ctasks;
+    std::vector<uint32_t> of_root(nd, UINT32_MAX);
+    for (uint32_t i = 0; i < nd; ++i) {
+        uint32_t &c = of_root[find(i)];
+        if (c == UINT32_MAX) {
+            c = static_cast<uint32_t>(members.size());
+            members.emplace_back();
+            ctasks.emplace_back();
+        }
+        comp[i] = c;
+        local[i] = static_cast<uint32_t>(members[c].size());
+        members[c].push_back(i);
+    }
+    for (uint32_t t = 0; t < n_tasks; ++t)
+        if (ta[t] != UINT32_MAX) ctasks[comp[ta[t]]].push_back(t);
+    uint64_t entries = 0, all_rows = 0, all_cap = 0;
+    for (uint32_t t = 0; t < n_tasks; ++t)
+        if (ta[t] != UINT32_MAX) all_rows += std::max(tasks[t].a->n_genes, tasks[t].b->n_genes);
+    for (const pdp_dict *d : dicts) all_cap += d->capacity;
+    // small plans: smaller items and tiles, so that the chip's work-group slots are filled once
+    const uint64_t target = std::min<uint64_t>(kGroupTarget, std::max<uint64_t>(256, all_cap / 1024));
+    const double fill_rows = std::max(16.0, double(all_rows) / 1536.0);
+    struct Run {  // the items of one group: buckets in steps of nb
+        uint32_t dict0, n_dicts, nb, n_buckets;
+        bool wide;
+    };
+    std::vector<Run> runs;
+    for (uint32_t c = 0; c < members.size(); ++c) {
+        const std::vector<uint32_t> &M = members[c];
+        const uint32_t D = static_cast<uint32_t>(M.size());
+        if (D < 3 || D > kGroupMaxDicts) continue;
+        uint64_t cap = 0, genes = 0, searched = 0;
+        for (uint32_t i : M) {
+            cap += dicts[i]->capacity;
+            genes += dicts[i]->n_genes;
+        }
+        for (uint32_t t : ctasks[c]) searched += std::min(tasks[t].a->capacity, tasks[t].b->capacity);
+        if (searched * kGroupGainDen < cap * kGroupGainNum || ctasks[c].size() * 8 < uint64_t(D) * (D - 1)) continue;
+        const pdp_dict *d0 = dicts[M[0]];
+        const AlphaSpec al = alpha_spec(d0->alphabet);
+        const double chance = std::pow(double(al.sigma), -double(d0->k)) * (double(cap) / D) *
+                              (double(cap) / double(std::max<uint64_t>(genes, 1)));
+        if (chance > kGroupChance || entries + cap >= UINT32_MAX) continue;
+        // directed edges: both directions as one edge whose columns give the other's best hits
+        std::vector<uint8_t> map(uint64_t(D) * D, 255);
+        std::vector<std::vector<DevGroupTgt>> out(D);
+        std::vector<uint32_t> deg(D, 0);
+        for (uint32_t t : ctasks[c]) {
+            ++deg[local[ta[t]]];
+            ++deg[local[tb[t]]];
+        }
+        bool ok = true;
+        for (uint32_t t : ctasks[c]) {
+            uint32_t s = local[ta[t]], x = local[tb[t]];
+            uint32_t row = P->ab_row[t], col = P->ba_row[t];
+            const bool both = row != UINT32_MAX && col != UINT32_MAX;
+            // rows at the genome with many more comparisons; else at the group's earlier one, so that a
+            // source's targets follow it in every run of postings
+            const bool turn = both ? deg[x] > 2 * deg[s] || (deg[s] <= 2 * deg[x] && s > x) : row == UINT32_MAX;
+            if (turn) {
+                std::swap(s, x);
+                std::swap(row, col);
+            }
+            uint8_t &m = map[uint64_t(s) * D + x];
+            if (s == x || m != 255 || (both && map[uint64_t(x) * D + s] != 255)) {
+                ok = false;  // a genome with itself, or the same comparison twice
+                break;
+            }
+            m = static_cast<uint8_t>(out[s].size());
+            const pdp_dict *target = dicts[M[x]];
+            out[s].push_back(DevGroupTgt{target->nwin, target->n_genes, row, both ? col : UINT32_MAX, 0});
+        }
+        if (!ok) continue;
+        // items: buckets holding about kGroupTarget entries; a k-mer's identity there is its code's
+        // low word when the codes of every item span less than 2^32
+        const uint64_t nbk = d0->n_buckets;
+        uint64_t nb = std::min<uint64_t>(nbk, std::max<uint64_t>(1, target * nbk / std::max<uint64_t>(cap, 1)));
+        const uint32_t tail = al.bits * (d0->k - d0->lead);
+        auto narrow = [&](uint64_t n) {
+            if (al.bits * d0->k <= 32) return true;
+            if (tail > 32) return false;
+            for (uint64_t b = 0; b < nbk; b += n) {
+                const uint64_t last = std::min(nbk, b + n) - 1;
+                if (bucket_code(d0, last) - bucket_code(d0, b) + (1ull << tail) > (1ull << 32)) return false;
+            }
+            return true;
+        };
+        bool is_narrow = narrow(nb);
+        if (!is_narrow && nb > 1 && narrow(1)) {  // smaller items keep the narrow identity
+            while (!(is_narrow = narrow(nb))) nb = std::max<uint64_t>(1, nb / 2);
+        }
+        runs.push_back({static_cast<uint32_t>(P->gdicts.size()), D, static_cast<uint32_t>(nb), static_cast<uint32_t>(nbk),
+                        !is_narrow});
+        // a tile's rows share one table: fewer rows where rows meet many columns by chance
+        const double want = std::min(std::min<double>(kGroupTileRows, fill_rows), 1100.0 / (chance + 2.0));
+        for (uint32_t i = 0; i < D; ++i) {
+            const pdp_dict *d = dicts[M[i]];
+            DevGroupDict g{};
+            g.ix_code = d->ix_code;
+            g.ix_gene = d->ix_gene;
+            g.ix_cnt = d->ix_cnt;
+            g.ix_dir = d->ix_dir;
+            g.nwin = d->nwin;
+            g.mv_ptr = d->mv_ptr;
+            g.n_genes = d->n_genes;
+            g.n_tgt = static_cast<uint32_t>(out[i].size());
+            g.tgt_base = static_cast<uint32_t>(P->gtgts.size());
+            g.tmap_base = static_cast<uint32_t>(P->tmap.size());
+            g.n_dicts = D;
+            g.k = d->k;
+            for (uint32_t x = 0; x < i; ++x) g.back |= map[uint64_t(i) * D + x] != 255;
+            while ((1ull << P->shape.gene_bits) < d->n_genes) ++P->shape.gene_bits;
+            g.tile_base = static_cast<uint32_t>(P->gtiles.size());
+            g.desc_base = static_cast<uint32_t>(entries);
+            entries += d->capacity;
+            while (g.n_tgt && (2u << g.gshift) * g.n_tgt <= want) ++g.gshift;
+            if (g.n_tgt)
+                for (uint32_t g0 = 0; g0 < d->n_genes; g0 += 1u << g.gshift)
+                    P->gtiles.push_back(DevGroupTile{static_cast<uint32_t>(P->gdicts.size()), g0,
+                                                     std::min<uint32_t>(1u << g.gshift, d->n_genes - g0), 0});
+            P->gtgts.insert(P->gtgts.end(), out[i].begin(), out[i].end());
+            P->tmap.insert(P->tmap.end(), map.begin() + uint64_t(i) * D, map.begin() + uint64_t(i + 1) * D);
+            P->gdicts.push_back(g);
+        }
+        P->shape.gmax_dicts = std::max(P->shape.gmax_dicts, D);
+        for (uint32_t t : ctasks[c]) in_group[t] = 1;
+    }
+    // items of all groups by bucket range (as a fraction of the group's buckets)
+    std::vector<std::pair<double, DevGroupItem>> order[2];
+    for (const Run &r : runs)
+        for (uint64_t b = 0; b < r.n_buckets; b += r.nb)
+            order[r.wide].push_back({double(b) / r.n_buckets,
+                                     DevGroupItem{r.dict0, r.n_dicts, static_cast<uint32_t>(b),
+                                                  static_cast<uint32_t>(std::min<uint64_t>(r.nb, r.n_buckets - b))}});
+    for (int w = 0; w < 2; ++w) {
+        if (runs.size() > 1)
+            std::stable_sort(order[w].begin(), order[w].end(), [](const auto &x, const auto &y) { return x.first < y.first; });
+        for (const auto &x : order[w]) (w ? P->gitems_wide : P->gitems).push_back(x.second);
+    }
+    return entries;
+}
+
 int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *params, pdp_plan **out) {
     if (!out || (n_tasks && !tasks)) return fail(PDP_E_INVAL, "pdp_plan_create: null pointer");
     *out = nullptr;
@@ -399,14 +597,31 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         P->bbh_row.push_back((flags & PDP_TASK_BBH) ? d.bbh_row_base : UINT32_MAX);
         if (bh_rows >= UINT32_MAX) return bail(fail(PDP_E_LIMIT, "plan too large for 32-bit indices"));
     }
+    // Tasks of a group leave the pair path: no join items and no tiles of their own.
+    std::memset(&P->shape, 0, sizeof(P->shape));
+    std::vector<uint8_t> in_group(n_tasks, 0);
+    if (n_tasks >= 3 && !(prm.flags & (PDP_PARAM_PERSISTENT | PDP_PARAM_TWO_PASS))) {
+        P->shape.gentries = plan_groups(P, tasks, n_tasks, is_long, in_group);
+        for (uint32_t t = 0; t < n_tasks; ++t) {
+            if (!in_group[t]) continue;
+            DevTask &d = caller[t];
+            d.a = dev_dict(tasks[t].a);
+            d.b = dev_dict(tasks[t].b);
+            d.flags = 0;
+            d.n_chunks = 0;
+            d.tiles_n[0] = d.tiles_n[1] = 0;
+            d.row_base[0] = P->ab_row[t];
+            d.row_base[1] = P->ba_row[t];
+            any_colmax = true;
+        }
+    }
     // Pass 2, largest tasks first: join items and tiles are numbered in this order, so work-groups
     // (and the persistent kernels' counters) take the long items early.
     // each tile's expected records, the estimate rec_est sums: a region of the one-pass join each
     std::vector<uint64_t> tile_est;
     {
-        uint64_t n_items = 0, n_tiles = 0;
+        uint64_t n_tiles = 0;
         for (const DevTask &d : caller) {
-            n_items += d.n_chunks;
             n_tiles += uint64_t(d.tiles_n[0]) + d.tiles_n[1];
         }
         P->tiles.reserve(n_tiles);
@@ -494,6 +709,16 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         }
     }
     P->shape.n_tasks = n_tasks;
+    P->shape.n_gdicts = static_cast<uint32_t>(P->gdicts.size());
+    P->shape.n_gtgts = static_cast<uint32_t>(P->gtgts.size());
+    P->shape.n_gitems = static_cast<uint32_t>(P->gitems.size());
+    P->shape.n_gitems_wide = static_cast<uint32_t>(P->gitems_wide.size());
+    P->shape.n_gtiles = static_cast<uint32_t>(P->gtiles.size());
+    P->shape.n_tmap = static_cast<uint32_t>(P->tmap.size());
+    P->shape.theta_n = prm.theta_num;
+    P->shape.theta_d = prm.theta_den;
+    P->shape.tau_n = prm.tau_num;
+    P->shape.tau_d = prm.tau_den;
     P->shape.total_chunks = static_cast<uint32_t>(chunks);
     P->shape.total_tiles = static_cast<uint32_t>(P->tiles.size());
     P->shape.total_cells = static_cast<uint32_t>(cells);
@@ -546,6 +771,17 @@ int32_t plan_rebind(pdp_plan *P, const pdp_dict *from, const pdp_dict *to) {
         if (t.a.ix_dir == from->ix_dir) t.a = nd;
         if (t.b.ix_dir == from->ix_dir) t.b = nd;
     }
+    for (DevGroupDict &g : P->gdicts)
+        if (g.ix_dir == from->ix_dir) {
+            g.ix_code = to->ix_code;
+            g.ix_gene = to->ix_gene;
+            g.ix_cnt = to->ix_cnt;
+            g.ix_dir = to->ix_dir;
+            g.nwin = to->nwin;
+            g.mv_ptr = to->mv_ptr;
+        }
+    for (DevGroupTgt &g : P->gtgts)
+        if (g.nwin == from->nwin) g.nwin = to->nwin;
     for (DevItem &it : P->items) {
         it.adir = move(it.adir);
         it.bdir = move(it.bdir);
@@ -563,8 +799,8 @@ int32_t pdp_plan_info_get(const pdp_plan *plan, pdp_plan_info *info) {
     info->bh_rows = plan->shape.bh_rows;
     info->bbh_rows = plan->shape.bbh_rows;
     info->n_tasks = plan->shape.n_tasks;
-    info->join_groups = plan->shape.total_chunks;
-    info->tiles = plan->shape.total_tiles;
+    info->join_groups = plan->shape.total_chunks + plan->shape.n_gitems + plan->shape.n_gitems_wide;
+    info->tiles = plan->shape.total_tiles + plan->shape.n_gtiles;
     info->tile_lds = plan->shape.tile_lds;
     info->long_rows = plan->shape.long_rows;
     info->reserved = 0;
@@ -597,6 +833,18 @@ int32_t pdp_plan_upload(const pdp_plan *plan, void *ws, uint64_t ws_bytes, void 
     }
     if (!plan->tiles.empty()) {
         e = hipMemcpyAsync(w.tiles, plan->tiles.data(), sizeof(DevTile) * plan->tiles.size(), hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return hip_fail(e, "pdp_plan_upload");
+    }
+    if (!plan->gdicts.empty()) {
+        auto put = [&](void *dst, const void *src, uint64_t bytes) {
+            if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+        };
+        put(w.gdicts, plan->gdicts.data(), sizeof(DevGroupDict) * plan->gdicts.size());
+        put(w.gtgts, plan->gtgts.data(), sizeof(DevGroupTgt) * plan->gtgts.size());
+        put(w.gitems, plan->gitems.data(), sizeof(DevGroupItem) * plan->gitems.size());
+        put(w.gitems + plan->gitems.size(), plan->gitems_wide.data(), sizeof(DevGroupItem) * plan->gitems_wide.size());
+        put(w.gtiles, plan->gtiles.data(), sizeof(DevGroupTile) * plan->gtiles.size());
+        put(w.tmap, plan->tmap.data(), plan->tmap.size());
         if (e != hipSuccess) return hip_fail(e, "pdp_plan_upload");
     }
     if (!plan->long_segs.empty()) {

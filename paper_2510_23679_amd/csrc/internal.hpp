@@ -39,6 +39,7 @@ constexpr uint32_t kHashMax = kHashSlots * 3 / 4;  // records one table pass tak
 constexpr uint32_t kDefaultLdsBudget = 8 * kTileCap;
 constexpr uint32_t kMaxTileLds = 160 * 1024 - 4096;  // gfx950 LDS per work-group, less the static part
 constexpr uint32_t kSlab = 4;                // best hits per row kept by the first tile pass
+constexpr uint32_t kCounterWords = 16;       // launch counters in the workspace
 constexpr uint32_t kLongCols = 4096;         // long-gene path: column genes per LDS block (one word per sum)
 
 inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
@@ -141,6 +142,53 @@ struct DevTile {
     uint32_t rcap;
 };
 
+// ------------------------------------------------------------- group path
+// Tasks that compare most pairs of a set of dictionaries (a group) share one pass over all of the
+// group's indexes instead of a join per pair (group.hip).
+constexpr uint32_t kGroupMaxDicts = 255;     // dictionaries of a group (8-bit ids, 255 = no target)
+constexpr uint32_t kGroupCap = 2048;         // index entries a grouping work-group keeps in LDS
+constexpr uint32_t kGroupTarget = 1536;      // entries the plan aims at per item (room for uneven buckets)
+constexpr uint32_t kGroupTileRows = 256;     // (gene, target) rows per tile at most (8-bit row field)
+constexpr uint32_t kGroupCursorStride = 16;  // words between two tiles' cursors: atomics on one line queue up
+constexpr uint32_t kGroupHashBits = 11;      // LDS hash table of a tile: 2^11 (row, column) sums
+constexpr uint32_t kGroupHashSlots = 1u << kGroupHashBits;
+
+// A dictionary of a group.  As a source it owns best-hit rows: n_tgt targets (entries tgt_base..
+// of the target table), its genes in tiles of 2^gshift.
+struct DevGroupDict {
+    const uint64_t *ix_code;
+    const uint32_t *ix_gene;
+    const uint32_t *ix_cnt;
+    const uint32_t *ix_dir;
+    const uint32_t *nwin;
+    const uint32_t *mv_ptr;
+    uint32_t n_genes;
+    uint32_t n_tgt;
+    uint32_t tgt_base;
+    uint32_t tmap_base;  // tmap[tmap_base + x]: target index of the group's dictionary x, 255 = none
+    uint32_t n_dicts;    // dictionaries of the group
+    uint32_t k;
+    uint32_t gshift;
+    uint32_t tile_base;  // first group tile
+    uint32_t desc_base;  // its k-mer descriptors: entry e of its multiplicity vectors owns desc_base + e
+    uint32_t back;       // some target precedes it in the group
+};
+// A directed comparison: rows are the source's genes, columns the target's.
+struct DevGroupTgt {
+    const uint32_t *nwin;  // window counts of the target's genes
+    uint32_t n_genes;
+    uint32_t row_base;     // best-hit rows of the source's genes
+    uint32_t col_base;     // best-hit rows of the target's genes, from the column maxima (UINT32_MAX: none)
+    uint32_t pad;
+};
+// A work item of the grouping kernel: buckets [b0, b0 + nb) of a group's dictionaries.
+struct DevGroupItem {
+    uint32_t dict0, n_dicts, b0, nb;
+};
+struct DevGroupTile {
+    uint32_t dict, g0, ng, pad;
+};
+
 // ------------------------------------------------------------- launchers
 // All return hipError_t of the launch.
 hipError_t launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
@@ -211,6 +259,16 @@ struct PairWs {
     uint4 *cands;
     uint32_t *cand_count;         // counters word 6
     DevLongSeg *long_segs;        // long-gene path, by first row
+    // group path
+    DevGroupDict *gdicts;
+    DevGroupTgt *gtgts;
+    DevGroupItem *gitems;         // narrow items (32-bit identities), then wide ones
+    DevGroupTile *gtiles;
+    uint8_t *tmap;
+    uint32_t *gcursor;            // per group tile: end of its descriptors, start of its inline ones
+    uint2 *gdesc;                 // shared k-mers of each tile's genes
+    uint32_t *gpost;              // postings of the shared k-mers, and their aux words
+    uint32_t *gaux;
 };
 
 struct PlanShape {
@@ -225,6 +283,12 @@ struct PlanShape {
     uint32_t n_long_segs;           // long-gene path: segments and rows
     uint32_t long_rows;
     uint32_t long_lds;              // long-gene path: LDS bytes of a work-group (one or three sums per column)
+    // group path: table sizes, items of each identity width, postings and descriptors held
+    uint32_t n_gdicts, n_gtgts, n_gitems, n_gitems_wide, n_gtiles, n_tmap;
+    uint32_t gmax_dicts;            // most dictionaries of one group
+    uint32_t gene_bits;             // bits of a gene index in the groups' dictionaries
+    uint64_t gentries;              // capacities of all groups' dictionaries
+    uint32_t theta_n, theta_d, tau_n, tau_d;
 };
 // Records the message that pdp_last_error() returns on this thread; returns code.
 int32_t api_fail(int32_t code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
@@ -247,6 +311,9 @@ struct KernelTimer {
 };
 hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp_bbh_out *bbh,
                         pdp_status *st, hipStream_t s, const KernelTimer *timer);
+// The group path's part of a launch: k_group_join (timed as the join) and k_group_tile.
+hipError_t launch_group_join(const PlanShape &p, const PairWs &w, hipStream_t s);
+hipError_t launch_group_tiles(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, hipStream_t s);
 // Families (connected components of the BBH network) into labels[n_nodes].
 hipError_t launch_families(const PlanShape &p, const PairWs &w, const pdp_bbh_out *bbh, const uint32_t *node_a,
                            const uint32_t *node_b, uint32_t n_nodes, uint32_t *labels, pdp_status *st, hipStream_t s);

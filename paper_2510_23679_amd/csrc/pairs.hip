@@ -41,6 +41,7 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "pair_dev.hpp"
 
 namespace pdp {
 
@@ -402,7 +403,7 @@ __global__ void k_pairs_init(pdp_status *st, uint32_t *counters, uint32_t *tile_
         st->needed = 0;
         st->where = ~0ull;
     }
-    if (i0 < 16) counters[i0] = 0;
+    if (i0 < kCounterWords) counters[i0] = 0;
     for (uint32_t t = i0; t < n_tiles; t += gridDim.x * blockDim.x) {
         tile_tot[t] = 0;
         fill[t] = 0;
@@ -806,16 +807,6 @@ __device__ __forceinline__ void fused_chunk(uint32_t chunk, const DevTask *__res
     __syncthreads();
 }
 
-// Work-groups of a launch go to the XCDs in turn (work-group b to XCD b mod 8); item b' below gives
-// XCD x a contiguous run of items.  The plan orders items by leading-letter bucket range across
-// tasks, so an XCD works on one stretch of every genome's index at a time and its L2 serves
-// the same slices to all the genome pairs that read them.
-constexpr uint32_t kXcds = 8;
-__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
-    const uint32_t q = n / kXcds, r = n % kXcds, x = b % kXcds;
-    return x * q + min(x, r) + b / kXcds;  // a bijection of [0, n)
-}
-
 __global__ __launch_bounds__(kJoinThreads) void k_join_fused(const DevTask *__restrict__ tasks,
                                                              const DevItem *__restrict__ items,
                                                              uint32_t *__restrict__ fill,
@@ -887,32 +878,6 @@ __global__ void k_tile_ranges(DevTile *__restrict__ tiles, uint32_t n_tiles, con
     }
 }
 
-__device__ __forceinline__ bool j_greater(uint32_t m1, uint32_t d1, uint32_t m2, uint32_t d2) {
-    return static_cast<uint64_t>(m1) * d2 > static_cast<uint64_t>(m2) * d1;
-}
-__device__ __forceinline__ bool j_equal(uint32_t m1, uint32_t d1, uint32_t m2, uint32_t d2) {
-    return static_cast<uint64_t>(m1) * d2 == static_cast<uint64_t>(m2) * d1;
-}
-
-__device__ __forceinline__ uint32_t rec_min(uint32_t y) { return min(y & 0xFFFFu, y >> 16); }
-
-// Candidate filters on one (row, column) pair: nr / nc windows of the two genes (their
-// lengths are windows + k - 1: a pair with a shared k-mer has windows on both sides),
-// sr / sc the occurrences of the shared k-mers in the row / column gene.  Eq.
-// length_threshold: each length at least theta times the other; Eq. directional_jaccard:
-// sr / nr and sc / nc at least tau.  Exact 64-bit products; a zero denominator is "off".
-__device__ __forceinline__ bool candidate(const DevTask &T, uint32_t nr, uint32_t nc, uint32_t sr, uint32_t sc) {
-    if (T.theta_d) {
-        const uint64_t lr = nr + T.a.k - 1, lc = nc + T.a.k - 1;
-        if (lr * T.theta_d < uint64_t(T.theta_n) * lc || lc * T.theta_d < uint64_t(T.theta_n) * lr) return false;
-    }
-    if (T.tau_d) {
-        if (uint64_t(sr) * T.tau_d < uint64_t(T.tau_n) * nr || uint64_t(sc) * T.tau_d < uint64_t(T.tau_n) * nc)
-            return false;
-    }
-    return true;
-}
-
 // Static LDS of a tile work-group.
 struct TileLds {
     uint32_t rowlen[kTileMaxRows];    // distinct columns per row (sorted path)
@@ -926,30 +891,6 @@ struct TileLds {
     uint32_t next;
     uint32_t cand_n, cand_base;  // column candidates of a row group (column maxima)
 };
-
-// Column maxima: the scratch of the tasks with kTaskColmax.
-struct ColWs {
-    unsigned long long *key;  // per best-hit row (a BA row): the running maximum key of its column
-    uint4 *cands;             // pairs that reached their column's running maximum: (BA row, a, m, d)
-    uint32_t *count;
-    uint64_t cap;
-};
-
-// Key of J = m/d that orders values exactly: the bits of the correctly rounded double m / d.
-// Distinct values differ by at least 1/(d1 d2) > 2^-34 (d < 2^17), far more than the rounding
-// error (2^-53 relative, values at most 1), so their quotients keep their order; equal values
-// round alike; positive doubles order as their bit patterns.  (An integer key floor(m 2^42 / d)
-// orders them too, but its 64-bit division is a long instruction sequence per pair.)
-__device__ __forceinline__ unsigned long long colmax_key(uint32_t m, uint32_t d) {
-    return static_cast<unsigned long long>(__double_as_longlong(static_cast<double>(m) / static_cast<double>(d)));
-}
-
-// Raises the column's running maximum by the pair's key; true when the pair is at or above
-// the maximum so far (the final maximum is never below it, so no final best hit is missed).
-__device__ __forceinline__ bool colmax_raise(const ColWs &cw, uint32_t ba_row, uint32_t m, uint32_t d) {
-    const unsigned long long k = colmax_key(m, d);
-    return k >= atomicMax(&cw.key[ba_row], k);
-}
 
 // Best hits of one row, given its candidates one lane-chunk at a time in ascending
 // column order: cand(e, &c, &m, &d) yields the column, the sum of minima and the sum of
@@ -1967,8 +1908,8 @@ uint64_t pair_ws_bytes(const PlanShape &p) {
     s += align_up(sizeof(DevTile) * std::max<uint64_t>(p.total_tiles, 1), A);
     s += align_up(sizeof(DevItem) * std::max<uint64_t>(p.total_chunks, 1), A);
     s += align_up(4 * std::max<uint64_t>(p.n_tasks, 1), A);
-    s += align_up(8 * std::max<uint64_t>(p.rec_cap, 1), A);
-    s += align_up(64, A);
+    s += align_up(8 * std::max<uint64_t>(p.total_tiles ? p.rec_cap : 0, 1), A);
+    s += align_up(4 * kCounterWords, A);
     s += align_up(4 * (uint64_t(p.total_cells) + 1), A);
     s += align_up(4 * (uint64_t(p.total_tiles) + 1), A);  // records per tile (join), consumed by the write pass
     s += align_up(4 * (uint64_t(p.total_tiles) + 1), A);  // scanned: each tile's first record
@@ -1982,6 +1923,13 @@ uint64_t pair_ws_bytes(const PlanShape &p) {
     s += align_up(4 * colrows, A);                                  // big-row cursors
     s += align_up(16 * std::max<uint64_t>(p.colmax ? p.cand_cap : 0, 1), A);  // candidates
     s += align_up(sizeof(DevLongSeg) * std::max<uint64_t>(p.n_long_segs, 1), A);
+    if (p.n_gdicts) {
+        s += align_up(sizeof(DevGroupDict) * uint64_t(p.n_gdicts), A) + align_up(sizeof(DevGroupTgt) * uint64_t(p.n_gtgts), A);
+        s += align_up(sizeof(DevGroupItem) * (uint64_t(p.n_gitems) + p.n_gitems_wide), A);
+        s += align_up(sizeof(DevGroupTile) * std::max<uint64_t>(p.n_gtiles, 1), A) + align_up(p.n_tmap, A);
+        s += align_up(4 * kGroupCursorStride * (uint64_t(p.n_gtiles) + 1), A);
+        s += align_up(8 * p.gentries, A) + 2 * align_up(4 * p.gentries, A);
+    }
     return s;
 }
 
@@ -1998,8 +1946,8 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
     w.tiles = reinterpret_cast<DevTile *>(take(sizeof(DevTile) * std::max<uint64_t>(p.total_tiles, 1)));
     w.items = reinterpret_cast<DevItem *>(take(sizeof(DevItem) * std::max<uint64_t>(p.total_chunks, 1)));
     w.order = reinterpret_cast<uint32_t *>(take(4 * std::max<uint64_t>(p.n_tasks, 1)));
-    w.recs = reinterpret_cast<uint2 *>(take(8 * std::max<uint64_t>(p.rec_cap, 1)));
-    w.counters = reinterpret_cast<unsigned long long *>(take(64));
+    w.recs = reinterpret_cast<uint2 *>(take(8 * std::max<uint64_t>(p.total_tiles ? p.rec_cap : 0, 1)));
+    w.counters = reinterpret_cast<unsigned long long *>(take(4 * kCounterWords));
     w.overflow_count = reinterpret_cast<uint32_t *>(w.counters) + 2;
     w.next_join = reinterpret_cast<uint32_t *>(w.counters) + 3;
     w.next_tile = reinterpret_cast<uint32_t *>(w.counters) + 4;
@@ -2020,6 +1968,18 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
     w.cands = reinterpret_cast<uint4 *>(take(16 * std::max<uint64_t>(p.colmax ? p.cand_cap : 0, 1)));
     w.cand_count = reinterpret_cast<uint32_t *>(w.counters) + 6;
     w.long_segs = reinterpret_cast<DevLongSeg *>(take(sizeof(DevLongSeg) * std::max<uint64_t>(p.n_long_segs, 1)));
+    w.gdicts = nullptr;
+    if (p.n_gdicts) {
+        w.gdicts = reinterpret_cast<DevGroupDict *>(take(sizeof(DevGroupDict) * uint64_t(p.n_gdicts)));
+        w.gtgts = reinterpret_cast<DevGroupTgt *>(take(sizeof(DevGroupTgt) * uint64_t(p.n_gtgts)));
+        w.gitems = reinterpret_cast<DevGroupItem *>(take(sizeof(DevGroupItem) * (uint64_t(p.n_gitems) + p.n_gitems_wide)));
+        w.gtiles = reinterpret_cast<DevGroupTile *>(take(sizeof(DevGroupTile) * std::max<uint64_t>(p.n_gtiles, 1)));
+        w.tmap = reinterpret_cast<uint8_t *>(take(p.n_tmap));
+        w.gcursor = reinterpret_cast<uint32_t *>(take(4 * kGroupCursorStride * (uint64_t(p.n_gtiles) + 1)));
+        w.gdesc = reinterpret_cast<uint2 *>(take(8 * p.gentries));
+        w.gpost = reinterpret_cast<uint32_t *>(take(4 * p.gentries));
+        w.gaux = reinterpret_cast<uint32_t *>(take(4 * p.gentries));
+    }
     return w;
 }
 
@@ -2042,6 +2002,10 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         PDP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(w.colkey), 2 * (uint64_t(p.bh_rows) + 1), 0u, s));
         PDP_TRY(launch_fill_u32(w.colcursor, uint64_t(p.bh_rows) + 1, 0u, s));
     }
+    if (p.n_gdicts) {  // the group path's join; timed as the join with the pair path's, when a plan has both
+        PDP_TRY(mark(PDP_KERNEL_JOIN, true));
+        PDP_TRY(launch_group_join(p, w, s));
+    }
     // the join: the one-pass kernel (PDP_KERNEL_JOIN), then its back-up, the two-pass join gated on
     // the fallback flag (PDP_KERNEL_JOIN_BACKUP); with PDP_PARAM_TWO_PASS the two passes are the join
     if (p.total_chunks) {
@@ -2051,7 +2015,7 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         dim3 g2 = pers ? dim3(std::min(p.join_grid, (p.total_chunks + kClaimJoin - 1) / kClaimJoin)) : dim3(p.total_chunks);
         if (p.fused) {
             const uint32_t dyn = 8 * p.join_tiles;
-            PDP_TRY(mark(PDP_KERNEL_JOIN, true));
+            if (!p.n_gdicts) PDP_TRY(mark(PDP_KERNEL_JOIN, true));
             if (pers)
                 hipLaunchKernelGGL(k_join_fused_persistent,
                                    dim3(std::min(p.join_grid, (p.total_chunks + kClaimJoin - 1) / kClaimJoin)),
@@ -2091,8 +2055,8 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
             PDP_TRY(mark(PDP_KERNEL_JOIN, false));
             PDP_TRY(mark(PDP_KERNEL_JOIN_BACKUP, true));
         }
-    } else {  // no join items (every task on the long-gene path): empty intervals for the join timers
-        PDP_TRY(mark(PDP_KERNEL_JOIN, true));
+    } else {  // no join items (every task on the long-gene or the group path)
+        if (!p.n_gdicts) PDP_TRY(mark(PDP_KERNEL_JOIN, true));
         PDP_TRY(mark(PDP_KERNEL_JOIN, false));
         PDP_TRY(mark(PDP_KERNEL_BUCKET, true));
         PDP_TRY(mark(PDP_KERNEL_BUCKET, false));
@@ -2129,6 +2093,7 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
                                w.overflow_tiles, w.overflow_count, cmx);
         PDP_TRY(hipGetLastError());
     }
+    PDP_TRY(launch_group_tiles(p, w, bh, s));
     const uint32_t col_grid = std::max<uint32_t>(1, std::min<uint32_t>(2048, static_cast<uint32_t>((p.cand_cap + 255) / 256)));
     if (p.colmax) {
         hipLaunchKernelGGL(k_colmax_rows, dim3(col_grid), dim3(256), 0, s, cmx, bh->ptr, w.slab, st);
