@@ -97,20 +97,66 @@ __device__ __forceinline__ void wave_lds_sync() {
 __device__ __forceinline__ uint32_t xor_lanes32(uint32_t x, uint32_t lj) {
     const int v = static_cast<int>(x);
     switch (lj) {
-        case 1: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false));
-        case 2: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false));
-        case 8: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false));
+        case 1: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true));
+        case 2: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true));
+        case 8: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true));
         case 4: return static_cast<uint32_t>(__builtin_amdgcn_ds_swizzle(v, 0x101F));
         case 16: return static_cast<uint32_t>(__builtin_amdgcn_ds_swizzle(v, 0x401F));
         default: return __shfl_xor(x, lj, kWave);
     }
 }
-// 32-bit keys only: with 64-bit keys, and in the work-group sort (whose distance is not a
-// compile-time constant), the variants raised register use enough to cost occupancy.
-template <typename K>
-__device__ __forceinline__ K xor_lanes(K x, uint32_t lj) {
-    if constexpr (sizeof(K) == 4) return xor_lanes32(x, lj);
-    else return __shfl_xor(x, lj, kWave);
+// The middle of three values (v_med3_u32): with bound 0 the smaller of a and b, with all ones the
+// larger, so a comparator whose direction depends on the lane takes one instruction per output.
+__device__ __forceinline__ uint32_t pick(uint32_t a, uint32_t b, uint32_t bound) {
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(bound));  // asm: the compiler does not end on a network of the min / max form
+    return r;
+}
+// All ones in lanes with bit b of the lane number set.
+__device__ __forceinline__ uint32_t lane_bit_mask(uint32_t b) {
+    return static_cast<uint32_t>(static_cast<int32_t>(lane_id() << (31u - b)) >> 31);
+}
+constexpr uint32_t log2_of(uint32_t x) { return x <= 1 ? 0 : 1 + log2_of(x >> 1); }
+
+// The same network as below for 32-bit keys.  A comparator keeps the minimum where the lane bits of
+// its distance and of its direction agree: their masks' exclusive or is the bound that picks it.
+// 45 stages of 512 keys: 66 instructions a key where compare, select and exchange took ~115.
+template <uint32_t E>
+__device__ __forceinline__ void wave_bitonic_sort(uint32_t (&key)[E]) {
+    constexpr uint32_t N = kWave * E;
+    uint32_t bit[6];
+#pragma unroll
+    for (uint32_t b = 0; b < 6; ++b) bit[b] = lane_bit_mask(b);
+#pragma unroll
+    for (uint32_t size = 2; size <= N; size <<= 1) {
+        // all ones in lanes that sort this run downwards (the last run goes up everywhere)
+        const uint32_t down = size < E || size == N ? 0u : bit[log2_of(size / E)];
+#pragma unroll
+        for (uint32_t j = size >> 1; j > 0; j >>= 1) {
+            if (j < E) {
+#pragma unroll
+                for (uint32_t e = 0; e < E; ++e) {
+                    if (e & j) continue;
+                    const uint32_t a = key[e], b = key[e | j];
+                    if (size < E && (e & size)) {
+                        key[e] = max(a, b);
+                        key[e | j] = min(a, b);
+                    } else if (size < E || size == N) {
+                        key[e] = min(a, b);
+                        key[e | j] = max(a, b);
+                    } else {
+                        key[e] = pick(a, b, down);
+                        key[e | j] = pick(a, b, ~down);
+                    }
+                }
+            } else {
+                const uint32_t lj = j / E;
+                const uint32_t bound = bit[log2_of(lj)] ^ down;
+#pragma unroll
+                for (uint32_t e = 0; e < E; ++e) key[e] = pick(key[e], xor_lanes32(key[e], lj), bound);
+            }
+        }
+    }
 }
 
 // Ascending bitonic sort of kWave * E keys, E per lane in blocked order (lane l holds
@@ -139,7 +185,7 @@ __device__ __forceinline__ void wave_bitonic_sort(K (&key)[E]) {
                 const bool lower = (l & lj) == 0;
 #pragma unroll
                 for (uint32_t e = 0; e < E; ++e) {
-                    const K o = xor_lanes(key[e], lj);
+                    const K o = __shfl_xor(key[e], lj, kWave);
                     const bool keep_min = lower == (((l * E + e) & size) == 0);
                     const K mn = o < key[e] ? o : key[e], mx = o < key[e] ? key[e] : o;
                     key[e] = keep_min ? mn : mx;
@@ -252,7 +298,8 @@ __device__ __forceinline__ void mv_wave_gene(const DevBuild &B, const uint8_t *s
     K key[E];
     // the lane's windows p0 .. p0+E-1 are consecutive
     window_keys<E, K, B20>(sym, lane * E, nw, k, B.bits, key);
-    wave_bitonic_sort<E, K>(key);
+    if constexpr (sizeof(K) == 4) wave_bitonic_sort<E>(key);
+    else wave_bitonic_sort<E, K>(key);
     const K before = __shfl_up(key[E - 1], 1, kWave);
     uint32_t hmask = 0, nh = 0;
 #pragma unroll
@@ -355,6 +402,10 @@ __global__ __launch_bounds__(kMvThreads) void k_mv_wave(const DevBuild *__restri
     if (lane == 0) dcnt[G] = total;
 }
 
+// The smaller or the larger of two keys.
+__device__ __forceinline__ uint32_t keep(uint32_t a, uint32_t b, bool smaller) { return pick(a, b, smaller ? 0u : ~0u); }
+__device__ __forceinline__ uint64_t keep(uint64_t a, uint64_t b, bool smaller) { return (a < b) == smaller ? a : b; }
+
 // Ascending bitonic sort of kMvThreads * E keys by one work-group, E per thread in blocked
 // order (thread t holds elements t*E .. t*E+E-1): comparators inside a thread swap
 // registers, those inside a wave pair lanes by shuffles, and only those across waves go
@@ -370,26 +421,16 @@ __device__ __forceinline__ void block_bitonic_sort(K (&key)[E], K *xch) {
 #pragma unroll
             for (uint32_t e = 0; e < E; ++e) xch[e * kMvThreads + t] = key[e];
             __syncthreads();
-            const bool lower = (t & lj) == 0;
+            const bool keep_min = ((t & lj) == 0) == ((t * E & size) == 0);  // size > E: the same for all e
 #pragma unroll
-            for (uint32_t e = 0; e < E; ++e) {
-                const K o = xch[e * kMvThreads + (t ^ lj)];
-                const bool keep_min = lower == (((t * E + e) & size) == 0);
-                const K mn = o < key[e] ? o : key[e], mx = o < key[e] ? key[e] : o;
-                key[e] = keep_min ? mn : mx;
-            }
+            for (uint32_t e = 0; e < E; ++e) key[e] = keep(key[e], xch[e * kMvThreads + (t ^ lj)], keep_min);
             __syncthreads();
         }
         for (uint32_t j = min(size >> 1, kWave * E / 2); j >= E; j >>= 1) {  // partner lane in this wave
             const uint32_t lj = j / E;
-            const bool lower = (t & lj) == 0;
+            const bool keep_min = ((t & lj) == 0) == ((t * E & size) == 0);
 #pragma unroll
-            for (uint32_t e = 0; e < E; ++e) {
-                const K o = __shfl_xor(key[e], lj, kWave);
-                const bool keep_min = lower == (((t * E + e) & size) == 0);
-                const K mn = o < key[e] ? o : key[e], mx = o < key[e] ? key[e] : o;
-                key[e] = keep_min ? mn : mx;
-            }
+            for (uint32_t e = 0; e < E; ++e) key[e] = keep(key[e], __shfl_xor(key[e], lj, kWave), keep_min);
         }
 #pragma unroll
         for (uint32_t j = E / 2; j > 0; j >>= 1) {  // partner in this thread's registers
@@ -399,9 +440,8 @@ __device__ __forceinline__ void block_bitonic_sort(K (&key)[E], K *xch) {
                 if (e & j) continue;
                 const bool asc = ((t * E + e) & size) == 0;
                 const K a = key[e], b = key[e | j];
-                const bool sw = asc ? a > b : a < b;
-                key[e] = sw ? b : a;
-                key[e | j] = sw ? a : b;
+                key[e] = keep(a, b, asc);
+                key[e | j] = keep(a, b, !asc);
             }
         }
     }
