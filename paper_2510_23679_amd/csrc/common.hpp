@@ -59,9 +59,8 @@ __device__ __forceinline__ uint32_t sym_in(uint32_t byte, uint32_t bits) { retur
 // number.
 __device__ __forceinline__ uint32_t bucket_of(uint64_t code, uint32_t k, uint32_t lead, uint32_t bits) {
     if (bits == 2u) return static_cast<uint32_t>(code >> (2u * (k - lead)));
-    uint32_t b = 0;
-    for (uint32_t i = 0; i < lead; ++i) b = b * 20u + static_cast<uint32_t>((code >> (5u * (k - 1u - i))) & 31u);
-    return b;
+    const uint32_t x = static_cast<uint32_t>(code >> (5u * (k - lead)));  // at most 4 letters: no loop over them
+    return (x & 31u) + ((x >> 5) & 31u) * 20u + ((x >> 10) & 31u) * 400u + ((x >> 15) & 31u) * 8000u;
 }
 
 // Loads and stores issued as global (not flat) accesses, for pointers read out of memory (a

@@ -27,6 +27,7 @@
 // Genes and buckets of all genomes of a call are numbered consecutively; a
 // work-group finds its genome by binary search over the per-genome bases.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "internal.hpp"
@@ -284,15 +285,32 @@ constexpr uint32_t kMvWaveEMax = 16;
 constexpr uint32_t kMvWaveCap = kWave * kMvWaveEMax;  // windows a wave sorts in registers
 constexpr uint32_t kMvWaves = kMvThreads / kWave;
 
+constexpr uint32_t kMvHalf = 512;  // sorted keys a wave passes through LDS at a time
+
+// A key of the narrow form (32 bits: base-20 value or code) from a code, and back.
+__device__ __forceinline__ uint32_t code_to_base20(uint64_t c, uint32_t k) {
+    uint32_t v = 0;
+    for (uint32_t i = 0; i < k; ++i) v = v * 20u + static_cast<uint32_t>((c >> (5u * (k - 1u - i))) & 31u);
+    return v;
+}
+__device__ __forceinline__ uint32_t code_to_key(const DevBuild &B, uint64_t c) {
+    return base20_keys(B) ? code_to_base20(c, B.k) : static_cast<uint32_t>(c);
+}
+__device__ __forceinline__ uint64_t key_to_code(const DevBuild &B, uint32_t key) {
+    return base20_keys(B) ? base20_to_code(key, B.k) : key;
+}
+
 // One gene's multiplicity vector by one wave: codes E per lane in registers, sorted by the
-// wave's bitonic network (E = 4, 8 or 16: the smallest that holds the gene), then run
-// heads ranked by a wave scan; head positions in LDS give the run lengths.  sym holds the
-// gene's residue symbols, hp kWave*E+1 slots.
+// wave's bitonic network (E = 4, 8 or 16: the smallest that holds the gene).  The sorted keys then
+// pass through LDS (kMvHalf at a time) so that consecutive lanes hold consecutive keys: run heads
+// are ranked by ballots and the keys and counts go out in whole cache lines (each lane storing its
+// own run of the blocked order touches 64 lines per store).  buf: kMvHalf keys over the gene's
+// symbols; hp: kWave*E+1 head positions.
 // K: the key type, 32 bits when the codes fit (bits * k <= 32), halving the shuffles.
-// B20: base-20 keys (base20_keys).
-template <uint32_t E, typename K, bool B20 = false>
-__device__ __forceinline__ void mv_wave_gene(const DevBuild &B, const uint8_t *sym, uint16_t *hp, uint64_t o,
-                                             uint32_t nw, uint32_t *cnt_out) {
+// B20: base-20 keys (base20_keys).  NARROW: the slots take 32-bit keys instead of codes.
+template <uint32_t E, typename K, bool B20, bool NARROW>
+__device__ __forceinline__ void mv_wave_gene(const DevBuild &B, uint8_t *sym, uint16_t *hp, uint64_t o, uint32_t nw,
+                                             uint32_t *cnt_out) {
     const uint32_t lane = lane_id();
     const uint32_t k = B.k;
     K key[E];
@@ -300,34 +318,40 @@ __device__ __forceinline__ void mv_wave_gene(const DevBuild &B, const uint8_t *s
     window_keys<E, K, B20>(sym, lane * E, nw, k, B.bits, key);
     if constexpr (sizeof(K) == 4) wave_bitonic_sort<E>(key);
     else wave_bitonic_sort<E, K>(key);
-    const K before = __shfl_up(key[E - 1], 1, kWave);
-    uint32_t hmask = 0, nh = 0;
+    constexpr uint32_t kRounds = kWave * E > kMvHalf ? kWave * E / kMvHalf : 1;
+    constexpr uint32_t kLanes = kWave / kRounds;  // lanes whose keys make one round
+    K *buf = reinterpret_cast<K *>(sym);
+    uint32_t total = 0;
+    K last = 0;
 #pragma unroll
-    for (uint32_t e = 0; e < E; ++e) {
-        const uint32_t i = lane * E + e;
-        const K prev = e ? key[e - 1] : before;
-        const bool h = i < nw && (i == 0 || key[e] != prev);
-        hmask |= static_cast<uint32_t>(h) << e;
-        nh += h;
+    for (uint32_t h = 0; h < kRounds; ++h) {
+        if (h * kMvHalf >= nw) break;  // uniform
+        wave_lds_sync();
+        if (lane / kLanes == h) {
+#pragma unroll
+            for (uint32_t e = 0; e < E; ++e) buf[(lane % kLanes) * E + e] = key[e];
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t q = 0; q < kLanes * E / kWave; ++q) {
+            const uint32_t x = q * kWave + lane, i = h * kMvHalf + x;
+            const K c = buf[x], prev = x ? buf[x - 1] : last;
+            const bool head = i < nw && (i == 0 || c != prev);
+            const uint64_t mask = __ballot(head);
+            const uint32_t r = total + mask_below(mask);
+            if (head) {
+                hp[r] = static_cast<uint16_t>(i);
+                if constexpr (NARROW) store_global(reinterpret_cast<uint32_t *>(B.slot_code) + o + r, static_cast<uint32_t>(c));
+                else store_global(B.slot_code + o + r, key_code<B20>(c, k));
+            }
+            total += static_cast<uint32_t>(__popcll(mask));
+        }
+        last = buf[kLanes * E - 1];
     }
-    const uint32_t incl = wave_inclusive_sum(nh);
-    const uint32_t total = __shfl(incl, kWave - 1, kWave);
-    uint32_t r = incl - nh;
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e)
-        if ((hmask >> e) & 1u) hp[r++] = static_cast<uint16_t>(lane * E + e);
     if (lane == 0) hp[total] = static_cast<uint16_t>(nw);
     wave_lds_sync();
-    uint64_t *slot_code = B.slot_code + o;
-    uint32_t *slot_cnt = B.slot_cnt + o;
-    r = incl - nh;
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e) {
-        if (!((hmask >> e) & 1u)) continue;
-        store_global(slot_code + r, key_code<B20>(key[e], k));
-        store_global(slot_cnt + r, static_cast<uint32_t>(hp[r + 1]) - hp[r]);
-        ++r;
-    }
+    for (uint32_t r = lane; r < total; r += kWave)
+        store_global(B.slot_cnt + o + r, static_cast<uint32_t>(hp[r + 1]) - hp[r]);
     *cnt_out = total;
 }
 
@@ -340,7 +364,10 @@ __global__ __launch_bounds__(kMvThreads) void k_mv_wave(const DevBuild *__restri
                                                         uint32_t total_genes, uint32_t *__restrict__ dcnt,
                                                         uint64_t *__restrict__ mid_list, uint64_t *__restrict__ long_list,
                                                         uint32_t stride, uint32_t *__restrict__ counters) {
-    __shared__ uint8_t sym_all[kMvWaves][kMvWaveCap + kKMaxAll];
+    // symbols, then sorted keys
+    constexpr uint32_t kBuf = (kMvHalf * (NARROW ? 4 : 8) + 15) / 16 * 16;
+    static_assert(kBuf >= kMvWaveCap + kKMaxAll, "a gene's symbols fit");
+    __shared__ __align__(16) uint8_t sym_all[kMvWaves][kBuf];
     __shared__ uint16_t hp_all[kMvWaves][kMvWaveCap + 1];
     const uint32_t w = threadIdx.x / kWave, lane = lane_id();
     const uint32_t G = blockIdx.x * kMvWaves + w;
@@ -385,18 +412,18 @@ __global__ __launch_bounds__(kMvThreads) void k_mv_wave(const DevBuild *__restri
     wave_lds_sync();
     uint32_t total;
     if (B.bits * B.k <= 32) {  // uniform per wave
-        if (nw <= kWave * 4) mv_wave_gene<4, uint32_t>(B, sym, hp_all[w], o, nw, &total);
-        else if (nw <= kWave * 8) mv_wave_gene<8, uint32_t>(B, sym, hp_all[w], o, nw, &total);
-        else mv_wave_gene<16, uint32_t>(B, sym, hp_all[w], o, nw, &total);
+        if (nw <= kWave * 4) mv_wave_gene<4, uint32_t, false, NARROW>(B, sym, hp_all[w], o, nw, &total);
+        else if (nw <= kWave * 8) mv_wave_gene<8, uint32_t, false, NARROW>(B, sym, hp_all[w], o, nw, &total);
+        else mv_wave_gene<16, uint32_t, false, NARROW>(B, sym, hp_all[w], o, nw, &total);
     } else if (base20_keys(B)) {
-        if (nw <= kWave * 4) mv_wave_gene<4, uint32_t, true>(B, sym, hp_all[w], o, nw, &total);
-        else if (nw <= kWave * 8) mv_wave_gene<8, uint32_t, true>(B, sym, hp_all[w], o, nw, &total);
-        else mv_wave_gene<16, uint32_t, true>(B, sym, hp_all[w], o, nw, &total);
+        if (nw <= kWave * 4) mv_wave_gene<4, uint32_t, true, NARROW>(B, sym, hp_all[w], o, nw, &total);
+        else if (nw <= kWave * 8) mv_wave_gene<8, uint32_t, true, NARROW>(B, sym, hp_all[w], o, nw, &total);
+        else mv_wave_gene<16, uint32_t, true, NARROW>(B, sym, hp_all[w], o, nw, &total);
     } else {
         if constexpr (!NARROW) {
-            if (nw <= kWave * 4) mv_wave_gene<4, uint64_t>(B, sym, hp_all[w], o, nw, &total);
-            else if (nw <= kWave * 8) mv_wave_gene<8, uint64_t>(B, sym, hp_all[w], o, nw, &total);
-            else mv_wave_gene<16, uint64_t>(B, sym, hp_all[w], o, nw, &total);
+            if (nw <= kWave * 4) mv_wave_gene<4, uint64_t, false, false>(B, sym, hp_all[w], o, nw, &total);
+            else if (nw <= kWave * 8) mv_wave_gene<8, uint64_t, false, false>(B, sym, hp_all[w], o, nw, &total);
+            else mv_wave_gene<16, uint64_t, false, false>(B, sym, hp_all[w], o, nw, &total);
         }
     }
     if (lane == 0) dcnt[G] = total;
@@ -453,7 +480,7 @@ __device__ __forceinline__ void block_bitonic_sort(K (&key)[E], K *xch) {
 // run heads ranked by a work-group scan give the multiplicity vector.  The symbols, the
 // sort's exchange area and the head positions share one LDS array.
 // One gene of k_mv_mid: len letters at offset o, nw <= kMvThreads * E windows; K as in the wave kernel.
-template <uint32_t E, typename K, bool B20 = false>
+template <uint32_t E, typename K, bool B20, bool NARROW>
 __device__ __forceinline__ void mid_gene(const DevBuild &B, uint32_t G, uint64_t o, uint32_t len, uint32_t nw,
                                          uint64_t *xch64, K *s_last, uint32_t *tmp, uint32_t *__restrict__ dcnt) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
@@ -500,21 +527,48 @@ __device__ __forceinline__ void mid_gene(const DevBuild &B, uint32_t G, uint64_t
     }
     uint32_t total;
     const uint32_t r0 = block_exclusive_scan<kMvThreads>(nh, tmp, &total);
-    uint32_t r = r0;
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e)
-        if ((hmask >> e) & 1u) hp[r++] = static_cast<uint16_t>(tid * E + e);
-    if (tid == 0) hp[total] = static_cast<uint16_t>(nw);
-    __syncthreads();
-    uint64_t *slot_code = B.slot_code + o;
     uint32_t *slot_cnt = B.slot_cnt + o;
-    r = r0;
+    if constexpr (NARROW) {
+        // as in the wave kernel: the keys back through LDS, so that the stores are whole lines; the
+        // wave's first rank comes from the scan
+        hp = reinterpret_cast<uint16_t *>(xch + kMvThreads * E);
 #pragma unroll
-    for (uint32_t e = 0; e < E; ++e) {
-        if (!((hmask >> e) & 1u)) continue;
-        store_global(slot_code + r, key_code<B20>(key[e], k));
-        store_global(slot_cnt + r, static_cast<uint32_t>(hp[r + 1]) - hp[r]);
-        ++r;
+        for (uint32_t e = 0; e < E; ++e) xch[tid * E + e] = key[e];
+        uint32_t r = __shfl(r0, 0, kWave);
+        __syncthreads();
+        uint32_t *slot_key = reinterpret_cast<uint32_t *>(B.slot_code) + o;
+        for (uint32_t q = 0; q < E; ++q) {
+            const uint32_t i = w * kWave * E + q * kWave + lane;
+            const K c = xch[i];
+            const bool head = i < nw && (i == 0 || c != xch[i - 1]);
+            const uint64_t mask = __ballot(head);
+            const uint32_t at = r + mask_below(mask);
+            if (head) {
+                hp[at] = static_cast<uint16_t>(i);
+                store_global(slot_key + at, c);
+            }
+            r += static_cast<uint32_t>(__popcll(mask));
+        }
+        if (tid == 0) hp[total] = static_cast<uint16_t>(nw);
+        __syncthreads();
+        for (uint32_t x = tid; x < total; x += kMvThreads)
+            store_global(slot_cnt + x, static_cast<uint32_t>(hp[x + 1]) - hp[x]);
+    } else {
+        uint32_t r = r0;
+#pragma unroll
+        for (uint32_t e = 0; e < E; ++e)
+            if ((hmask >> e) & 1u) hp[r++] = static_cast<uint16_t>(tid * E + e);
+        if (tid == 0) hp[total] = static_cast<uint16_t>(nw);
+        __syncthreads();
+        uint64_t *slot_code = B.slot_code + o;
+        r = r0;
+#pragma unroll
+        for (uint32_t e = 0; e < E; ++e) {
+            if (!((hmask >> e) & 1u)) continue;
+            store_global(slot_code + r, key_code<B20>(key[e], k));
+            store_global(slot_cnt + r, static_cast<uint32_t>(hp[r + 1]) - hp[r]);
+            ++r;
+        }
     }
     if (tid == 0) dcnt[G] = total;
     __syncthreads();  // LDS takes the next gene
@@ -525,8 +579,8 @@ __global__ __launch_bounds__(kMvThreads) void k_mv_mid(const DevBuild *__restric
                                                        const uint64_t *__restrict__ list,
                                                        const uint32_t *__restrict__ count) {
     constexpr uint32_t N = kMvThreads * E;
-    static_assert(N + kKMaxAll <= 8 * N && N + 1 <= 4 * N && N <= 65535, "symbols and u16 head positions fit");
-    __shared__ uint64_t xch[N];
+    static_assert(N + kKMaxAll <= 6 * N && N + 1 <= 4 * N && N <= 65535, "symbols and u16 head positions fit");
+    __shared__ uint64_t xch[NARROW ? N * 3 / 4 + 1 : N];  // NARROW: N keys and N + 1 head positions
     __shared__ uint64_t s_last[kMvWaves];
     __shared__ uint32_t tmp[kMvWaves + 1];
     const uint32_t n_items = *count;
@@ -538,17 +592,18 @@ __global__ __launch_bounds__(kMvThreads) void k_mv_mid(const DevBuild *__restric
         const uint32_t len = static_cast<uint32_t>(B.off[g + 1] - o);
         const uint32_t nw = len - B.k + 1;  // k_mv_wave queued this gene for nw <= kMvThreads * E
         if (B.bits * B.k <= 32) {  // uniform per work-group
-            mid_gene<E, uint32_t>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp, dcnt);
+            mid_gene<E, uint32_t, false, NARROW>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp, dcnt);
         } else if (base20_keys(B)) {
-            mid_gene<E, uint32_t, true>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp,
+            mid_gene<E, uint32_t, true, NARROW>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp,
                                         dcnt);
         } else {
-            if constexpr (!NARROW) mid_gene<E, uint64_t>(B, B.gene_base + g, o, len, nw, xch, s_last, tmp, dcnt);
+            if constexpr (!NARROW) mid_gene<E, uint64_t, false, false>(B, B.gene_base + g, o, len, nw, xch, s_last, tmp, dcnt);
         }
     }
 }
 
 // Genes with more windows than fit in LDS: same steps, codes sorted in global memory.
+template <bool NARROW>
 __global__ __launch_bounds__(kMvThreads) void k_mv_long(const DevBuild *__restrict__ table, uint32_t *__restrict__ dcnt,
                                                         const uint64_t *__restrict__ long_list,
                                                         const uint32_t *__restrict__ counters) {
@@ -591,7 +646,8 @@ __global__ __launch_bounds__(kMvThreads) void k_mv_long(const DevBuild *__restri
                 const uint64_t c = w[i];
                 uint32_t end = i + 1;
                 while (end < nw && w[end] == c) ++end;
-                B.slot_code[o + base + r] = c;
+                if constexpr (NARROW) reinterpret_cast<uint32_t *>(B.slot_code)[o + base + r] = code_to_key(B, c);
+                else B.slot_code[o + base + r] = c;
                 B.slot_cnt[o + base + r] = end - i;
             }
             base += total;
@@ -601,15 +657,15 @@ __global__ __launch_bounds__(kMvThreads) void k_mv_long(const DevBuild *__restri
     }
 }
 
-// One wave per gene: CSR offset of the gene, its vector moved into place, and the
-// gene of every entry noted for the index.
+// One wave per gene: CSR offset of the gene and its vector moved into place.  For the index every
+// entry leaves its record (REC: key and gene | count << 16, 8 bytes) or its gene, in the order of
+// all genomes' entries.  NARROW: the slots hold 32-bit keys.  Bound by memory.
+template <bool NARROW, bool REC>
 __global__ __launch_bounds__(kWave) void k_mv_compact(const DevBuild *__restrict__ table, uint32_t n_genomes,
-                                                      const uint32_t *__restrict__ gptr, uint32_t *__restrict__ ent_gene) {
-    __shared__ uint32_t s_t;
+                                                      const uint32_t *__restrict__ gptr, uint32_t *__restrict__ ent_gene,
+                                                      uint2 *__restrict__ ent_rec) {
     const uint32_t G = blockIdx.x;
-    if (threadIdx.x == 0) s_t = find_genome_by_gene(table, n_genomes, G);
-    __syncthreads();
-    const DevBuild &B = table[s_t];
+    const DevBuild &B = table[find_genome_by_gene(table, n_genomes, G)];
     const uint32_t g = G - B.gene_base;
     const uint64_t o = B.off[g];
     const uint32_t base = gptr[B.gene_base];
@@ -619,10 +675,29 @@ __global__ __launch_bounds__(kWave) void k_mv_compact(const DevBuild *__restrict
         B.mv_ptr[g] = p;
         if (g + 1 == B.n_genes) B.mv_ptr[g + 1] = p + d;
     }
-    for (uint32_t e = threadIdx.x; e < d; e += kWave) {
-        store_global(B.mv_code + p + e, load_global(B.slot_code + o + e));
-        store_global(B.mv_cnt + p + e, load_global(B.slot_cnt + o + e));
-        ent_gene[gptr[G] + e] = g;
+    const uint32_t *slot_key = reinterpret_cast<const uint32_t *>(B.slot_code) + o;
+    constexpr uint32_t U = 4;  // entries a thread has in flight
+    for (uint32_t e0 = threadIdx.x; e0 < d; e0 += U * kWave) {
+        uint64_t c[U];
+        uint32_t n[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t e = e0 + u * kWave;
+            if (e >= d) continue;
+            if constexpr (NARROW) c[u] = load_global(slot_key + e);
+            else c[u] = load_global(B.slot_code + o + e);
+            n[u] = load_global(B.slot_cnt + o + e);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t e = e0 + u * kWave;
+            if (e >= d) continue;
+            if constexpr (NARROW) store_global(B.mv_code + p + e, key_to_code(B, static_cast<uint32_t>(c[u])));
+            else store_global(B.mv_code + p + e, c[u]);
+            store_global(B.mv_cnt + p + e, n[u]);
+            if constexpr (REC) ent_rec[base + p + e] = make_uint2(static_cast<uint32_t>(c[u]), g | (n[u] << 16));
+            else ent_gene[base + p + e] = g;
+        }
     }
 }
 
@@ -657,10 +732,20 @@ __device__ __forceinline__ void block_range(const DevBuild &B, const uint32_t *g
     *e1 = min(E, (j + 1) * kIxBlock);
 }
 
+// Bucket of an entry: from its 32-bit key (REC) or its code.
+template <bool REC>
+__device__ __forceinline__ uint32_t entry_bucket(const DevBuild &B, uint64_t c) {
+    if constexpr (REC)
+        if (base20_keys(B)) return static_cast<uint32_t>(c) / 8000u;  // 20^3: the last three letters
+    return bucket_of(c, B.k, B.lead, B.bits);
+}
+
 // One work-group per block of entries: coarse-bin histogram in LDS, added to the genome's
 // bin totals with one global atomic per non-empty bin.
+template <bool REC>
 __global__ __launch_bounds__(256) void k_ix_hist(const DevBuild *__restrict__ table, uint32_t n_genomes,
-                                                 const uint32_t *__restrict__ gptr, uint32_t *__restrict__ bintot) {
+                                                 const uint32_t *__restrict__ gptr, const uint2 *__restrict__ ent_rec,
+                                                 uint32_t *__restrict__ bintot) {
     extern __shared__ uint32_t h[];
     __shared__ uint32_t s_t;
     if (threadIdx.x == 0) s_t = find_genome_by_block(table, n_genomes, blockIdx.x);
@@ -677,11 +762,12 @@ __global__ __launch_bounds__(256) void k_ix_hist(const DevBuild *__restrict__ ta
 #pragma unroll
         for (uint32_t q = 0; q < kIxBatch; ++q) {
             const uint32_t e = base + q * 256 + threadIdx.x;
-            c[q] = e < e1 ? load_global(B.mv_code + e) : 0ull;
+            if constexpr (REC) c[q] = load_global(reinterpret_cast<const uint32_t *>(ent_rec + gbase + min(e, e1 - 1)));
+            else c[q] = e < e1 ? load_global(B.mv_code + e) : 0ull;
         }
 #pragma unroll
         for (uint32_t q = 0; q < kIxBatch; ++q)
-            if (base + q * 256 + threadIdx.x < e1) atomicAdd(&h[bucket_of(c[q], B.k, B.lead, B.bits) >> B.hshift], 1u);
+            if (base + q * 256 + threadIdx.x < e1) atomicAdd(&h[entry_bucket<REC>(B, c[q]) >> B.hshift], 1u);
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < B.nh; i += blockDim.x)
@@ -698,16 +784,6 @@ __device__ __forceinline__ uint32_t rec_cnt(const uint2 &r) { return r.y >> 16; 
 // count), or, when every genome of the build has 32-bit keys (codes of at most 32 bits, or
 // base-20 values: base20_keys) and at most 65536 genes, uint2 = (key, gene | count << 16):
 // half the LDS, more work-groups per CU.  A base-20 key orders records as the code does.
-__device__ __forceinline__ uint32_t code_to_base20(uint64_t c, uint32_t k) {
-    uint32_t v = 0;
-    for (uint32_t i = 0; i < k; ++i) v = v * 20u + static_cast<uint32_t>((c >> (5u * (k - 1u - i))) & 31u);
-    return v;
-}
-__device__ __forceinline__ void to_rec(const DevBuild &, const uint4 &v, uint4 *r) { *r = v; }
-__device__ __forceinline__ void to_rec(const DevBuild &B, const uint4 &v, uint2 *r) {
-    const uint32_t key = base20_keys(B) ? code_to_base20((static_cast<uint64_t>(v.y) << 32) | v.x, B.k) : v.x;
-    *r = make_uint2(key, v.z | (v.w << 16));
-}
 // The 5-bit code of a record.
 __device__ __forceinline__ uint64_t rec_code5(const DevBuild &, const uint4 &r) { return rec_code(r); }
 __device__ __forceinline__ uint64_t rec_code5(const DevBuild &B, const uint2 &r) {
@@ -729,7 +805,9 @@ static_assert(kIxPerThread % kIxBatch == 0, "placement rounds divide the entries
 template <typename R>
 __global__ __launch_bounds__(kIxPlaceThreads) void k_ix_place(const DevBuild *__restrict__ table, uint32_t n_genomes,
                                                   const uint32_t *__restrict__ gptr, const uint32_t *__restrict__ binoff,
-                                                  uint32_t *__restrict__ bintot, const uint32_t *__restrict__ ent_gene) {
+                                                  uint32_t *__restrict__ bintot, const uint32_t *__restrict__ ent_gene,
+                                                  const uint2 *__restrict__ ent_rec) {
+    constexpr bool REC = sizeof(R) == 8;
     extern __shared__ uint32_t cur[];
     __shared__ uint32_t s_t;
     if (threadIdx.x == 0) s_t = find_genome_by_block(table, n_genomes, blockIdx.x);
@@ -740,16 +818,25 @@ __global__ __launch_bounds__(kIxPlaceThreads) void k_ix_place(const DevBuild *__
     __syncthreads();
     uint32_t e0, e1, gbase;
     block_range(B, gptr, j, &e0, &e1, &gbase);
-    uint64_t c[kIxPerThread];
+    if (e0 == e1) return;  // uniform
+    using Key = typename std::conditional<REC, uint32_t, uint64_t>::type;
+    Key c[kIxPerThread];
+    uint32_t second[kIxPerThread];  // REC: gene and count
     uint32_t rank[kIxPerThread];
 #pragma unroll
     for (uint32_t q = 0; q < kIxPerThread; ++q) {
         const uint32_t e = e0 + q * kIxPlaceThreads + threadIdx.x;
-        c[q] = e < e1 ? load_global(B.mv_code + e) : 0ull;
+        if constexpr (REC) {
+            const uint64_t r = load_global(reinterpret_cast<const uint64_t *>(ent_rec + gbase + min(e, e1 - 1)));
+            c[q] = static_cast<uint32_t>(r);
+            second[q] = static_cast<uint32_t>(r >> 32);
+        } else {
+            c[q] = e < e1 ? load_global(B.mv_code + e) : 0ull;
+        }
     }
 #pragma unroll
     for (uint32_t q = 0; q < kIxPerThread; ++q)
-        if (e0 + q * kIxPlaceThreads + threadIdx.x < e1) rank[q] = atomicAdd(&cur[bucket_of(c[q], B.k, B.lead, B.bits) >> B.hshift], 1u);
+        if (e0 + q * kIxPlaceThreads + threadIdx.x < e1) rank[q] = atomicAdd(&cur[entry_bucket<REC>(B, c[q]) >> B.hshift], 1u);
     __syncthreads();
     const uint32_t gstart = binoff[B.bin_base];  // the genome's first entry in the scanned order
     for (uint32_t i = threadIdx.x; i < B.nh; i += blockDim.x) {
@@ -757,27 +844,32 @@ __global__ __launch_bounds__(kIxPlaceThreads) void k_ix_place(const DevBuild *__
         if (n) cur[i] = binoff[B.bin_base + i] - gstart + atomicSub(&bintot[B.bin_base + i], n) - n;
     }
     __syncthreads();
-    for (uint32_t q0 = 0; q0 < kIxPerThread; q0 += kIxBatch) {
-        uint32_t gn[kIxBatch], ct[kIxBatch];
+    if constexpr (REC) {
 #pragma unroll
-        for (uint32_t q = 0; q < kIxBatch; ++q) {
-            const uint32_t e = e0 + (q0 + q) * kIxPlaceThreads + threadIdx.x;
-            const bool v = e < e1;
-            gn[q] = v ? ent_gene[gbase + e] : 0u;
-            ct[q] = v ? load_global(B.mv_cnt + e) : 0u;
+        for (uint32_t q = 0; q < kIxPerThread; ++q) {
+            if (e0 + q * kIxPlaceThreads + threadIdx.x >= e1) continue;
+            const uint32_t pos = cur[entry_bucket<REC>(B, c[q]) >> B.hshift] + rank[q];
+            // one 64-bit word, through a global (not flat) store
+            store_global(reinterpret_cast<uint64_t *>(B.ix_tmp) + pos, (static_cast<uint64_t>(second[q]) << 32) | c[q]);
         }
+    } else {
+        for (uint32_t q0 = 0; q0 < kIxPerThread; q0 += kIxBatch) {
+            uint32_t gn[kIxBatch], ct[kIxBatch];
 #pragma unroll
-        for (uint32_t q = 0; q < kIxBatch; ++q) {
-            if (e0 + (q0 + q) * kIxPlaceThreads + threadIdx.x >= e1) continue;
-            const uint64_t code = c[q0 + q];
-            const uint32_t pos = cur[bucket_of(code, B.k, B.lead, B.bits) >> B.hshift] + rank[q0 + q];
-            // one record per entry: a single scattered store instead of three
-            R r;
-            to_rec(B, make_uint4(static_cast<uint32_t>(code), static_cast<uint32_t>(code >> 32), gn[q], ct[q]), &r);
-            if constexpr (sizeof(R) == 8)  // as one 64-bit word, through a global (not flat) store
-                store_global(reinterpret_cast<uint64_t *>(B.ix_tmp) + pos, (static_cast<uint64_t>(r.y) << 32) | r.x);
-            else
-                reinterpret_cast<R *>(B.ix_tmp)[pos] = r;
+            for (uint32_t q = 0; q < kIxBatch; ++q) {
+                const uint32_t e = e0 + (q0 + q) * kIxPlaceThreads + threadIdx.x;
+                const bool v = e < e1;
+                gn[q] = v ? ent_gene[gbase + e] : 0u;
+                ct[q] = v ? load_global(B.mv_cnt + e) : 0u;
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < kIxBatch; ++q) {
+                if (e0 + (q0 + q) * kIxPlaceThreads + threadIdx.x >= e1) continue;
+                const uint64_t code = c[q0 + q];
+                const uint32_t pos = cur[entry_bucket<REC>(B, code) >> B.hshift] + rank[q0 + q];
+                // one record per entry: a single scattered store instead of three
+                B.ix_tmp[pos] = make_uint4(static_cast<uint32_t>(code), static_cast<uint32_t>(code >> 32), gn[q], ct[q]);
+            }
         }
     }
 }
@@ -1161,15 +1253,21 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
         PDP_TRY(hipGetLastError());
     }
     const uint32_t tg = static_cast<uint32_t>(sh.total_genes);
+    // keys of 32 bits (codes, or base-20 values); records of 8 bytes when every gene index also fits
+    // 16 bits and every multiplicity 16 bits (no long-gene dictionary)
+    bool narrow = true, narrow_rec = true;
+    for (uint32_t i = 0; i < n; ++i) {
+        narrow &= alpha_spec(d[i]->alphabet).bits * d[i]->k <= 32 || (d[i]->alphabet == PDP_ALPHA_AMINO && d[i]->k == 7);
+        narrow_rec &= g[i].n_genes <= 65536 && !(d[i]->flags & PDP_DICT_LONG_GENES);
+    }
+    narrow_rec &= narrow;
+    uint2 *ent_rec = reinterpret_cast<uint2 *>(long_tmp);  // free once the multiplicity vectors are in their slots
     const uint32_t hist_lds = static_cast<uint32_t>(4 * sh.max_nh);
     const uint64_t init_items = std::max<uint64_t>(std::max<uint64_t>(n, sh.total_bins), 4);
     hipLaunchKernelGGL(k_build_init, dim3(static_cast<uint32_t>(std::min<uint64_t>((init_items + 255) / 256, 1024))),
                        dim3(256), 0, s, table, n, counters, bintot, static_cast<uint32_t>(sh.total_bins));
     PDP_TRY(hipGetLastError());
     if (tg > 0) {
-        bool narrow = true;
-        for (uint32_t i = 0; i < n; ++i)
-            narrow &= alpha_spec(d[i]->alphabet).bits * d[i]->k <= 32 || (d[i]->alphabet == PDP_ALPHA_AMINO && d[i]->k == 7);
         if (narrow)
             hipLaunchKernelGGL(k_mv_wave<true>, dim3((tg + kMvWaves - 1) / kMvWaves), dim3(kMvThreads), 0, s, table, n,
                                tg, dcnt, mid_list, long_list, stride, counters);
@@ -1201,30 +1299,36 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
         }
         PDP_TRY(hipGetLastError());
         const uint32_t long_groups = tg < 64 ? tg : 64;
-        hipLaunchKernelGGL(k_mv_long, dim3(long_groups), dim3(kMvThreads), 0, s, table, dcnt, long_list, counters);
+        if (narrow)
+            hipLaunchKernelGGL(k_mv_long<true>, dim3(long_groups), dim3(kMvThreads), 0, s, table, dcnt, long_list, counters);
+        else
+            hipLaunchKernelGGL(k_mv_long<false>, dim3(long_groups), dim3(kMvThreads), 0, s, table, dcnt, long_list, counters);
         PDP_TRY(hipGetLastError());
     }
     PDP_TRY(launch_scan(dcnt, dcnt, tg, partials, s));  // in place: dcnt becomes the global offsets
     if (tg > 0) {
-        hipLaunchKernelGGL(k_mv_compact, dim3(tg), dim3(kWave), 0, s, table, n, dcnt, ent_gene);
+        if (narrow_rec)
+            hipLaunchKernelGGL((k_mv_compact<true, true>), dim3(tg), dim3(kWave), 0, s, table, n, dcnt, ent_gene, ent_rec);
+        else if (narrow)
+            hipLaunchKernelGGL((k_mv_compact<true, false>), dim3(tg), dim3(kWave), 0, s, table, n, dcnt, ent_gene, ent_rec);
+        else
+            hipLaunchKernelGGL((k_mv_compact<false, false>), dim3(tg), dim3(kWave), 0, s, table, n, dcnt, ent_gene, ent_rec);
         PDP_TRY(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_ix_hist, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(256), hist_lds, s, table, n, dcnt,
-                       bintot);
+    if (narrow_rec)
+        hipLaunchKernelGGL(k_ix_hist<true>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(256), hist_lds, s, table, n,
+                           dcnt, ent_rec, bintot);
+    else
+        hipLaunchKernelGGL(k_ix_hist<false>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(256), hist_lds, s, table, n,
+                           dcnt, ent_rec, bintot);
     PDP_TRY(hipGetLastError());
     PDP_TRY(launch_scan(bintot, binoff, sh.total_bins, partials, s));  // every bin's range
-    // bins placed and sorted as 8-byte records when every key fits 32 bits, every gene index 16
-    // bits and every multiplicity 16 bits (no long-gene dictionary)
-    bool narrow_rec = true;
-    for (uint32_t i = 0; i < n; ++i)
-        narrow_rec &= (alpha_spec(d[i]->alphabet).bits * d[i]->k <= 32 || (d[i]->alphabet == PDP_ALPHA_AMINO && d[i]->k == 7)) &&
-                      g[i].n_genes <= 65536 && !(d[i]->flags & PDP_DICT_LONG_GENES);
     if (narrow_rec)
         hipLaunchKernelGGL(k_ix_place<uint2>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(kIxPlaceThreads), hist_lds,
-                           s, table, n, dcnt, binoff, bintot, ent_gene);
+                           s, table, n, dcnt, binoff, bintot, ent_gene, ent_rec);
     else
         hipLaunchKernelGGL(k_ix_place<uint4>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(kIxPlaceThreads), hist_lds,
-                           s, table, n, dcnt, binoff, bintot, ent_gene);
+                           s, table, n, dcnt, binoff, bintot, ent_gene, ent_rec);
     PDP_TRY(hipGetLastError());
     if (narrow_rec)
         hipLaunchKernelGGL(k_ix_sort_bin<uint2>, dim3(static_cast<uint32_t>(sh.total_bins)), dim3(256), 0, s, table, n,
