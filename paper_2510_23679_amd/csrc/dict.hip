@@ -15,14 +15,14 @@
 //    and k_mv_compact packs the vectors (and notes each entry's gene).
 // 3. The inverted index (all entries ordered by k-mer code, ties by gene) is a
 //    two-level partition: the leading-letter buckets are grouped into coarse
-//    bins of 2^s buckets (s per genome, ~500 entries per bin); k_ix_hist
+//    bins of 2^s buckets (s per genome, up to kIxBinTarget entries per bin); k_ix_hist
 //    counts bins per block of entries in LDS and adds them to the bin totals
 //    (one global atomic per block and bin), a scan gives every bin its output
 //    range, k_ix_place hands each block a run of every bin's range (again one
 //    atomic per block and bin) and drops its entries there by LDS rank, and
 //    k_ix_sort_bin sorts each bin by (code, gene) in LDS (a counting sort by
 //    bucket and the next one or two letters, which leaves about one entry per
-//    slot, then a sort inside each slot) and writes the bin's part of the
+//    slot, then ranks inside each slot) and writes the bin's part of the
 //    bucket directory.
 // Genes and buckets of all genomes of a call are numbered consecutively; a
 // work-group finds its genome by binary search over the per-genome bases.
@@ -728,8 +728,8 @@ __device__ __forceinline__ void block_range(const DevBuild &B, const uint32_t *g
     const uint32_t base = gptr[B.gene_base];
     const uint32_t E = gptr[B.gene_base + B.n_genes] - base;
     *gbase = base;
-    *e0 = min(E, j * kIxBlock);
-    *e1 = min(E, (j + 1) * kIxBlock);
+    *e0 = min(E, j * B.blk);
+    *e1 = min(E, (j + 1) * B.blk);
 }
 
 // Bucket of an entry: from its 32-bit key (REC) or its code.
@@ -791,8 +791,6 @@ __device__ __forceinline__ uint64_t rec_code5(const DevBuild &B, const uint2 &r)
 }
 
 constexpr uint32_t kIxPlaceThreads = 1024;  // a placement work-group: its block of entries in registers, 16 per thread
-constexpr uint32_t kIxPerThread = kIxBlock / kIxPlaceThreads;  // entries a placement thread keeps
-static_assert(kIxPerThread % kIxBatch == 0, "placement rounds divide the entries of a thread");
 
 // Same blocks: each entry goes to its bin's range.  The block counts its entries per bin in
 // LDS (every entry's rank among the block's entries of its bin comes back from the LDS
@@ -802,7 +800,7 @@ static_assert(kIxPerThread % kIxBatch == 0, "placement rounds divide the entries
 // keeps (8 bytes when the build allows it, so the scattered stores and the sort's loads move
 // half the bytes).  The order inside a bin depends on scheduling; k_ix_sort_bin sorts every
 // bin completely.
-template <typename R>
+template <typename R, uint32_t kIxPerThread>
 __global__ __launch_bounds__(kIxPlaceThreads) void k_ix_place(const DevBuild *__restrict__ table, uint32_t n_genomes,
                                                   const uint32_t *__restrict__ gptr, const uint32_t *__restrict__ binoff,
                                                   uint32_t *__restrict__ bintot, const uint32_t *__restrict__ ent_gene,
@@ -853,17 +851,18 @@ __global__ __launch_bounds__(kIxPlaceThreads) void k_ix_place(const DevBuild *__
             store_global(reinterpret_cast<uint64_t *>(B.ix_tmp) + pos, (static_cast<uint64_t>(second[q]) << 32) | c[q]);
         }
     } else {
-        for (uint32_t q0 = 0; q0 < kIxPerThread; q0 += kIxBatch) {
-            uint32_t gn[kIxBatch], ct[kIxBatch];
+        constexpr uint32_t kRound = kIxPerThread < kIxBatch ? kIxPerThread : kIxBatch;
+        for (uint32_t q0 = 0; q0 < kIxPerThread; q0 += kRound) {
+            uint32_t gn[kRound], ct[kRound];
 #pragma unroll
-            for (uint32_t q = 0; q < kIxBatch; ++q) {
+            for (uint32_t q = 0; q < kRound; ++q) {
                 const uint32_t e = e0 + (q0 + q) * kIxPlaceThreads + threadIdx.x;
                 const bool v = e < e1;
                 gn[q] = v ? ent_gene[gbase + e] : 0u;
                 ct[q] = v ? load_global(B.mv_cnt + e) : 0u;
             }
 #pragma unroll
-            for (uint32_t q = 0; q < kIxBatch; ++q) {
+            for (uint32_t q = 0; q < kRound; ++q) {
                 if (e0 + (q0 + q) * kIxPlaceThreads + threadIdx.x >= e1) continue;
                 const uint64_t code = c[q0 + q];
                 const uint32_t pos = cur[entry_bucket<REC>(B, code) >> B.hshift] + rank[q0 + q];
@@ -944,9 +943,17 @@ __device__ __forceinline__ void sort_recs(R *r, uint32_t n) {
     });
 }
 
-constexpr uint32_t kIxSmallBucket = 16;   // slots up to this size are sorted by one thread
+constexpr uint32_t kIxSmallBucket = 32;   // slots up to this size are ranked entry by entry
 constexpr uint32_t kIxBigList = 64;       // larger slots a bin sorts one by one with the work-group
-constexpr uint32_t kIxPer = kIxBinSlots / 256;  // counting-sort slots per thread
+// A bin sort's work-group: LDS for 4096 records of 8 bytes or 1024 of 16, and twice as many slots.
+template <typename R>
+struct BinSort {
+    static constexpr uint32_t kThreads = sizeof(R) == 8 ? 512 : 256;
+    static constexpr uint32_t kPer = sizeof(R) == 8 ? 8 : 4;   // entries per thread
+    static constexpr uint32_t kLds = kThreads * kPer;      // entries of a bin sorted in LDS
+    static constexpr uint32_t kSlots = 2 * kLds;           // counting-sort slots of a bin (buckets x sub-slots)
+    static constexpr uint32_t kWords = kSlots / 2 / kThreads;  // 16-bit slot counters, words per thread
+};
 
 // Counting-sort slot of a code inside the bin starting at bucket b0: the bucket, then the
 // next xb bits of the code (whole letters), so slots ascend like codes.
@@ -967,26 +974,30 @@ __device__ __forceinline__ uint32_t rec_slot(const DevBuild &B, const uint2 &r, 
     return B.xb ? (b << B.xb) | ((r.x / 400u) % 20u) : b;
 }
 
+__device__ __forceinline__ uint32_t slot16(const uint32_t *w, uint32_t s) { return (w[s >> 1] >> ((s & 1u) * 16u)) & 0xFFFFu; }
+
 // One work-group per coarse bin: its entries ordered by (code, gene) and the bin's part of
-// the bucket directory.  Usual case (the bin fits LDS and its slots fit kIxBinSlots): a
-// counting sort by slot (LDS histogram, scan, scatter), whose offsets at the first slot of
-// every bucket are the directory, then every slot sorted on its own, by one thread
-// (insertion sort) or, if large, by the work-group.  Otherwise the whole bin is sorted in
-// LDS, or in place in global memory when it does not fit.
+// the bucket directory.  Usual case (the bin fits LDS and its slots fit kSlots): a counting sort
+// by slot (LDS histogram, scan, scatter), whose offsets at the first slot of every bucket are the
+// directory; then every entry finds its rank among its slot's entries and goes straight to its
+// place.  Slots past kIxSmallBucket entries are sorted by the work-group first.  Otherwise the
+// whole bin is sorted in LDS, or in place in global memory when it does not fit.
+// Bins of 1350 to 2700 8-byte records on average (50 genomes of 3000 to 5000 genes: 2176): sort 0.44 ms,
+// placement 0.45 ms.  With half of that 0.56 and 0.55 ms, with a quarter 0.87 and 0.70 ms: the
+// placement's runs per (block, bin) get shorter and the work-groups emptier.
 template <typename R>
-__global__ __launch_bounds__(256) void k_ix_sort_bin(const DevBuild *__restrict__ table, uint32_t n_genomes,
-                                                     const uint32_t *__restrict__ off) {
-    __shared__ R s_rec[kIxBinLds];
-    __shared__ uint32_t s_bstart[kIxBinSlots + 1];
+__global__ __launch_bounds__(BinSort<R>::kThreads) void k_ix_sort_bin(const DevBuild *__restrict__ table,
+                                                                      uint32_t n_genomes,
+                                                                      const uint32_t *__restrict__ off) {
+    using S = BinSort<R>;
+    constexpr uint32_t NT = S::kThreads, kIxPer = S::kPer;
+    __shared__ R s_rec[S::kLds];
+    __shared__ uint32_t s_slot[S::kSlots / 2 + 1];  // two 16-bit counters, then starts, per word
     __shared__ uint32_t s_big[kIxBigList];
-    __shared__ uint32_t s_tmp[256 / kWave + 1];
-    __shared__ uint32_t s_t, s_nbig;
-    if (threadIdx.x == 0) {
-        s_t = find_genome_by_bin(table, n_genomes, blockIdx.x);
-        s_nbig = 0;
-    }
-    __syncthreads();
-    const DevBuild &B = table[s_t];
+    __shared__ uint32_t s_tmp[NT / kWave + 1];
+    __shared__ uint32_t s_nbig;
+    const uint32_t tid = threadIdx.x;
+    const DevBuild &B = table[find_genome_by_bin(table, n_genomes, blockIdx.x)];
     const uint32_t h = blockIdx.x - B.bin_base;
     const uint32_t base = off[B.bin_base];
     const uint32_t lo = off[B.bin_base + h] - base;
@@ -997,14 +1008,14 @@ __global__ __launch_bounds__(256) void k_ix_sort_bin(const DevBuild *__restrict_
     const uint32_t nbb = b1 - b0;
     const uint32_t nslot = nbb << B.xb;
     const R *tmp = reinterpret_cast<const R *>(B.ix_tmp);  // the placement wrote R records
-    if (n <= kIxBinLds && nslot <= kIxBinSlots) {
-        for (uint32_t i = threadIdx.x; i <= nslot; i += 256) s_bstart[i] = 0;
-        __syncthreads();
+    if (n <= S::kLds && nslot <= S::kSlots) {
+        for (uint32_t i = tid; i <= S::kSlots / 2; i += NT) s_slot[i] = 0;
+        if (tid == 0) s_nbig = 0;
         R r[kIxPer];
-        uint32_t slot[kIxPer], bk[kIxPer];
+        uint32_t rank[kIxPer], bk[kIxPer];
 #pragma unroll
         for (uint32_t q = 0; q < kIxPer; ++q) {  // every load issued before the first atomic
-            const uint32_t i = q * 256 + threadIdx.x;
+            const uint32_t i = q * NT + tid;
             if constexpr (sizeof(R) == 8) {  // one 64-bit word, through a global (not flat) load
                 const uint64_t w = i < n ? load_global(reinterpret_cast<const uint64_t *>(tmp) + lo + i) : 0ull;
                 r[q] = R{static_cast<uint32_t>(w), static_cast<uint32_t>(w >> 32)};
@@ -1012,78 +1023,71 @@ __global__ __launch_bounds__(256) void k_ix_sort_bin(const DevBuild *__restrict_
                 r[q] = i < n ? tmp[lo + i] : R{};
             }
         }
+        __syncthreads();
 #pragma unroll
         for (uint32_t q = 0; q < kIxPer; ++q) {
-            const uint32_t i = q * 256 + threadIdx.x;
-            if (i < n) {
-                bk[q] = rec_slot(B, r[q], b0);
-                slot[q] = atomicAdd(&s_bstart[bk[q]], 1u);
+            if (q * NT + tid >= n) continue;
+            const uint32_t b = rec_slot(B, r[q], b0), sh = (b & 1u) * 16u;
+            bk[q] = b;
+            rank[q] = (atomicAdd(&s_slot[b >> 1], 1u << sh) >> sh) & 0xFFFFu;
+        }
+        __syncthreads();
+        {  // exclusive scan of the slot sizes
+            uint32_t w[S::kWords], sum = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < S::kWords; ++q) {
+                w[q] = s_slot[tid * S::kWords + q];
+                sum += (w[q] & 0xFFFFu) + (w[q] >> 16);
             }
-        }
-        __syncthreads();
-        // exclusive scan of the slot sizes; thread t owns slots [kIxPer*t, kIxPer*t + kIxPer)
-        uint32_t c[kIxPer], sum = 0;
+            uint32_t total;
+            uint32_t run = block_exclusive_scan<NT>(sum, s_tmp, &total);
 #pragma unroll
-        for (uint32_t q = 0; q < kIxPer; ++q) {
-            const uint32_t b = threadIdx.x * kIxPer + q;
-            c[q] = b < nslot ? s_bstart[b] : 0u;
-            sum += c[q];
-        }
-        uint32_t total;
-        uint32_t run = block_exclusive_scan<256>(sum, s_tmp, &total);
-#pragma unroll
-        for (uint32_t q = 0; q < kIxPer; ++q) {
-            const uint32_t b = threadIdx.x * kIxPer + q;
-            if (b < nslot) s_bstart[b] = run;
-            run += c[q];
-        }
-        if (threadIdx.x == 0) s_bstart[nslot] = n;
-        __syncthreads();
-#pragma unroll
-        for (uint32_t q = 0; q < kIxPer; ++q) {
-            const uint32_t i = q * 256 + threadIdx.x;
-            if (i < n) s_rec[s_bstart[bk[q]] + slot[q]] = r[q];
-        }
-        __syncthreads();
-        for (uint32_t b = threadIdx.x; b < nbb; b += 256) store_global(B.ix_dir + b0 + b, lo + s_bstart[b << B.xb]);
-        for (uint32_t b = threadIdx.x; b < nslot; b += 256) {
-            const uint32_t st = s_bstart[b], size = s_bstart[b + 1] - st;
-            if (size <= kIxSmallBucket) {
-                for (uint32_t x = st + 1; x < st + size; ++x) {
-                    const R v = s_rec[x];
-                    uint32_t y = x;
-                    while (y > st && rec_less(v, s_rec[y - 1])) {
-                        s_rec[y] = s_rec[y - 1];
-                        --y;
+            for (uint32_t q = 0; q < S::kWords; ++q) {
+                const uint32_t b = (tid * S::kWords + q) * 2, c0 = w[q] & 0xFFFFu, c1 = w[q] >> 16;
+                s_slot[tid * S::kWords + q] = run | ((run + c0) << 16);
+                run += c0 + c1;
+                for (uint32_t x = 0; x < 2; ++x)
+                    if ((x ? c1 : c0) > kIxSmallBucket) {
+                        const uint32_t idx = atomicAdd(&s_nbig, 1u);
+                        if (idx < kIxBigList) s_big[idx] = b + x;
                     }
-                    s_rec[y] = v;
-                }
-            } else {
-                const uint32_t idx = atomicAdd(&s_nbig, 1u);
-                if (idx < kIxBigList) s_big[idx] = b;
             }
+            if (tid == 0) s_slot[S::kSlots / 2] = n;
         }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < kIxPer; ++q)
+            if (q * NT + tid < n) s_rec[slot16(s_slot, bk[q]) + rank[q]] = r[q];
+        for (uint32_t b = tid; b < nbb; b += NT) store_global(B.ix_dir + b0 + b, lo + slot16(s_slot, b << B.xb));
         __syncthreads();
         const uint32_t nbig = s_nbig;
         if (nbig > kIxBigList) {
             sort_recs(s_rec, n);
         } else {
             for (uint32_t j = 0; j < nbig; ++j) {  // uniform loop
-                const uint32_t b = s_big[j];
-                sort_recs(s_rec + s_bstart[b], s_bstart[b + 1] - s_bstart[b]);
+                const uint32_t a = slot16(s_slot, s_big[j]);
+                sort_recs(s_rec + a, slot16(s_slot, s_big[j] + 1) - a);
             }
         }
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < n; i += 256) put_entry(B, lo + i, s_rec[i]);
-    } else if (n <= kIxBinLds) {
-        for (uint32_t i = threadIdx.x; i < n; i += 256) s_rec[i] = tmp[lo + i];
+        for (uint32_t p = tid; p < n; p += NT) {
+            const R v = s_rec[p];
+            uint32_t at = p;
+            const uint32_t b = rec_slot(B, v, b0), a = slot16(s_slot, b), e = slot16(s_slot, b + 1);
+            if (e - a <= kIxSmallBucket && nbig <= kIxBigList) {
+                at = a;
+                for (uint32_t x = a; x < e; ++x) at += rec_less(s_rec[x], v);
+            }
+            put_entry(B, lo + at, v);
+        }
+    } else if (n <= S::kLds) {
+        for (uint32_t i = tid; i < n; i += NT) s_rec[i] = tmp[lo + i];
         __syncthreads();
         sort_recs(s_rec, n);
-        for (uint32_t i = threadIdx.x; i < n; i += 256) put_entry(B, lo + i, s_rec[i]);
+        for (uint32_t i = tid; i < n; i += NT) put_entry(B, lo + i, s_rec[i]);
         __syncthreads();
         bin_directory(B, B.ix_code + lo, n, lo, b0, b1);
     } else {
-        for (uint32_t i = threadIdx.x; i < n; i += 256) {
+        for (uint32_t i = tid; i < n; i += NT) {
             const R v = tmp[lo + i];
             B.ix_code[lo + i] = rec_code5(B, v);
             B.ix_gene[lo + i] = rec_gene(v);
@@ -1092,35 +1096,34 @@ __global__ __launch_bounds__(256) void k_ix_sort_bin(const DevBuild *__restrict_
         __syncthreads();
         sort_entries(B.ix_code + lo, B.ix_gene + lo, B.ix_cnt + lo, n);
         if (B.key_shift)
-            for (uint32_t i = threadIdx.x; i < n; i += 256) B.ix_key[lo + i] = entry_key(B, B.ix_code[lo + i], B.ix_gene[lo + i]);
+            for (uint32_t i = tid; i < n; i += NT) B.ix_key[lo + i] = entry_key(B, B.ix_code[lo + i], B.ix_gene[lo + i]);
         bin_directory(B, B.ix_code + lo, n, lo, b0, b1);
     }
-    if (h + 1 == B.nh && threadIdx.x == 0) B.ix_dir[B.nb] = hi;
+    if (h + 1 == B.nh && tid == 0) B.ix_dir[B.nb] = hi;
 }
 
 // ------------------------------------------------------------------ host
 
-// Coarse-bin shift: bins of 2^s buckets holding about kIxBinTarget entries on average.
-static uint32_t bin_shift(uint32_t nb, uint64_t cap) {
+// Coarse-bin shift: bins of 2^s buckets holding at most `target` entries on average.
+static uint32_t bin_shift(uint32_t nb, uint64_t cap, uint32_t target) {
     uint32_t s = 0;
-    while ((uint64_t(nb) >> (s + 1)) > 0 && (cap << (s + 1)) <= uint64_t(nb) * kIxBinTarget) ++s;
+    while ((uint64_t(nb) >> (s + 1)) > 0 && (cap << (s + 1)) <= uint64_t(nb) * target) ++s;
     while ((uint64_t(nb) >> s) > kIxMaxBins) ++s;  // keep the LDS histogram bounded
     return s;
 }
 
 // Bin shift s and sub-slot bits xb of one genome: a bin's counting sort goes by bucket and,
-// where the slots still fit kIxBinSlots, the next letter (amino acids, 5 bits) or two
-// (nucleotides, 4 bits), so that a slot holds about one entry.  (Smaller bins to make room
-// for the sub-slots cost more in the histogram and placement than they save.)
+// where the slots still fit, the next letter (amino acids, 5 bits) or two (nucleotides, 4 bits), so
+// that a slot holds about one entry.
 struct BinPlan {
     uint32_t s, xb;
 };
-static BinPlan bin_plan(uint32_t nb, uint64_t cap, uint32_t k, uint32_t alphabet) {
+static BinPlan bin_plan(uint32_t nb, uint64_t cap, uint32_t k, uint32_t alphabet, uint32_t target, uint32_t slots) {
     const AlphaSpec a = alpha_spec(alphabet);
-    const uint32_t s = bin_shift(nb, cap);
+    const uint32_t s = bin_shift(nb, cap, target);
     const uint32_t rest = k - lead_letters(k, alphabet);
     uint32_t xb = a.bits * std::min<uint32_t>(rest, a.bits == 2 ? 2u : 1u);
-    while (xb && (1ull << (s + xb)) > kIxBinSlots) xb -= a.bits;
+    while (xb && (1ull << (s + xb)) > slots) xb -= a.bits;
     return {s, xb};
 }
 
@@ -1130,14 +1133,11 @@ static BuildShape shape_of(const pdp_genome *g, const pdp_dict *const *d, uint32
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t cap = g[i].n_residues + 1;
         const uint32_t nb = d[i]->n_buckets;
-        const uint32_t sh = bin_plan(nb, cap, d[i]->k, d[i]->alphabet).s;
+        const uint32_t sh = bin_shift(nb, cap, kIxBinTargetWide);  // the most bins a launch may choose
         const uint64_t nh = (uint64_t(nb) + (1ull << sh) - 1) >> sh;
-        const uint64_t nblk = (cap + kIxBlock - 1) / kIxBlock;
         s.total_genes += g[i].n_genes;
         s.total_residues += cap;
-        s.total_blocks += nblk;
         s.total_bins += nh;
-        s.max_nh = std::max<uint64_t>(s.max_nh, nh);
     }
     return s;
 }
@@ -1201,6 +1201,23 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
     const uint64_t np = std::max<uint64_t>(scan_partials(sh.total_genes), scan_partials(sh.total_bins));
     uint32_t *partials = reinterpret_cast<uint32_t *>(take(4 * np));
 
+    // keys of 32 bits (codes, or base-20 values); records of 8 bytes when every gene index also fits
+    // 16 bits and every multiplicity 16 bits (no long-gene dictionary)
+    bool narrow = true, narrow_rec = true;
+    for (uint32_t i = 0; i < n; ++i) {
+        narrow &= alpha_spec(d[i]->alphabet).bits * d[i]->k <= 32 || (d[i]->alphabet == PDP_ALPHA_AMINO && d[i]->k == 7);
+        narrow_rec &= g[i].n_genes <= 65536 && !(d[i]->flags & PDP_DICT_LONG_GENES);
+    }
+    narrow_rec &= narrow;
+    // entries per placement block and per bin: large ones give each (block, bin) a longer run; where
+    // the chip is not filled, small blocks and bins (one genome of 1503 genes: histogram
+    // 13 -> 8 us, placement 16 -> 14 us with blocks of 2048 instead of 16384)
+    const bool small = sh.total_residues <= 512ull * kIxBlock / 4;
+    const uint32_t blk = small ? kIxBlockSmall : kIxBlock;
+    const uint32_t target = narrow_rec && !small ? kIxBinTarget : kIxBinTargetWide;
+    const uint32_t slots = narrow_rec ? BinSort<uint2>::kSlots : BinSort<uint4>::kSlots;
+    uint32_t max_nh = 0;
+
     // descriptors, passed by value to a tiny kernel in chunks
     uint64_t gene_base = 0, res_base = 0, blk_base = 0, bin_base = 0;
     for (uint32_t c0 = 0; c0 < n; c0 += kDescPerLaunch) {
@@ -1220,11 +1237,13 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
             B.nb = D.n_buckets;
             B.lead = D.lead;
             B.bits = alpha_spec(D.alphabet).bits;
-            const BinPlan bp = bin_plan(D.n_buckets, cap, D.k, D.alphabet);
+            const BinPlan bp = bin_plan(D.n_buckets, cap, D.k, D.alphabet, target, slots);
             B.hshift = bp.s;
             B.xb = bp.xb;
             B.nh = static_cast<uint32_t>((uint64_t(D.n_buckets) + (1ull << B.hshift) - 1) >> B.hshift);
-            B.nblk = static_cast<uint32_t>((cap + kIxBlock - 1) / kIxBlock);
+            B.blk = blk;
+            B.nblk = static_cast<uint32_t>((cap + blk - 1) / blk);
+            max_nh = std::max(max_nh, B.nh);
             B.gene_base = static_cast<uint32_t>(gene_base);
             B.blk_base = static_cast<uint32_t>(blk_base);
             B.bin_base = static_cast<uint32_t>(bin_base);
@@ -1253,19 +1272,12 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
         PDP_TRY(hipGetLastError());
     }
     const uint32_t tg = static_cast<uint32_t>(sh.total_genes);
-    // keys of 32 bits (codes, or base-20 values); records of 8 bytes when every gene index also fits
-    // 16 bits and every multiplicity 16 bits (no long-gene dictionary)
-    bool narrow = true, narrow_rec = true;
-    for (uint32_t i = 0; i < n; ++i) {
-        narrow &= alpha_spec(d[i]->alphabet).bits * d[i]->k <= 32 || (d[i]->alphabet == PDP_ALPHA_AMINO && d[i]->k == 7);
-        narrow_rec &= g[i].n_genes <= 65536 && !(d[i]->flags & PDP_DICT_LONG_GENES);
-    }
-    narrow_rec &= narrow;
     uint2 *ent_rec = reinterpret_cast<uint2 *>(long_tmp);  // free once the multiplicity vectors are in their slots
-    const uint32_t hist_lds = static_cast<uint32_t>(4 * sh.max_nh);
-    const uint64_t init_items = std::max<uint64_t>(std::max<uint64_t>(n, sh.total_bins), 4);
+    const uint32_t total_bins = static_cast<uint32_t>(bin_base), total_blocks = static_cast<uint32_t>(blk_base);
+    const uint32_t hist_lds = 4 * max_nh;
+    const uint64_t init_items = std::max<uint64_t>(std::max<uint64_t>(n, total_bins), 4);
     hipLaunchKernelGGL(k_build_init, dim3(static_cast<uint32_t>(std::min<uint64_t>((init_items + 255) / 256, 1024))),
-                       dim3(256), 0, s, table, n, counters, bintot, static_cast<uint32_t>(sh.total_bins));
+                       dim3(256), 0, s, table, n, counters, bintot, total_bins);
     PDP_TRY(hipGetLastError());
     if (tg > 0) {
         if (narrow)
@@ -1316,26 +1328,30 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
         PDP_TRY(hipGetLastError());
     }
     if (narrow_rec)
-        hipLaunchKernelGGL(k_ix_hist<true>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(256), hist_lds, s, table, n,
+        hipLaunchKernelGGL(k_ix_hist<true>, dim3(total_blocks), dim3(256), hist_lds, s, table, n,
                            dcnt, ent_rec, bintot);
     else
-        hipLaunchKernelGGL(k_ix_hist<false>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(256), hist_lds, s, table, n,
+        hipLaunchKernelGGL(k_ix_hist<false>, dim3(total_blocks), dim3(256), hist_lds, s, table, n,
                            dcnt, ent_rec, bintot);
     PDP_TRY(hipGetLastError());
-    PDP_TRY(launch_scan(bintot, binoff, sh.total_bins, partials, s));  // every bin's range
-    if (narrow_rec)
-        hipLaunchKernelGGL(k_ix_place<uint2>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(kIxPlaceThreads), hist_lds,
-                           s, table, n, dcnt, binoff, bintot, ent_gene, ent_rec);
-    else
-        hipLaunchKernelGGL(k_ix_place<uint4>, dim3(static_cast<uint32_t>(sh.total_blocks)), dim3(kIxPlaceThreads), hist_lds,
-                           s, table, n, dcnt, binoff, bintot, ent_gene, ent_rec);
+    PDP_TRY(launch_scan(bintot, binoff, total_bins, partials, s));  // every bin's range
+    auto place = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kIxPlaceThreads), hist_lds, s, table, n, dcnt, binoff, bintot,
+                           ent_gene, ent_rec);
+    };
+    constexpr uint32_t kPer = kIxBlock / kIxPlaceThreads, kPerSmall = kIxBlockSmall / kIxPlaceThreads;
+    if (narrow_rec) {
+        if (small) place(k_ix_place<uint2, kPerSmall>);
+        else place(k_ix_place<uint2, kPer>);
+    } else {
+        if (small) place(k_ix_place<uint4, kPerSmall>);
+        else place(k_ix_place<uint4, kPer>);
+    }
     PDP_TRY(hipGetLastError());
     if (narrow_rec)
-        hipLaunchKernelGGL(k_ix_sort_bin<uint2>, dim3(static_cast<uint32_t>(sh.total_bins)), dim3(256), 0, s, table, n,
-                           binoff);
+        hipLaunchKernelGGL(k_ix_sort_bin<uint2>, dim3(total_bins), dim3(BinSort<uint2>::kThreads), 0, s, table, n, binoff);
     else
-        hipLaunchKernelGGL(k_ix_sort_bin<uint4>, dim3(static_cast<uint32_t>(sh.total_bins)), dim3(256), 0, s, table, n,
-                           binoff);
+        hipLaunchKernelGGL(k_ix_sort_bin<uint4>, dim3(total_bins), dim3(BinSort<uint4>::kThreads), 0, s, table, n, binoff);
     PDP_TRY(hipGetLastError());
     return hipSuccess;
 }

@@ -19,10 +19,10 @@ namespace pdp {
 constexpr uint32_t kScanItems = 4096;        // elements per scan work-group (256 threads x 16)
 constexpr uint32_t kMvSortCap = 8192;        // windows a gene may have to be sorted in LDS
 constexpr uint32_t kKMaxAll = PDP_K_MAX_NT > PDP_K_MAX ? PDP_K_MAX_NT : PDP_K_MAX;  // k bound over alphabets
-constexpr uint32_t kIxBlock = 16384;         // index entries per histogram block
-constexpr uint32_t kIxBinTarget = 512;       // average index entries per coarse bin
-constexpr uint32_t kIxBinLds = 1024;         // coarse bins up to this size are sorted in LDS
-constexpr uint32_t kIxBinSlots = 2048;       // counting-sort slots of a bin (buckets x sub-slots)
+constexpr uint32_t kIxBlock = 16384;         // index entries per placement block (large builds)
+constexpr uint32_t kIxBlockSmall = 2048;     // the same where that fills the chip no more than twice
+constexpr uint32_t kIxBinTarget = 2700;      // index entries per coarse bin, at most on average (8-byte records)
+constexpr uint32_t kIxBinTargetWide = 512;   // the same for 16-byte records, and small builds
 constexpr uint32_t kIxMaxBins = 8192;        // coarse bins per genome at most (LDS histogram)
 constexpr uint32_t kJoinLdsCap = 1024;       // target index entries staged in LDS per join sub-range
 constexpr uint32_t kJoinLdsCapP = 2048;      // the same for dictionaries with packed 32-bit keys
@@ -206,6 +206,7 @@ struct DevBuild {
     uint64_t n_residues;
     uint32_t n_genes, k, nb, lead, gene_base;
     uint32_t hshift, nh, nblk;            // coarse bins of 2^hshift buckets; entry blocks for the histogram
+    uint32_t blk;                         // entries per block
     uint32_t xb;                          // sub-slot bits per bucket of a bin's counting sort (next letters)
     uint32_t blk_base, bin_base;          // first block and bin of the genome
     uint32_t *nwin, *mv_ptr;
@@ -224,7 +225,7 @@ struct DevBuild {
     uint4 *ix_tmp;        // index entries placed by coarse bin, before the bin sort
 };
 struct BuildShape {
-    uint64_t n_genomes, total_genes, total_residues, total_blocks, total_bins, max_nh;
+    uint64_t n_genomes, total_genes, total_residues, total_bins;
 };
 BuildShape build_shape(const pdp_genome *g, const pdp_dict *const *d, uint32_t n);
 BuildShape single_build_shape(uint32_t n_genes, uint64_t n_residues, uint32_t k, uint32_t alphabet);
