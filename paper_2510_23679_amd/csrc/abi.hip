@@ -270,6 +270,15 @@ static DevDict dev_dict(const pdp_dict *d) {
     return x;
 }
 
+// Records expected in one direction of a task: divergent homologs share a fraction of their k-mers;
+// an eighth of the entries per direction covers the family workloads with room; more needs a
+// capacity retry.
+static uint64_t direction_estimate(const pdp_task &t) { return (t.a->capacity + t.b->capacity) / 8 + 4096; }
+// Room of a tile's record region over its rows' share of the estimate, in quarters: the fewer rows, the
+// further their lengths and their share lie from the average (a region that overflows costs the
+// two-pass join: two genomes of 1001 genes, tiles of 4 rows, 37 us of 90).
+static uint64_t tile_slack(uint32_t shift) { return shift >= 6 ? 4u : 4u + 3u * (6u - shift); }
+
 // Code of the first k-mer of bucket b.
 static uint64_t bucket_code(const pdp_dict *d, uint64_t b) {
     const AlphaSpec a = alpha_spec(d->alphabet);
@@ -489,6 +498,13 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         delete P;
         return rc;
     };
+    // Rows of all tasks and directions: short plans take lower tiles, to fill the chip.
+    uint64_t all_rows = 0;
+    for (uint32_t t = 0; t < n_tasks; ++t)
+        if (tasks[t].a && tasks[t].b) {
+            const uint32_t f = (tasks[t].flags & PDP_TASK_BBH) ? PDP_TASK_AB | PDP_TASK_BA : tasks[t].flags;
+            all_rows += ((f & PDP_TASK_AB) ? tasks[t].a->n_genes : 0u) + ((f & PDP_TASK_BA) ? tasks[t].b->n_genes : 0u);
+        }
     // Pass 1, in the caller's order: validation, output row layout, tile height per direction.
     uint64_t bh_rows = 0, bbh_rows = 0, rec_est = 0;
     // the sorted and hashed tile paths keep 8 bytes per record (12 with the filters' sums)
@@ -549,14 +565,13 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             orow[odir] = static_cast<uint32_t>(bh_rows);
             bh_rows += (odir == 0 ? tk.a : tk.b)->n_genes;
         }
-        uint32_t ndirs = 0;
+        const uint64_t dir_est = direction_estimate(tk);
         for (uint32_t dir = 0; dir < 2; ++dir) {  // the task's own directions from here on
             d.row_base[dir] = orow[swap ? 1 - dir : dir];
             d.tile_shift[dir] = base_shift;
             d.tiles_n[dir] = 0;
             if (!(dflags & (1u << dir))) continue;
             if ((dir == 1 && colmax) || long_task) continue;  // rows in the output, no tiles and no records of their own
-            ++ndirs;
             const pdp_dict *R = dir == 0 ? qa : qb;
             const pdp_dict *C = dir == 0 ? qb : qa;
             // a tile whose records overflow the LDS sort is summed densely: the column genome's
@@ -567,11 +582,22 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             if (dense > kMaxTileLds)
                 return bail(fail(PDP_E_LIMIT, "task %u: %u target genes do not fit an LDS tile", t, C->n_genes));
             tile_lds = std::max<uint32_t>(tile_lds, static_cast<uint32_t>(dense));
-            // a tile's (row, column) sums share one LDS hash table, and a row meets more
-            // columns by chance the more k-mers it has: unless the caller fixed the height,
-            // rows of long genes (over 512 letters on average, e.g. nucleotide genes) go 32
-            // to a tile instead of 64
-            if (!prm.tile_rows && R->n_genes && R->capacity / R->n_genes > 512) d.tile_shift[dir] = kDefaultTileShift - 1;
+            // a tile's (row, column) sums share one LDS hash table, and a row meets more columns by
+            // chance the more k-mers it has.  Unless the caller fixed the height, a tile has as many
+            // rows as their expected records fit the table (more go in several passes, each reading
+            // all of them), and fewer where the plan has under 512 tiles, down to 4 and up to 128
+            // tiles per direction (two genomes of 200 genes, k = 4: four tiles of 64 rows each way take
+            // 108 us, tiles of 4 rows 12).  Rows of long genes go 32 to a tile at most.
+            if (!prm.tile_rows && R->n_genes) {
+                const AlphaSpec al = alpha_spec(R->alphabet);
+                const double len = double(R->capacity) / R->n_genes;
+                const double met = 8.0 + len * double(C->capacity) * std::pow(double(al.sigma), -double(R->k));
+                uint32_t &sh = d.tile_shift[dir];
+                if (len > 512) --sh;
+                while (sh > 2 && double(1u << sh) * met > kHashMax) --sh;
+                while (sh > 2 && (all_rows >> sh) < 512 && (R->n_genes >> (sh - 1)) <= 128) --sh;
+            }
+            rec_est += dir_est * tile_slack(d.tile_shift[dir]) / 4;
             d.tiles_n[dir] = static_cast<uint32_t>((uint64_t(R->n_genes) + (1u << d.tile_shift[dir]) - 1) >>
                                                    d.tile_shift[dir]);
         }
@@ -588,9 +614,6 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         }
         d.bbh_row_base = static_cast<uint32_t>(bbh_rows);
         if (flags & PDP_TASK_BBH) bbh_rows += tk.a->n_genes;
-        // divergent homologs share a fraction of their k-mers: an eighth of the entries per
-        // direction covers the family workloads with room; more needs a capacity retry
-        rec_est += ndirs * ((tk.a->capacity + tk.b->capacity) / 8 + 4096);
         cost[t] = tk.a->capacity + tk.b->capacity;
         P->ab_row.push_back(orow[0]);
         P->ba_row.push_back(orow[1]);
@@ -641,7 +664,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         chunks += d.n_chunks;
         d.cell_base = static_cast<uint32_t>(cells);
         uint32_t tile_local = 0;
-        const uint64_t dir_est = (tasks[t].a->capacity + tasks[t].b->capacity) / 8 + 4096;
+        const uint64_t dir_est = direction_estimate(tasks[t]);
         for (uint32_t dir = 0; dir < 2; ++dir) {
             d.tile_base[dir] = static_cast<uint32_t>(P->tiles.size());
             if (!(d.flags & (1u << dir))) continue;
@@ -663,7 +686,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
                 tl.rcap = 0;
                 P->tiles.push_back(tl);
                 // the direction's estimate split by rows (a direction without genes expects none)
-                tile_est.push_back(nrows ? dir_est * tl.nrows / nrows : 0);
+                tile_est.push_back(nrows ? dir_est * tile_slack(d.tile_shift[dir]) / 4 * tl.nrows / nrows : 0);
             }
         }
         join_tiles = std::max(join_tiles, tile_local);
