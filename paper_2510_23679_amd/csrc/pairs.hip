@@ -1671,32 +1671,67 @@ __global__ __launch_bounds__(256) void k_bbh_pair(uint32_t rows, const uint32_t 
 // maximum in column order.  WRITE = false puts the first kSlab ties in the row's slab and the
 // count in bh_ptr, as the tiles do; WRITE = true writes the rows with more than kSlab ties
 // straight into the CSR output after the scan.
+// A row costs a chain of dependent loads per k-mer (bucket, binary search, postings), so a thread
+// of the long rows' launch searches four k-mers at a time, and rows past kLongRowEntries k-mers, which would each hold
+// one small work-group for most of the launch, go to work-groups of 1024 threads in a launch of
+// their own.  Two genomes of 700 genes, two of them 70,000 letters long, k = 6: 664 us with 256
+// threads and one k-mer at a time, 199 + 28 us so (a row of 70,000 k-mers is then bound by the gathers
+// of its one CU); with every row of 10 x 3000 genes on this path the step keeps its 4.8 ms.
 constexpr uint32_t kLongThreads = 256;
+constexpr uint32_t kLongThreadsBig = 1024;
+constexpr uint32_t kLongRowEntries = 2048;
 constexpr uint32_t kLongGrid = 4096;   // work-groups at most; each takes rows in turn
 
-template <bool WRITE>
-__global__ __launch_bounds__(kLongThreads) void k_long_rows(const DevTask *__restrict__ tasks,
-                                                            const DevLongSeg *__restrict__ segs, uint32_t n_segs,
-                                                            uint32_t n_rows, uint32_t *__restrict__ bh_ptr,
-                                                            uint4 *__restrict__ slab, uint32_t *__restrict__ bh_col,
-                                                            uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
-                                                            uint64_t bh_cap) {
+template <bool WRITE, uint32_t NT>
+__global__ __launch_bounds__(NT) void k_long_rows(const DevTask *__restrict__ tasks,
+                                                  const DevLongSeg *__restrict__ segs, uint32_t n_segs,
+                                                  uint32_t n_rows, uint32_t *__restrict__ bh_ptr,
+                                                  uint4 *__restrict__ slab, uint32_t *__restrict__ bh_col,
+                                                  uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
+                                                  uint64_t bh_cap) {
     // dynamic LDS: the sums of minima per column gene of the block, and with filters the
     // occurrences in the row gene and in the column gene of the shared k-mers (kLongCols each)
     extern __shared__ uint32_t long_lds[];
     uint32_t *acc = long_lds;
     uint32_t *asr = long_lds + kLongCols;
     uint32_t *asc = long_lds + 2 * kLongCols;
-    __shared__ uint32_t red[2 * (kLongThreads / kWave)];
-    constexpr uint32_t NW = kLongThreads / kWave;
+    __shared__ uint32_t red[2 * (NT / kWave)];
+    constexpr uint32_t NW = NT / kWave;
+    constexpr uint32_t kLongThreads = NT, kLongBatch = NT == kLongThreadsBig ? 4 : 1;
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
-    for (uint32_t lr = blockIdx.x; lr < n_rows; lr += gridDim.x) {
+    auto seg_of = [&](uint32_t lr) {
         uint32_t lo = 0, hi = n_segs;  // the last segment whose first row is <= lr (segments are non-empty)
         while (hi - lo > 1) {
             const uint32_t mid = (lo + hi) >> 1;
             if (segs[mid].first <= lr) lo = mid;
             else hi = mid;
         }
+        return lo;
+    };
+    // the long rows' launch: a work-group looks at a stretch of rows, one per thread, and takes the
+    // long ones it finds in turn; the other launch takes every row and leaves those out
+    __shared__ uint32_t s_long[NT == kLongThreadsBig ? kLongThreadsBig : 1];
+    __shared__ uint32_t s_n_long;
+    const uint32_t stretch = NT == kLongThreadsBig ? min(NT, (n_rows + gridDim.x - 1) / gridDim.x) : 1u;
+    for (uint32_t lr0 = blockIdx.x * stretch; lr0 < n_rows; lr0 += gridDim.x * stretch) {
+      uint32_t todo = 1;
+      if constexpr (NT == kLongThreadsBig) {
+        __syncthreads();
+        if (tid == 0) s_n_long = 0;
+        __syncthreads();
+        if (tid < stretch && lr0 + tid < n_rows) {
+            const DevLongSeg sg = segs[seg_of(lr0 + tid)];
+            const DevDict &R = sg.dir == 0 ? tasks[sg.task].a : tasks[sg.task].b;
+            const uint32_t row = lr0 + tid - sg.first;
+            if (load_global(R.mv_ptr + row + 1) - load_global(R.mv_ptr + row) > kLongRowEntries)
+                s_long[atomicAdd(&s_n_long, 1u)] = lr0 + tid;
+        }
+        __syncthreads();
+        todo = s_n_long;
+      }
+      for (uint32_t job = 0; job < todo; ++job) {
+        const uint32_t lr = NT == kLongThreadsBig ? s_long[job] : lr0;
+        const uint32_t lo = seg_of(lr);
         const DevLongSeg sg = segs[lo];
         const DevTask &T = tasks[sg.task];
         const DevDict &R = sg.dir == 0 ? T.a : T.b;
@@ -1705,9 +1740,10 @@ __global__ __launch_bounds__(kLongThreads) void k_long_rows(const DevTask *__res
         const uint32_t grow = T.row_base[sg.dir] + row;
         const uint32_t pos0 = WRITE ? bh_ptr[grow] : 0u;
         if (WRITE && bh_ptr[grow + 1] - pos0 <= kSlab) continue;  // the slab copy placed this row
+        const uint32_t e0 = load_global(R.mv_ptr + row), e1 = load_global(R.mv_ptr + row + 1);
+        if (NT != kLongThreadsBig && e1 - e0 > kLongRowEntries) continue;  // the other launch's row
         const bool filt = T.theta_d || T.tau_d;
         const uint32_t nr = load_global(R.nwin + row);
-        const uint32_t e0 = load_global(R.mv_ptr + row), e1 = load_global(R.mv_ptr + row + 1);
         const uint32_t ncols = C.n_genes;
         const uint32_t nblk = (ncols + kLongCols - 1) / kLongCols;
         // sums of column genes [c0, c0 + cn) into acc / asr / asc
@@ -1720,28 +1756,49 @@ __global__ __launch_bounds__(kLongThreads) void k_long_rows(const DevTask *__res
                 }
             }
             __syncthreads();
-            for (uint32_t e = e0 + tid; e < e1; e += kLongThreads) {
-                const uint64_t code = load_global(R.mv_code + e);
-                const uint32_t cr = load_global(R.mv_cnt + e);
-                const uint32_t b = bucket_of(code, C.k, C.lead, C.bits);
-                if (b >= C.n_buckets) continue;  // not a k-mer of the alphabet: in no index
-                const uint32_t end = load_global(C.ix_dir + b + 1);
-                uint32_t l = load_global(C.ix_dir + b), h = end;  // first entry of the code: entries ascend by (code, gene)
-                while (l < h) {
-                    const uint32_t mid = (l + h) >> 1;
-                    if (load_global(C.ix_code + mid) < code) l = mid + 1;
-                    else h = mid;
+            for (uint32_t first = e0 + tid; first < e1; first += kLongBatch * kLongThreads) {
+                uint64_t code[kLongBatch];
+                uint32_t cr[kLongBatch], l[kLongBatch], h[kLongBatch], end[kLongBatch];
+#pragma unroll
+                for (uint32_t q = 0; q < kLongBatch; ++q) {
+                    const uint32_t e = min(first + q * kLongThreads, e1 - 1);
+                    code[q] = load_global(R.mv_code + e);
+                    cr[q] = load_global(R.mv_cnt + e);
                 }
-                for (uint32_t i = l; i < end && load_global(C.ix_code + i) == code; ++i) {
-                    const uint32_t g = load_global(C.ix_gene + i) - c0;  // genes below c0 wrap past cn
-                    if (g >= cn) continue;
-                    const uint32_t cc = load_global(C.ix_cnt + i);
-                    atomicAdd(&acc[g], min(cr, cc));
-                    if (filt) {
-                        atomicAdd(&asr[g], cr);
-                        atomicAdd(&asc[g], cc);
+                uint32_t most = 0;  // entries of the largest of the batch's buckets
+#pragma unroll
+                for (uint32_t q = 0; q < kLongBatch; ++q) {
+                    const uint32_t b = bucket_of(code[q], C.k, C.lead, C.bits);
+                    // past the row's end, or not a k-mer of the alphabet (in no index): nothing to find
+                    const bool in = first + q * kLongThreads < e1 && b < C.n_buckets;
+                    l[q] = in ? load_global(C.ix_dir + b) : 0u;
+                    end[q] = in ? load_global(C.ix_dir + b + 1) : 0u;
+                }
+#pragma unroll
+                for (uint32_t q = 0; q < kLongBatch; ++q) {
+                    h[q] = end[q];
+                    most = max(most, end[q] - l[q]);
+                }
+                for (; most; most >>= 1)  // first entry of each code: entries ascend by (code, gene)
+#pragma unroll
+                    for (uint32_t q = 0; q < kLongBatch; ++q) {
+                        if (l[q] >= h[q]) continue;
+                        const uint32_t mid = (l[q] + h[q]) >> 1;
+                        if (load_global(C.ix_code + mid) < code[q]) l[q] = mid + 1;
+                        else h[q] = mid;
                     }
-                }
+#pragma unroll
+                for (uint32_t q = 0; q < kLongBatch; ++q)
+                    for (uint32_t i = l[q]; i < end[q] && load_global(C.ix_code + i) == code[q]; ++i) {
+                        const uint32_t g = load_global(C.ix_gene + i) - c0;  // genes below c0 wrap past cn
+                        if (g >= cn) continue;
+                        const uint32_t cc = load_global(C.ix_cnt + i);
+                        atomicAdd(&acc[g], min(cr[q], cc));
+                        if (filt) {
+                            atomicAdd(&asr[g], cr[q]);
+                            atomicAdd(&asc[g], cc);
+                        }
+                    }
             }
             __syncthreads();
         };
@@ -1840,6 +1897,7 @@ __global__ __launch_bounds__(kLongThreads) void k_long_rows(const DevTask *__res
             }
         }
         if (!WRITE && tid == 0) bh_ptr[grow] = pos;
+      }
     }
 }
 
@@ -2100,9 +2158,13 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         PDP_TRY(hipGetLastError());
     }
     const dim3 long_grid(std::min(p.long_rows, kLongGrid));
+    const dim3 long_grid_big(std::min((p.long_rows + 3) / 4, 1024u));
     if (p.long_rows) {
-        hipLaunchKernelGGL(k_long_rows<false>, long_grid, dim3(kLongThreads), p.long_lds, s, w.tasks, w.long_segs, p.n_long_segs,
-                           p.long_rows, bh->ptr, w.slab, nullptr, nullptr, nullptr, 0);
+        hipLaunchKernelGGL((k_long_rows<false, kLongThreadsBig>), long_grid_big, dim3(kLongThreadsBig), p.long_lds, s, w.tasks,
+                           w.long_segs, p.n_long_segs, p.long_rows, bh->ptr, w.slab, nullptr, nullptr, nullptr, 0);
+        PDP_TRY(hipGetLastError());
+        hipLaunchKernelGGL((k_long_rows<false, kLongThreads>), long_grid, dim3(kLongThreads), p.long_lds, s, w.tasks,
+                           w.long_segs, p.n_long_segs, p.long_rows, bh->ptr, w.slab, nullptr, nullptr, nullptr, 0);
         PDP_TRY(hipGetLastError());
     }
     PDP_TRY(mark(PDP_KERNEL_TILE_COUNT, false));
@@ -2121,8 +2183,11 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         PDP_TRY(hipGetLastError());
     }
     if (p.long_rows) {
-        hipLaunchKernelGGL(k_long_rows<true>, long_grid, dim3(kLongThreads), p.long_lds, s, w.tasks, w.long_segs, p.n_long_segs,
-                           p.long_rows, bh->ptr, nullptr, bh->col, bh->num, bh->den, bh->capacity);
+        hipLaunchKernelGGL((k_long_rows<true, kLongThreadsBig>), long_grid_big, dim3(kLongThreadsBig), p.long_lds, s, w.tasks,
+                           w.long_segs, p.n_long_segs, p.long_rows, bh->ptr, nullptr, bh->col, bh->num, bh->den, bh->capacity);
+        PDP_TRY(hipGetLastError());
+        hipLaunchKernelGGL((k_long_rows<true, kLongThreads>), long_grid, dim3(kLongThreads), p.long_lds, s, w.tasks,
+                           w.long_segs, p.n_long_segs, p.long_rows, bh->ptr, nullptr, bh->col, bh->num, bh->den, bh->capacity);
         PDP_TRY(hipGetLastError());
     }
     if (p.colmax && p.bh_rows) {
