@@ -38,20 +38,6 @@ using GjMap = uint32_t;  // the dictionaries of a thread's consecutive flat entr
 static_assert(kGjPer == sizeof(GjMap), "a thread maps its entries as one word");
 static_assert(kGroupMaxDicts <= kGjThreads, "one dictionary per thread in the set-up");
 
-// Descriptor cursors of the tiles: tile t's part of the descriptors is that of its genes' entries in
-// the source's multiplicity vectors; descriptors with postings fill it from the front, inline ones
-// from the back.
-__global__ __launch_bounds__(256) void k_group_init(const DevGroupDict *__restrict__ dicts,
-                                                    const DevGroupTile *__restrict__ tiles, uint32_t n_tiles,
-                                                    uint32_t *__restrict__ cursor) {
-    for (uint32_t t = blockIdx.x * 256u + threadIdx.x; t < n_tiles; t += gridDim.x * 256u) {
-        const DevGroupTile tl = tiles[t];
-        const DevGroupDict &d = dicts[tl.dict];
-        cursor[static_cast<uint64_t>(t) * kGroupCursorStride] = d.desc_base + load_global(d.mv_ptr + tl.g0);
-        cursor[static_cast<uint64_t>(t) * kGroupCursorStride + 1] = d.desc_base + load_global(d.mv_ptr + tl.g0 + tl.ng);
-    }
-}
-
 // A k-mer's identity inside an item: the low word of its code when the item's codes span less
 // than 2^32 (the plan checks it), else the whole code.
 template <bool WIDE>
@@ -797,11 +783,6 @@ __global__ __launch_bounds__(kGtThreads) void k_group_tile(const DevGroupDict *_
 
 hipError_t launch_group_join(const PlanShape &p, const PairWs &w, hipStream_t s) {
     if (!p.n_gdicts) return hipSuccess;
-    if (p.n_gtiles) {
-        hipLaunchKernelGGL(k_group_init, dim3(std::min<uint32_t>(1024, (p.n_gtiles + 255) / 256)), dim3(256), 0, s,
-                           w.gdicts, w.gtiles, p.n_gtiles, w.gcursor);
-        PDP_TRY(hipGetLastError());
-    }
     const uint32_t dyn = sizeof(GjDict) * p.gmax_dicts;
     const GjOut out{w.gpost, w.gaux, w.gdesc, w.gcursor, p.gene_bits};
     if (p.n_gitems) {

@@ -39,7 +39,7 @@ constexpr uint32_t kHashMax = kHashSlots * 3 / 4;  // records one table pass tak
 constexpr uint32_t kDefaultLdsBudget = 8 * kTileCap;
 constexpr uint32_t kMaxTileLds = 160 * 1024 - 4096;  // gfx950 LDS per work-group, less the static part
 constexpr uint32_t kSlab = 4;                // best hits per row kept by the first tile pass
-constexpr uint32_t kCounterWords = 16;       // launch counters in the workspace
+constexpr uint32_t kCounterWords = 32;       // launch counters in the workspace
 constexpr uint32_t kLongCols = 4096;         // long-gene path: column genes per LDS block (one word per sum)
 
 inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
@@ -257,6 +257,10 @@ struct PairWs {
     // a cursor for rows with more than kSlab ties, and the candidate list with its count
     unsigned long long *colkey;
     uint32_t *colcursor;
+    uint32_t *big_rows;           // rows with more than kSlab hits from the candidates
+    uint32_t *n_big;              // counters word 17
+    uint32_t *join_done;          // counters word 16: ended work-groups of the join's count pass
+    uint32_t *partials2;          // scan scratch of more than 1024 row groups
     uint4 *cands;
     uint32_t *cand_count;         // counters word 6
     DevLongSeg *long_segs;        // long-gene path, by first row

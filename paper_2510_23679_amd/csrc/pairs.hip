@@ -17,7 +17,7 @@
 //     totals gives every tile its exact range, k_join (write pass) writes the records
 //     there, and the regions are refitted to those counts for the next launch.  With no
 //     overflow these kernels exit at once.  PDP_PARAM_TWO_PASS runs the two passes alone.
-//  3. k_tile_ranges: each tile's record range for the tile pass.
+//  3. The same kernels leave each tile's record range for the tile pass.
 //  4. k_tile_count: one work-group per tile sums the tile's records into m per
 //     (row, column) in an LDS hash table, finds each row's maximum of
 //     J = m/d by exact cross-multiplication, and counts the columns that reach
@@ -395,8 +395,16 @@ __device__ __forceinline__ void join_chunk(uint32_t chunk, const DevTask *__rest
     __syncthreads();
 }
 
-__global__ void k_pairs_init(pdp_status *st, uint32_t *counters, uint32_t *tile_tot, uint32_t *fill, uint32_t n_tiles) {
-    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x;
+// Set-up of a launch: status, counters, the tiles' record counts; with column maxima the best-hit
+// counts (the column genomes' rows are counted by atomics) and the column keys; the group tiles'
+// descriptor cursors (a tile's part of the descriptors is that of its genes' entries in the source's
+// multiplicity vectors: descriptors with postings fill it from the front, inline ones from the back).
+__global__ __launch_bounds__(256) void k_pairs_init(pdp_status *st, uint32_t *counters, uint32_t *tile_tot, uint32_t *fill,
+                                                    uint32_t n_tiles, uint32_t *bh_ptr, unsigned long long *colkey,
+                                                    uint64_t n_rows, const DevGroupDict *__restrict__ gdicts,
+                                                    const DevGroupTile *__restrict__ gtiles, uint32_t n_gtiles,
+                                                    uint32_t *__restrict__ gcursor) {
+    const uint64_t i0 = blockIdx.x * 256ull + threadIdx.x, stride = gridDim.x * 256ull;
     if (i0 == 0) {
         st->code = 0;
         st->flags = 0;
@@ -404,9 +412,19 @@ __global__ void k_pairs_init(pdp_status *st, uint32_t *counters, uint32_t *tile_
         st->where = ~0ull;
     }
     if (i0 < kCounterWords) counters[i0] = 0;
-    for (uint32_t t = i0; t < n_tiles; t += gridDim.x * blockDim.x) {
+    for (uint64_t t = i0; t < n_tiles; t += stride) {
         tile_tot[t] = 0;
         fill[t] = 0;
+    }
+    for (uint64_t r = i0; r < n_rows; r += stride) {
+        bh_ptr[r] = 0;
+        colkey[r] = 0;
+    }
+    for (uint64_t t = i0; t < n_gtiles; t += stride) {
+        const DevGroupTile tl = gtiles[t];
+        const DevGroupDict &d = gdicts[tl.dict];
+        gcursor[t * kGroupCursorStride] = d.desc_base + load_global(d.mv_ptr + tl.g0);
+        gcursor[t * kGroupCursorStride + 1] = d.desc_base + load_global(d.mv_ptr + tl.g0 + tl.ng);
     }
 }
 
@@ -419,18 +437,73 @@ __device__ __forceinline__ bool join_overflow(const unsigned long long *total, u
     return true;
 }
 
+// The tiles' record ranges: what the tile kernels read, laid out by the first two-pass kernel.
+struct TileRanges {
+    DevTile *tiles;
+    uint32_t n_tiles;
+    const uint32_t *fill;  // records reserved in each region by the one-pass join (null: it did not run)
+    uint32_t *tile_off;
+    uint2 *rng;
+    uint32_t *done;        // work-groups of the count pass that have ended
+};
+
+// After the one-pass join: each region's filled part.
+__device__ __forceinline__ void ranges_filled(const TileRanges &R) {
+    for (uint32_t t = blockIdx.x * kJoinThreads + threadIdx.x; t < R.n_tiles; t += gridDim.x * kJoinThreads) {
+        const uint32_t b = R.tiles[t].rbase;
+        R.rng[t] = make_uint2(b, b + min(R.fill[t], R.tiles[t].rcap));
+    }
+}
+
+// After the count pass, by the work-group that ends last: the exclusive scan of the tiles' record
+// totals gives every tile its exact range.  When the two passes back up the one-pass join (and the
+// records fit the capacity), the regions are refitted to these counts: tile t's region starts at
+// off_t + floor(slack * off_t / total), with slack the capacity left over, so every region holds its
+// count and the regions still fill the capacity.  The next launch of the plan on the same
+// dictionaries then fits in one pass.
+__device__ __forceinline__ void ranges_counted(const TileRanges &R, const uint32_t *tile_tot,
+                                               const unsigned long long *total_ptr, uint64_t rec_cap, uint32_t *scan,
+                                               uint32_t *last) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        *last = atomicAdd(R.done, 1u) + 1u == gridDim.x ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!*last) return;
+    const uint64_t total = __hip_atomic_load(total_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool refit = R.fill != nullptr && total <= rec_cap && total > 0;
+    const uint64_t slack = refit ? rec_cap - total : 0;
+    uint32_t carry = 0;
+    for (uint32_t base = 0; base < R.n_tiles; base += kJoinThreads) {
+        const uint32_t t = base + threadIdx.x;
+        const uint32_t v = t < R.n_tiles ? __hip_atomic_load(&tile_tot[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        uint32_t sum;
+        const uint32_t o0 = carry + block_exclusive_scan<kJoinThreads>(v, scan, &sum), o1 = o0 + v;
+        carry += sum;
+        if (t >= R.n_tiles) continue;
+        R.tile_off[t] = o0;
+        R.rng[t] = make_uint2(o0, o1);
+        if (refit) {
+            const uint64_t r0 = o0 + slack * o0 / total, r1 = o1 + slack * o1 / total;
+            R.tiles[t].rbase = static_cast<uint32_t>(r0);
+            R.tiles[t].rcap = static_cast<uint32_t>(r1 - r0);
+        }
+    }
+    if (threadIdx.x == 0) R.tile_off[R.n_tiles] = carry;
+}
+
 template <bool WRITE>
 __global__ __launch_bounds__(kJoinThreads) void k_join(const DevTask *__restrict__ tasks, uint32_t n_tasks,
                                                        uint32_t *__restrict__ cells, uint32_t *__restrict__ tile_tot,
                                                        const uint32_t *__restrict__ tile_off,
                                                        unsigned long long *__restrict__ total,
                                                        uint2 *__restrict__ recs, uint64_t rec_cap, pdp_status *st,
-                                                       const uint32_t *__restrict__ gate) {
+                                                       TileRanges R) {
     __shared__ JoinLds<WRITE> L;
-    if (gate && *gate == 0u) return;  // backing up the one-pass join, which did not overflow
-    if (!WRITE && gate && blockIdx.x == 0 && threadIdx.x == 0) st->flags |= PDP_STATUS_TWO_PASS;
     if (WRITE && join_overflow(total, rec_cap, st)) return;
     join_chunk<WRITE>(blockIdx.x, tasks, n_tasks, cells, tile_tot, tile_off, total, recs, rec_cap, L);
+    if (!WRITE) ranges_counted(R, tile_tot, total, rec_cap, L.scan, &L.found);
 }
 
 // Persistent form: a fixed grid claims join items kClaimJoin at a time from a counter
@@ -446,9 +519,12 @@ __global__ __launch_bounds__(kJoinThreads) void k_join_persistent(const DevTask 
                                                                   unsigned long long *__restrict__ total,
                                                                   uint2 *__restrict__ recs, uint64_t rec_cap,
                                                                   pdp_status *st, uint32_t *__restrict__ next,
-                                                                  const uint32_t *__restrict__ gate) {
+                                                                  const uint32_t *__restrict__ gate, TileRanges R) {
     __shared__ JoinLds<WRITE> L;
-    if (gate && *gate == 0u) return;  // backing up the one-pass join, which did not overflow
+    if (gate && *gate == 0u) {  // backing up the one-pass join, which did not overflow
+        if (!WRITE) ranges_filled(R);
+        return;
+    }
     if (!WRITE && gate && blockIdx.x == 0 && threadIdx.x == 0) st->flags |= PDP_STATUS_TWO_PASS;
     if (WRITE && join_overflow(total, rec_cap, st)) return;
     for (;;) {
@@ -461,6 +537,7 @@ __global__ __launch_bounds__(kJoinThreads) void k_join_persistent(const DevTask 
         for (uint32_t chunk = first; chunk < last; ++chunk)
             join_chunk<WRITE>(chunk, tasks, n_tasks, cells, tile_tot, tile_off, total, recs, rec_cap, L);
     }
+    if (!WRITE) ranges_counted(R, tile_tot, total, rec_cap, L.scan, &L.found);
 }
 
 // ------------------------------------------------------------------ one-pass join
@@ -844,36 +921,6 @@ __global__ __launch_bounds__(kJoinThreads, 6) void k_join_fused_persistent(
             for (uint32_t j = first; j < last; ++j)
                 fused_chunk(xcd_item(x + kXcds * j, total_chunks), tasks, items, fill, tiles, fallback, recs, L,
                             join_dyn, join_dyn + join_tiles, join_tiles);
-        }
-    }
-}
-
-// Each tile's record range for the tile kernels: its region's filled part after the
-// one-pass join, its scanned range after the two-pass join.  When the two passes backed up
-// the one-pass join (and the records fitted the capacity), the regions are refitted to this
-// launch's exact counts: tile t's region starts at off_t + floor(slack * off_t / total), with
-// off_t its scanned offset and slack the capacity left over, so every region holds its count
-// and the regions still fill the capacity.  The next launch of the plan on the same
-// dictionaries then fits in one pass.
-__global__ void k_tile_ranges(DevTile *__restrict__ tiles, uint32_t n_tiles, const uint32_t *__restrict__ tile_off,
-                              const uint32_t *__restrict__ fill, const uint32_t *__restrict__ fallback,
-                              uint64_t rec_cap, uint2 *__restrict__ rng) {
-    const bool two = fill == nullptr || *fallback != 0u;
-    const uint64_t total = tile_off[n_tiles];
-    const bool refit = fill != nullptr && two && total <= rec_cap && total > 0;
-    const uint64_t slack = refit ? rec_cap - total : 0;
-    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n_tiles; t += gridDim.x * blockDim.x) {
-        if (two) {
-            const uint32_t o0 = tile_off[t], o1 = tile_off[t + 1];
-            rng[t] = make_uint2(o0, o1);
-            if (refit) {
-                const uint64_t r0 = o0 + slack * o0 / total, r1 = o1 + slack * o1 / total;
-                tiles[t].rbase = static_cast<uint32_t>(r0);
-                tiles[t].rcap = static_cast<uint32_t>(r1 - r0);
-            }
-        } else {
-            const uint32_t b = tiles[t].rbase;
-            rng[t] = make_uint2(b, b + min(fill[t], tiles[t].rcap));
         }
     }
 }
@@ -1455,19 +1502,63 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_write(const DevTask *__re
                            bh_num, bh_den, bh_cap, nullptr, nullptr, lds, S, ColWs{});
 }
 
-// One thread per best-hit row: the slab entries of a row with at most kSlab ties go to the CSR output.
-__global__ __launch_bounds__(256) void k_slab_copy(uint32_t bh_rows, const uint32_t *__restrict__ bh_ptr,
-                                                   const uint4 *__restrict__ slab, uint32_t *__restrict__ bh_col,
-                                                   uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
-                                                   uint64_t bh_cap, pdp_status *st) {
-    const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r == 0 && bh_ptr[bh_rows] > bh_cap) raise_status(st, PDP_E_CAPACITY, bh_ptr[bh_rows], 1);
-    if (r >= bh_rows) return;
-    const uint32_t p = bh_ptr[r], n = bh_ptr[r + 1] - p;
-    if (n > kSlab) return;
+// Row counts become row pointers group by group (256 rows, a row per thread): sums of the groups, then
+// each group adds those before it (up to kRowGroups groups; past them the sums are scanned in
+// between) and uses its pointers at once.  (16 rows per thread: 0.35 ms for the BBH of 5.0e6 rows
+// against 0.24, the rows' dependent loads one after another.)
+constexpr uint32_t kRowThreads = 256;
+constexpr uint32_t kRowGroups = 2048;
+
+__global__ __launch_bounds__(kRowThreads) void k_rows_sum(const uint32_t *__restrict__ cnt, uint32_t n,
+                                                          uint32_t *__restrict__ partials) {
+    __shared__ uint32_t tmp[kRowThreads / kWave + 1];
+    const uint32_t r = blockIdx.x * kRowThreads + threadIdx.x;
+    uint32_t total;
+    (void)block_exclusive_scan<kRowThreads>(r < n ? cnt[r] : 0u, tmp, &total);
+    if (threadIdx.x == 0) partials[blockIdx.x] = total;
+}
+
+// The pointer of this thread's row (ptr[] holds the rows' counts), also left in ptr; *cnt its count.  The
+// last group writes ptr[n]; *total: the end of the group's rows.  SUMMED: partials are the groups'
+// sums, else already scanned.  Contains barriers.
+template <bool SUMMED>
+__device__ __forceinline__ uint32_t row_pointer(uint32_t *__restrict__ ptr, uint32_t n, const uint32_t *__restrict__ partials,
+                                                uint32_t *tmp, uint32_t *cnt, uint32_t *total) {
+    const uint32_t r = blockIdx.x * kRowThreads + threadIdx.x;
+    const uint32_t c = r < n ? ptr[r] : 0u;
+    uint32_t before = 0, all;
+    if constexpr (SUMMED) {
+        uint32_t mine = 0;
+        for (uint32_t g = threadIdx.x; g < blockIdx.x; g += kRowThreads) mine += partials[g];
+        (void)block_exclusive_scan<kRowThreads>(mine, tmp, &before);
+    } else {
+        before = partials[blockIdx.x];
+    }
+    const uint32_t p = before + block_exclusive_scan<kRowThreads>(c, tmp, &all);
+    if (r < n) ptr[r] = p;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) ptr[n] = before + all;
+    *cnt = c;
+    *total = before + all;
+    return p;
+}
+
+// Best-hit counts to row pointers, and the slab entries of every row with at most kSlab ties to the
+// CSR output.
+template <bool SUMMED>
+__global__ __launch_bounds__(kRowThreads) void k_rows_slab(uint32_t bh_rows, uint32_t *__restrict__ bh_ptr,
+                                                           const uint32_t *__restrict__ partials,
+                                                           const uint4 *__restrict__ slab, uint32_t *__restrict__ bh_col,
+                                                           uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
+                                                           uint64_t bh_cap, pdp_status *st) {
+    __shared__ uint32_t tmp[kRowThreads / kWave + 1];
+    uint32_t n, end;
+    const uint32_t p = row_pointer<SUMMED>(bh_ptr, bh_rows, partials, tmp, &n, &end);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0 && end > bh_cap) raise_status(st, PDP_E_CAPACITY, end, 1);
+    if (n == 0 || n > kSlab) return;
+    const uint64_t r = uint64_t(blockIdx.x) * kRowThreads + threadIdx.x;
     uint4 e[kSlab];
 #pragma unroll
-    for (uint32_t i = 0; i < kSlab; ++i) e[i] = i < n ? slab[static_cast<uint64_t>(r) * kSlab + i] : make_uint4(~0u, 0, 0, 0);
+    for (uint32_t i = 0; i < kSlab; ++i) e[i] = i < n ? slab[r * kSlab + i] : make_uint4(~0u, 0, 0, 0);
     // the first tile launch leaves a row's ties in any order: insertion sort by column
 #pragma unroll
     for (uint32_t i = 1; i < kSlab; ++i)
@@ -1491,7 +1582,8 @@ __global__ __launch_bounds__(256) void k_slab_copy(uint32_t bh_rows, const uint3
 // is a best hit of the column's gene (Alg. 3's test S[l,k] = max_r S[r,k]).  The count goes
 // to the BA row's bh_ptr and the first kSlab hits to its slab, as the tiles do for AB rows.
 __global__ __launch_bounds__(256) void k_colmax_rows(ColWs cmx, uint32_t *__restrict__ bh_ptr, uint4 *__restrict__ slab,
-                                                     pdp_status *st) {
+                                                     uint32_t *__restrict__ cursor, uint32_t *__restrict__ big,
+                                                     uint32_t *__restrict__ n_big, pdp_status *st) {
     const uint32_t n = *cmx.count;
     if (blockIdx.x == 0 && threadIdx.x == 0 && n > cmx.cap) raise_status(st, PDP_E_CAPACITY, n, 0);
     const uint64_t lim = min(static_cast<uint64_t>(n), cmx.cap);
@@ -1499,16 +1591,24 @@ __global__ __launch_bounds__(256) void k_colmax_rows(ColWs cmx, uint32_t *__rest
         const uint4 c = cmx.cands[i];
         if (colmax_key(c.z, c.w) != cmx.key[c.x]) continue;
         const uint32_t t = atomicAdd(&bh_ptr[c.x], 1u);
-        if (t < kSlab) slab[static_cast<uint64_t>(c.x) * kSlab + t] = make_uint4(c.y, c.z, c.w, 0);
+        if (t < kSlab) {
+            slab[static_cast<uint64_t>(c.x) * kSlab + t] = make_uint4(c.y, c.z, c.w, 0);
+        } else if (t == kSlab) {  // one thread per row: the row is listed, its cursor cleared
+            cursor[c.x] = 0;
+            big[atomicAdd(n_big, 1u)] = c.x;
+        }
     }
 }
 
-// After the scan: hits of BA rows with more than kSlab of them go straight to the CSR (in
-// any order; k_colmax_sort orders those rows), slots taken from a per-row cursor.
+// After the scan: hits of listed rows, those with more than kSlab of them, go straight to the CSR
+// (in any order; k_colmax_sort orders those rows), slots taken from a per-row cursor.  Mostly there
+// are none, and nothing is read.
 __global__ __launch_bounds__(256) void k_colmax_big(ColWs cmx, uint32_t *__restrict__ cursor,
+                                                    const uint32_t *__restrict__ n_big,
                                                     const uint32_t *__restrict__ bh_ptr, uint32_t *__restrict__ bh_col,
                                                     uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
                                                     uint64_t bh_cap) {
+    if (*n_big == 0u) return;
     const uint64_t lim = min(static_cast<uint64_t>(*cmx.count), cmx.cap);
     for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < lim; i += gridDim.x * 256ull) {
         const uint4 c = cmx.cands[i];
@@ -1524,40 +1624,56 @@ __global__ __launch_bounds__(256) void k_colmax_big(ColWs cmx, uint32_t *__restr
     }
 }
 
-// One thread per row that k_colmax_big filled: insertion sort of its hits by column.
-__global__ __launch_bounds__(256) void k_colmax_sort(uint32_t bh_rows, const uint32_t *__restrict__ cursor,
-                                                     const uint32_t *__restrict__ bh_ptr, uint32_t *__restrict__ bh_col,
-                                                     uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
-                                                     uint64_t bh_cap) {
-    const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= bh_rows || !cursor[r]) return;
-    const uint64_t p0 = bh_ptr[r], p1 = min(static_cast<uint64_t>(bh_ptr[r + 1]), bh_cap);
-    for (uint64_t x = p0 + 1; x < p1; ++x) {
-        const uint32_t c = bh_col[x], m = bh_num[x], d = bh_den[x];
-        uint64_t y = x;
-        while (y > p0 && bh_col[y - 1] > c) {
-            bh_col[y] = bh_col[y - 1];
-            bh_num[y] = bh_num[y - 1];
-            bh_den[y] = bh_den[y - 1];
-            --y;
+// One wave per row that k_colmax_big filled, its hits ordered by column: up to 64 by their ranks, more
+// by a network in place.
+__global__ __launch_bounds__(kWave) void k_colmax_sort(const uint32_t *__restrict__ big, const uint32_t *__restrict__ n_big,
+                                                       const uint32_t *__restrict__ bh_ptr, uint32_t *__restrict__ bh_col,
+                                                       uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
+                                                       uint64_t bh_cap) {
+    const uint32_t rows = *n_big;
+    for (uint32_t i = blockIdx.x; i < rows; i += gridDim.x) {
+        const uint32_t r = big[i];
+        const uint64_t p0 = min(static_cast<uint64_t>(bh_ptr[r]), bh_cap);
+        const uint32_t n = static_cast<uint32_t>(min(static_cast<uint64_t>(bh_ptr[r + 1]), bh_cap) - p0);
+        uint32_t *col = bh_col + p0, *num = bh_num + p0, *den = bh_den + p0;
+        if (n <= kWave) {
+            const bool in = threadIdx.x < n;
+            const uint32_t c = in ? col[threadIdx.x] : ~0u, m = in ? num[threadIdx.x] : 0u, d = in ? den[threadIdx.x] : 0u;
+            uint32_t at = 0;
+            for (uint32_t x = 0; x < n; ++x) at += static_cast<uint32_t>(__shfl(c, x, kWave)) < c;  // columns are distinct
+            if (in) {
+                col[at] = c;
+                num[at] = m;
+                den[at] = d;
+            }
+        } else {
+            wg_network_sort(n, [&](uint32_t lo, uint32_t hi) {
+                const uint32_t cl = col[lo], ch = col[hi];
+                if (ch >= cl) return;
+                col[lo] = ch;
+                col[hi] = cl;
+                uint32_t x = num[lo];
+                num[lo] = num[hi];
+                num[hi] = x;
+                x = den[lo];
+                den[lo] = den[hi];
+                den[hi] = x;
+            });
         }
-        bh_col[y] = c;
-        bh_num[y] = m;
-        bh_den[y] = d;
     }
 }
 
-// BBH of one row: keep each best hit (a, b) whose reverse row contains a.  Every read stays
+// BBH of one row: keep each best hit (a, b) whose reverse row contains a; pairs go to pos on (WRITE),
+// and the place after the last one comes back (from 0: their number).  Every read stays
 // inside the best-hit arrays' capacity (bh_cap) and a column b outside the reverse rows
 // (ncols) is skipped, so a corrupt or overflowed input cannot send the walk out of bounds;
 // the callers stop before this when the best-hit output overflowed.
 template <bool WRITE>
-__device__ __forceinline__ void bbh_row(uint32_t a, uint32_t grow, uint32_t rab, uint32_t ba_base, uint32_t ncols,
-                                        const uint32_t *ab_ptr, const uint32_t *ab_col, const uint32_t *ab_num,
-                                        const uint32_t *ab_den, uint64_t ab_cap, const uint32_t *ba_ptr,
-                                        const uint32_t *ba_col, uint64_t ba_cap, uint32_t *out_ptr, uint32_t *out_a,
-                                        uint32_t *out_b, uint32_t *out_num, uint32_t *out_den, uint64_t cap) {
-    uint32_t pos = WRITE ? out_ptr[grow] : 0u;
+__device__ __forceinline__ uint32_t bbh_row(uint32_t a, uint32_t pos, uint32_t rab, uint32_t ba_base, uint32_t ncols,
+                                            const uint32_t *ab_ptr, const uint32_t *ab_col, const uint32_t *ab_num,
+                                            const uint32_t *ab_den, uint64_t ab_cap, const uint32_t *ba_ptr,
+                                            const uint32_t *ba_col, uint64_t ba_cap, uint32_t *out_a, uint32_t *out_b,
+                                            uint32_t *out_num, uint32_t *out_den, uint64_t cap) {
     const uint64_t pend = min(static_cast<uint64_t>(ab_ptr[rab + 1]), ab_cap);
     for (uint64_t p = ab_ptr[rab]; p < pend; ++p) {
         const uint32_t b = ab_col[p];
@@ -1582,7 +1698,7 @@ __device__ __forceinline__ void bbh_row(uint32_t a, uint32_t grow, uint32_t rab,
             ++pos;
         }
     }
-    if (!WRITE) out_ptr[grow] = pos;
+    return pos;
 }
 
 // The task table is stored in processing order (largest tasks first); order[]
@@ -1598,30 +1714,58 @@ __device__ __forceinline__ uint32_t find_bbh_task(const DevTask *tasks, const ui
     return order[lo];
 }
 
-// BBH of a plan: one thread per BBH row.  When an earlier kernel of the launch raised an
-// error (record or best-hit capacity, the best-hit entries then being incomplete), no row
-// is walked: the count pass writes zeros and the write pass writes nothing.
+// BBH of a plan, a thread per row: the count pass leaves the rows' counts in
+// out_ptr and the groups' sums in partials, the write pass turns the counts into row pointers and
+// writes the pairs.  When an earlier kernel of the launch raised an error (record or best-hit
+// capacity, the best-hit entries then being incomplete), no row is walked: the count pass writes
+// zeros and the write pass nothing but pointers.
+struct BbhArgs {
+    const DevTask *__restrict__ tasks;
+    const uint32_t *__restrict__ order;
+    uint32_t n_tasks, bbh_rows, bh_rows;
+    const uint32_t *__restrict__ bh_ptr;
+    const uint32_t *__restrict__ bh_col;
+    const uint32_t *__restrict__ bh_num;
+    const uint32_t *__restrict__ bh_den;
+    uint64_t bh_cap;
+    uint32_t *__restrict__ out_ptr;
+    uint32_t *__restrict__ out_a;
+    uint32_t *__restrict__ out_b;
+    uint32_t *__restrict__ out_num;
+    uint32_t *__restrict__ out_den;
+    uint64_t cap;
+    uint32_t *__restrict__ partials;
+    pdp_status *st;
+};
+// A row's pairs, counted (pos null) or written from *pos on.
 template <bool WRITE>
-__global__ __launch_bounds__(256) void k_bbh(const DevTask *__restrict__ tasks, const uint32_t *__restrict__ order,
-                                             uint32_t n_tasks, uint32_t bbh_rows, uint32_t bh_rows,
-                                             const uint32_t *__restrict__ bh_ptr, const uint32_t *__restrict__ bh_col,
-                                             const uint32_t *__restrict__ bh_num, const uint32_t *__restrict__ bh_den,
-                                             uint64_t bh_cap, uint32_t *__restrict__ out_ptr, uint32_t *__restrict__ out_a,
-                                             uint32_t *__restrict__ out_b, uint32_t *__restrict__ out_num,
-                                             uint32_t *__restrict__ out_den, uint64_t cap, pdp_status *st) {
-    const uint32_t grow = blockIdx.x * blockDim.x + threadIdx.x;
-    if (grow >= bbh_rows) return;
-    if (st->code != 0 || bh_ptr[bh_rows] > bh_cap) {
-        if (!WRITE) out_ptr[grow] = 0;
-        return;
-    }
-    if (WRITE && grow == 0 && out_ptr[bbh_rows] > cap) raise_status(st, PDP_E_CAPACITY, out_ptr[bbh_rows], 2);
-    const DevTask &T = tasks[find_bbh_task(tasks, order, n_tasks, grow)];
+__device__ __forceinline__ uint32_t bbh_plan_row(const BbhArgs &A, uint32_t grow, uint32_t pos) {
+    const DevTask &T = A.tasks[find_bbh_task(A.tasks, A.order, A.n_tasks, grow)];
     const uint32_t a = grow - T.bbh_row_base;  // a gene of the caller's a
     const bool sw = T.flags & kTaskSwapped;    // the caller's a is the task's b
     const uint32_t ab_base = T.row_base[sw ? 1 : 0], ba_base = T.row_base[sw ? 0 : 1];
-    bbh_row<WRITE>(a, grow, ab_base + a, ba_base, sw ? T.a.n_genes : T.b.n_genes, bh_ptr, bh_col, bh_num, bh_den, bh_cap,
-                   bh_ptr, bh_col, bh_cap, out_ptr, out_a, out_b, out_num, out_den, cap);
+    return bbh_row<WRITE>(a, pos, ab_base + a, ba_base, sw ? T.a.n_genes : T.b.n_genes, A.bh_ptr, A.bh_col, A.bh_num,
+                          A.bh_den, A.bh_cap, A.bh_ptr, A.bh_col, A.bh_cap, A.out_a, A.out_b, A.out_num, A.out_den, A.cap);
+}
+__device__ __forceinline__ bool bbh_stopped(const BbhArgs &A) { return A.st->code != 0 || A.bh_ptr[A.bh_rows] > A.bh_cap; }
+
+__global__ __launch_bounds__(kRowThreads) void k_bbh_count(BbhArgs A) {
+    __shared__ uint32_t tmp[kRowThreads / kWave + 1];
+    const uint32_t r = blockIdx.x * kRowThreads + threadIdx.x;
+    const uint32_t n = r < A.bbh_rows && !bbh_stopped(A) ? bbh_plan_row<false>(A, r, 0) : 0u;
+    if (r < A.bbh_rows) A.out_ptr[r] = n;
+    uint32_t total;
+    (void)block_exclusive_scan<kRowThreads>(n, tmp, &total);
+    if (threadIdx.x == 0) A.partials[blockIdx.x] = total;
+}
+
+template <bool SUMMED>
+__global__ __launch_bounds__(kRowThreads) void k_bbh_write(BbhArgs A) {
+    __shared__ uint32_t tmp[kRowThreads / kWave + 1];
+    uint32_t n, end;
+    const uint32_t p = row_pointer<SUMMED>(A.out_ptr, A.bbh_rows, A.partials, tmp, &n, &end);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0 && end > A.cap) raise_status(A.st, PDP_E_CAPACITY, end, 2);
+    if (n) (void)bbh_plan_row<true>(A, blockIdx.x * kRowThreads + threadIdx.x, p);  // after an error every count is zero
 }
 
 // pdp_bbh: the two best-hit outputs are the caller's.  A total past an output's capacity
@@ -1655,8 +1799,9 @@ __global__ __launch_bounds__(256) void k_bbh_pair(uint32_t rows, const uint32_t 
             return;
         }
     }
-    bbh_row<WRITE>(a, a, a, 0, ba_rows, ab_ptr, ab_col, ab_num, ab_den, ab_cap, ba_ptr, ba_col, ba_cap, out_ptr, out_a,
-                   out_b, out_num, out_den, cap);
+    const uint32_t end = bbh_row<WRITE>(a, WRITE ? out_ptr[a] : 0u, a, 0, ba_rows, ab_ptr, ab_col, ab_num, ab_den, ab_cap,
+                                        ba_ptr, ba_col, ba_cap, out_a, out_b, out_num, out_den, cap);
+    if (!WRITE) out_ptr[a] = end;
 }
 
 // ------------------------------------------------------------------ long genes
@@ -1955,8 +2100,9 @@ hipError_t allow_tile_lds(uint32_t tile_lds) {
     return hipSuccess;
 }
 
+static uint64_t row_groups(uint32_t rows) { return (uint64_t(rows) + kRowThreads - 1) / kRowThreads; }
 static uint64_t pair_partials(const PlanShape &p) {
-    return std::max({scan_partials(p.total_tiles), scan_partials(p.bh_rows), scan_partials(p.bbh_rows)});
+    return std::max({uint64_t(scan_partials(p.total_tiles)), row_groups(p.bh_rows), row_groups(p.bbh_rows)}) + 1;
 }
 
 uint64_t pair_ws_bytes(const PlanShape &p) {
@@ -1975,10 +2121,11 @@ uint64_t pair_ws_bytes(const PlanShape &p) {
     s += align_up(8 * (uint64_t(p.total_tiles) + 1), A);  // record range of each tile
     s += align_up(16 * kSlab * (uint64_t(p.bh_rows) + 1), A);
     s += align_up(4 * (uint64_t(p.total_tiles) + 1), A);
-    s += align_up(4 * pair_partials(p), A);
+    s += align_up(4 * pair_partials(p), A) + align_up(4 * (pair_partials(p) / 4096 + 2), A);
     const uint64_t colrows = p.colmax ? uint64_t(p.bh_rows) + 1 : 1;
     s += align_up(8 * colrows, A);                                  // column keys
     s += align_up(4 * colrows, A);                                  // big-row cursors
+    s += align_up(4 * colrows, A);                                  // big rows
     s += align_up(16 * std::max<uint64_t>(p.colmax ? p.cand_cap : 0, 1), A);  // candidates
     s += align_up(sizeof(DevLongSeg) * std::max<uint64_t>(p.n_long_segs, 1), A);
     if (p.n_gdicts) {
@@ -2020,9 +2167,13 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
     w.slab = reinterpret_cast<uint4 *>(take(16 * kSlab * (uint64_t(p.bh_rows) + 1)));
     w.overflow_tiles = reinterpret_cast<uint32_t *>(take(4 * (uint64_t(p.total_tiles) + 1)));
     w.partials = reinterpret_cast<uint32_t *>(take(4 * pair_partials(p)));
+    w.partials2 = reinterpret_cast<uint32_t *>(take(4 * (pair_partials(p) / 4096 + 2)));
+    w.join_done = reinterpret_cast<uint32_t *>(w.counters) + 16;
+    w.n_big = reinterpret_cast<uint32_t *>(w.counters) + 17;
     const uint64_t colrows = p.colmax ? uint64_t(p.bh_rows) + 1 : 1;
     w.colkey = reinterpret_cast<unsigned long long *>(take(8 * colrows));
     w.colcursor = reinterpret_cast<uint32_t *>(take(4 * colrows));
+    w.big_rows = reinterpret_cast<uint32_t *>(take(4 * colrows));
     w.cands = reinterpret_cast<uint4 *>(take(16 * std::max<uint64_t>(p.colmax ? p.cand_cap : 0, 1)));
     w.cand_count = reinterpret_cast<uint32_t *>(w.counters) + 6;
     w.long_segs = reinterpret_cast<DevLongSeg *>(take(sizeof(DevLongSeg) * std::max<uint64_t>(p.n_long_segs, 1)));
@@ -2051,15 +2202,13 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
     PDP_TRY(mark(PDP_KERNEL_ALL, true));
     // status and counters (record total (64 bits), overflow tiles, next join item (count
     // pass), next tile, next join item (write pass), column candidates) in one launch
-    hipLaunchKernelGGL(k_pairs_init, dim3(std::max<uint32_t>(1, std::min<uint32_t>(1024, (p.total_tiles + 255) / 256))),
-                       dim3(256), 0, s, st, reinterpret_cast<uint32_t *>(w.counters), w.tile_tot, w.fill, p.total_tiles);
+    const uint64_t key_rows = p.colmax ? uint64_t(p.bh_rows) + 1 : 0;
+    const uint64_t init = std::max({uint64_t(p.total_tiles), key_rows, uint64_t(p.n_gtiles), uint64_t(1)});
+    hipLaunchKernelGGL(k_pairs_init, dim3(static_cast<uint32_t>(std::min<uint64_t>(4096, (init + 255) / 256))), dim3(256), 0,
+                       s, st, reinterpret_cast<uint32_t *>(w.counters), w.tile_tot, w.fill, p.total_tiles, bh->ptr, w.colkey,
+                       key_rows, w.gdicts, w.gtiles, p.n_gdicts ? p.n_gtiles : 0u, w.gcursor);
     PDP_TRY(hipGetLastError());
     const ColWs cmx{w.colkey, w.cands, w.cand_count, p.colmax ? p.cand_cap : 0};
-    if (p.colmax) {  // BA rows are counted by atomics; column keys and cursors start at zero
-        PDP_TRY(launch_fill_u32(bh->ptr, uint64_t(p.bh_rows) + 1, 0u, s));
-        PDP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(w.colkey), 2 * (uint64_t(p.bh_rows) + 1), 0u, s));
-        PDP_TRY(launch_fill_u32(w.colcursor, uint64_t(p.bh_rows) + 1, 0u, s));
-    }
     if (p.n_gdicts) {  // the group path's join; timed as the join with the pair path's, when a plan has both
         PDP_TRY(mark(PDP_KERNEL_JOIN, true));
         PDP_TRY(launch_group_join(p, w, s));
@@ -2069,6 +2218,7 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
     if (p.total_chunks) {
         const bool pers = p.join_grid != 0;
         const uint32_t *gate = nullptr;
+        const TileRanges rg{w.tiles, p.total_tiles, p.fused ? w.fill : nullptr, w.tile_off, w.tile_rng, w.join_done};
         bool two_pers = pers;
         dim3 g2 = pers ? dim3(std::min(p.join_grid, (p.total_chunks + kClaimJoin - 1) / kClaimJoin)) : dim3(p.total_chunks);
         if (p.fused) {
@@ -2094,20 +2244,19 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         }
         if (two_pers)
             hipLaunchKernelGGL(k_join_persistent<false>, g2, dim3(kJoinThreads), 0, s, w.tasks, p.n_tasks, p.total_chunks,
-                               w.cells, w.tile_tot, w.tile_off, w.counters, w.recs, p.rec_cap, st, w.next_join, gate);
+                               w.cells, w.tile_tot, w.tile_off, w.counters, w.recs, p.rec_cap, st, w.next_join, gate, rg);
         else
             hipLaunchKernelGGL(k_join<false>, g2, dim3(kJoinThreads), 0, s, w.tasks, p.n_tasks, w.cells, w.tile_tot,
-                               w.tile_off, w.counters, w.recs, p.rec_cap, st, gate);
+                               w.tile_off, w.counters, w.recs, p.rec_cap, st, rg);
         PDP_TRY(hipGetLastError());
         PDP_TRY(mark(PDP_KERNEL_BUCKET, true));
-        PDP_TRY(launch_scan(w.tile_tot, w.tile_off, p.total_tiles, w.partials, s));
         PDP_TRY(mark(PDP_KERNEL_BUCKET, false));
         if (two_pers)
             hipLaunchKernelGGL(k_join_persistent<true>, g2, dim3(kJoinThreads), 0, s, w.tasks, p.n_tasks, p.total_chunks,
-                               w.cells, w.tile_tot, w.tile_off, w.counters, w.recs, p.rec_cap, st, w.next_join_write, gate);
+                               w.cells, w.tile_tot, w.tile_off, w.counters, w.recs, p.rec_cap, st, w.next_join_write, gate, rg);
         else
             hipLaunchKernelGGL(k_join<true>, g2, dim3(kJoinThreads), 0, s, w.tasks, p.n_tasks, w.cells, w.tile_tot,
-                               w.tile_off, w.counters, w.recs, p.rec_cap, st, gate);
+                               w.tile_off, w.counters, w.recs, p.rec_cap, st, rg);
         PDP_TRY(hipGetLastError());
         if (!p.fused) {
             PDP_TRY(mark(PDP_KERNEL_JOIN, false));
@@ -2119,13 +2268,6 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         PDP_TRY(mark(PDP_KERNEL_BUCKET, true));
         PDP_TRY(mark(PDP_KERNEL_BUCKET, false));
         PDP_TRY(mark(PDP_KERNEL_JOIN_BACKUP, true));
-        PDP_TRY(launch_fill_u32(w.tile_off, uint64_t(p.total_tiles) + 1, 0u, s));
-    }
-    if (p.total_tiles) {
-        hipLaunchKernelGGL(k_tile_ranges, dim3(std::min<uint32_t>(1024, (p.total_tiles + 255) / 256)), dim3(256), 0, s,
-                           w.tiles, p.total_tiles, w.tile_off, p.fused && p.total_chunks ? w.fill : nullptr, w.fallback,
-                           p.rec_cap, w.tile_rng);
-        PDP_TRY(hipGetLastError());
     }
     PDP_TRY(mark(PDP_KERNEL_JOIN_BACKUP, false));
     PDP_TRY(mark(PDP_KERNEL_TILE_COUNT, true));
@@ -2154,7 +2296,8 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
     PDP_TRY(launch_group_tiles(p, w, bh, s));
     const uint32_t col_grid = std::max<uint32_t>(1, std::min<uint32_t>(2048, static_cast<uint32_t>((p.cand_cap + 255) / 256)));
     if (p.colmax) {
-        hipLaunchKernelGGL(k_colmax_rows, dim3(col_grid), dim3(256), 0, s, cmx, bh->ptr, w.slab, st);
+        hipLaunchKernelGGL(k_colmax_rows, dim3(col_grid), dim3(256), 0, s, cmx, bh->ptr, w.slab, w.colcursor, w.big_rows,
+                           w.n_big, st);
         PDP_TRY(hipGetLastError());
     }
     const dim3 long_grid(std::min(p.long_rows, kLongGrid));
@@ -2168,12 +2311,27 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         PDP_TRY(hipGetLastError());
     }
     PDP_TRY(mark(PDP_KERNEL_TILE_COUNT, false));
-    PDP_TRY(launch_scan(bh->ptr, bh->ptr, p.bh_rows, w.partials, s));
     PDP_TRY(mark(PDP_KERNEL_TILE_WRITE, true));
+    // counts to row pointers: the groups' sums (past kRowGroups groups their scan), then the pointers
+    // and what each group does with them
+    auto scan_partials_of = [&](uint64_t groups) -> hipError_t {
+        return groups > kRowGroups ? launch_scan(w.partials, w.partials, groups, w.partials2, s) : hipSuccess;
+    };
     if (p.bh_rows) {
-        hipLaunchKernelGGL(k_slab_copy, dim3((p.bh_rows + 255) / 256), dim3(256), 0, s, p.bh_rows, bh->ptr, w.slab,
-                           bh->col, bh->num, bh->den, bh->capacity, st);
+        const uint64_t groups = row_groups(p.bh_rows);
+        const dim3 g(static_cast<uint32_t>(groups));
+        auto slab = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, g, dim3(kRowThreads), 0, s, p.bh_rows, bh->ptr, w.partials, w.slab, bh->col, bh->num, bh->den,
+                               bh->capacity, st);
+        };
+        hipLaunchKernelGGL(k_rows_sum, g, dim3(kRowThreads), 0, s, bh->ptr, p.bh_rows, w.partials);
         PDP_TRY(hipGetLastError());
+        PDP_TRY(scan_partials_of(groups));
+        if (groups > kRowGroups) slab(k_rows_slab<false>);
+        else slab(k_rows_slab<true>);
+        PDP_TRY(hipGetLastError());
+    } else {
+        PDP_TRY(launch_fill_u32(bh->ptr, 1, 0u, s));
     }
     if (p.total_tiles) {
         const uint32_t g = p.total_tiles < 256 ? p.total_tiles : 256;
@@ -2191,25 +2349,25 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         PDP_TRY(hipGetLastError());
     }
     if (p.colmax && p.bh_rows) {
-        hipLaunchKernelGGL(k_colmax_big, dim3(col_grid), dim3(256), 0, s, cmx, w.colcursor, bh->ptr, bh->col, bh->num,
-                           bh->den, bh->capacity);
+        hipLaunchKernelGGL(k_colmax_big, dim3(col_grid), dim3(256), 0, s, cmx, w.colcursor, w.n_big, bh->ptr, bh->col,
+                           bh->num, bh->den, bh->capacity);
         PDP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_colmax_sort, dim3((p.bh_rows + 255) / 256), dim3(256), 0, s, p.bh_rows, w.colcursor, bh->ptr,
-                           bh->col, bh->num, bh->den, bh->capacity);
+        hipLaunchKernelGGL(k_colmax_sort, dim3(std::min<uint32_t>(p.bh_rows, 1024)), dim3(kWave), 0, s, w.big_rows, w.n_big,
+                           bh->ptr, bh->col, bh->num, bh->den, bh->capacity);
         PDP_TRY(hipGetLastError());
     }
     PDP_TRY(mark(PDP_KERNEL_TILE_WRITE, false));
     PDP_TRY(mark(PDP_KERNEL_BBH, true));
     if (p.bbh_rows && bbh) {
-        const uint32_t g = (p.bbh_rows + 255) / 256;
-        hipLaunchKernelGGL(k_bbh<false>, dim3(g), dim3(256), 0, s, w.tasks, w.order, p.n_tasks, p.bbh_rows, p.bh_rows,
-                           bh->ptr, bh->col, bh->num, bh->den, bh->capacity, bbh->ptr, bbh->a, bbh->b, bbh->num, bbh->den,
-                           bbh->capacity, st);
+        const BbhArgs A{w.tasks, w.order, p.n_tasks, p.bbh_rows, p.bh_rows, bh->ptr, bh->col, bh->num, bh->den, bh->capacity,
+                        bbh->ptr, bbh->a, bbh->b, bbh->num, bbh->den, bbh->capacity, w.partials, st};
+        const uint64_t groups = row_groups(p.bbh_rows);
+        const dim3 g(static_cast<uint32_t>(groups));
+        hipLaunchKernelGGL(k_bbh_count, g, dim3(kRowThreads), 0, s, A);
         PDP_TRY(hipGetLastError());
-        PDP_TRY(launch_scan(bbh->ptr, bbh->ptr, p.bbh_rows, w.partials, s));
-        hipLaunchKernelGGL(k_bbh<true>, dim3(g), dim3(256), 0, s, w.tasks, w.order, p.n_tasks, p.bbh_rows, p.bh_rows,
-                           bh->ptr, bh->col, bh->num, bh->den, bh->capacity, bbh->ptr, bbh->a, bbh->b, bbh->num, bbh->den,
-                           bbh->capacity, st);
+        PDP_TRY(scan_partials_of(groups));
+        if (groups > kRowGroups) hipLaunchKernelGGL(k_bbh_write<false>, g, dim3(kRowThreads), 0, s, A);
+        else hipLaunchKernelGGL(k_bbh_write<true>, g, dim3(kRowThreads), 0, s, A);
         PDP_TRY(hipGetLastError());
     }
     PDP_TRY(mark(PDP_KERNEL_BBH, false));
