@@ -582,20 +582,22 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             if (dense > kMaxTileLds)
                 return bail(fail(PDP_E_LIMIT, "task %u: %u target genes do not fit an LDS tile", t, C->n_genes));
             tile_lds = std::max<uint32_t>(tile_lds, static_cast<uint32_t>(dense));
-            // a tile's (row, column) sums share one LDS hash table, and a row meets more columns by
-            // chance the more k-mers it has.  Unless the caller fixed the height, a tile has as many
-            // rows as their expected records fit the table (more go in several passes, each reading
-            // all of them), and fewer where the plan has under 512 tiles, down to 4 and up to 128
-            // tiles per direction (two genomes of 200 genes, k = 4: four tiles of 64 rows each way take
-            // 108 us, tiles of 4 rows 12).  Rows of long genes go 32 to a tile at most.
+            // Unless the caller fixed the height: rows of long genes (over 512 letters on average, e.g.
+            // nucleotide genes) go 32 to a tile, and to fill the chip a plan with under 256 tiles takes
+            // lower ones, or under 512 where a tile's records (a row meets columns by chance, `met`) then
+            // fit its hash table in one pass, down to 4 rows and up to 128 tiles per direction (two
+            // genomes of 200 genes, k = 4: four tiles of 64 rows each way take 108 us, tiles of 4 rows
+            // 12).  No lower in larger plans: each batch of the join reserves a run in every tile it
+            // feeds by a device atomic (12 x 3000 genes, k = 5: 0.81 ms with 64 rows, 1.44 with 16).
             if (!prm.tile_rows && R->n_genes) {
-                const AlphaSpec al = alpha_spec(R->alphabet);
                 const double len = double(R->capacity) / R->n_genes;
-                const double met = 8.0 + len * double(C->capacity) * std::pow(double(al.sigma), -double(R->k));
+                const double met = 8.0 + len * double(C->capacity) *
+                                             std::pow(double(alpha_spec(R->alphabet).sigma), -double(R->k));
                 uint32_t &sh = d.tile_shift[dir];
-                if (len > 512) --sh;
-                while (sh > 2 && double(1u << sh) * met > kHashMax) --sh;
-                while (sh > 2 && (all_rows >> sh) < 512 && (R->n_genes >> (sh - 1)) <= 128) --sh;
+                if (R->capacity / R->n_genes > 512) --sh;
+                while (sh > 2 && (R->n_genes >> (sh - 1)) <= 128 &&
+                       ((all_rows >> sh) < 256 || ((all_rows >> sh) < 512 && double(1u << (sh - 1)) * met <= kHashMax)))
+                    --sh;
             }
             rec_est += dir_est * tile_slack(d.tile_shift[dir]) / 4;
             d.tiles_n[dir] = static_cast<uint32_t>((uint64_t(R->n_genes) + (1u << d.tile_shift[dir]) - 1) >>
