@@ -7,10 +7,10 @@
 //    kMvWaveCap keys, eight per lane, lanes exchanging by shuffles) and
 //    run-length encodes them into the gene's multiplicity vector (Multiplicity
 //    vector building phase, Alg. 1: group equal identifiers, count, ascending
-//    order).  Longer genes are queued by size for k_mv_mid (one work-group
+//    order).  Longer genes are queued by size for k_mv_mid and k_mv_rest (one work-group
 //    per gene, 8, 16 or 32 codes per thread sorted in registers, exchanges
-//    across waves through LDS) and, past kMvSortCap windows, for k_mv_long
-//    (codes sorted in global memory).
+//    across waves through LDS; past kMvSortCap windows codes sorted in
+//    global memory).
 // 2. A scan of the distinct-k-mer counts of all genes gives the CSR offsets,
 //    and k_mv_compact packs the vectors (and notes each entry's gene).
 // 3. The inverted index (all entries ordered by k-mer code, ties by gene) is a
@@ -38,6 +38,7 @@ constexpr uint32_t kMvThreads = 256;
 static_assert(kMvSortCap == kMvThreads * 32, "the largest k_mv_mid class sorts 32 codes per thread");
 constexpr uint32_t kIxBatch = 8;  // index entries a thread loads per round in the histogram and placement
 constexpr uint32_t kDescPerLaunch = 16;
+constexpr uint32_t kBuildCounters = 8;  // [0..3] genes queued per size class, [4] ended histogram blocks
 
 struct DescChunk {
     uint32_t first, count;
@@ -45,11 +46,25 @@ struct DescChunk {
 };
 static_assert(sizeof(DescChunk) <= 4096, "descriptor chunks travel as kernel arguments");
 
-// Copies descriptors passed by value into the workspace table (kernel
-// arguments are captured at launch, so the host copy may go away at once).
-__global__ void k_put_desc(DevBuild *table, DescChunk c) {
-    const uint32_t i = threadIdx.x;
-    if (i < c.count) table[c.first + i] = c.d[i];
+// Set-up of a build: descriptors passed by value into the workspace table (kernel arguments are
+// captured at launch, so the host copy may go away at once), their genomes' statuses cleared and
+// the CSR of a genome without genes written (nothing else writes it).  The first chunk's launch also
+// zeroes the build's counters and the bin totals (total_bins of them).
+__global__ __launch_bounds__(256) void k_build_init(DevBuild *table, DescChunk c, uint32_t *counters, uint32_t *bintot,
+                                                    uint32_t total_bins) {
+    const uint32_t i0 = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+    if (i0 < c.count) {
+        const DevBuild &d = c.d[i0];
+        table[c.first + i0] = d;
+        d.status->code = 0;
+        d.status->flags = 0;
+        d.status->needed = 0;
+        d.status->where = ~0ull;
+        if (d.n_genes == 0) d.mv_ptr[0] = 0;
+    }
+    if (c.first) return;
+    if (i0 < kBuildCounters) counters[i0] = 0;
+    for (uint32_t b = i0; b < total_bins; b += stride) bintot[b] = 0;
 }
 
 __device__ __forceinline__ uint32_t find_genome_by_gene(const DevBuild *t, uint32_t n, uint32_t gene) {
@@ -63,24 +78,6 @@ __device__ __forceinline__ uint32_t find_genome_by_gene(const DevBuild *t, uint3
     return lo;
 }
 
-
-// Set-up of a build in one launch: every genome's status cleared and the CSR of a genome
-// without genes written (nothing else writes it), the build's counters and the bin totals
-// zeroed.
-__global__ void k_build_init(const DevBuild *table, uint32_t n, uint32_t *counters, uint32_t *bintot,
-                             uint32_t total_bins) {
-    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-    for (uint32_t t = i0; t < n; t += stride) {
-        pdp_status *st = table[t].status;
-        st->code = 0;
-        st->flags = 0;
-        st->needed = 0;
-        st->where = ~0ull;
-        if (table[t].n_genes == 0) table[t].mv_ptr[0] = 0;
-    }
-    if (i0 < 4) counters[i0] = 0;
-    for (uint32_t b = i0; b < total_bins; b += stride) bintot[b] = 0;
-}
 
 // Orders LDS writes of a wave before its later LDS reads (a wave runs in lock step,
 // so no work-group barrier is needed).
@@ -356,7 +353,7 @@ __device__ __forceinline__ void mv_wave_gene(const DevBuild &B, uint8_t *sym, ui
 }
 
 // Longer genes go to lists by size: counters[0] / long_list past kMvSortCap windows,
-// counters[c] / mid_list + (c - 1) * stride for k_mv_mid<8 << (c - 1)>, c = 1, 2, 3.
+// counters[c] / mid_list + (c - 1) * stride for genes sorted 8 << (c - 1) codes a thread, c = 1, 2, 3.
 // NARROW: every genome of the build sorts 32-bit keys (5-bit codes of at most 32 bits, or
 // base-20 values): a separate instance without the 64-bit path, which needs fewer registers.
 template <bool NARROW>
@@ -479,7 +476,7 @@ __device__ __forceinline__ void block_bitonic_sort(K (&key)[E], K *xch) {
 // windows (one new letter per window), the work-group sorts the codes in registers, and
 // run heads ranked by a work-group scan give the multiplicity vector.  The symbols, the
 // sort's exchange area and the head positions share one LDS array.
-// One gene of k_mv_mid: len letters at offset o, nw <= kMvThreads * E windows; K as in the wave kernel.
+// One queued gene: len letters at offset o, nw <= kMvThreads * E windows; K as in the wave kernel.
 template <uint32_t E, typename K, bool B20, bool NARROW>
 __device__ __forceinline__ void mid_gene(const DevBuild &B, uint32_t G, uint64_t o, uint32_t len, uint32_t nw,
                                          uint64_t *xch64, K *s_last, uint32_t *tmp, uint32_t *__restrict__ dcnt) {
@@ -574,86 +571,105 @@ __device__ __forceinline__ void mid_gene(const DevBuild &B, uint32_t G, uint64_t
     __syncthreads();  // LDS takes the next gene
 }
 
+// One queued gene of at most kMvThreads * E windows.  xch: mid_words<E, NARROW> words.
 template <uint32_t E, bool NARROW>
-__global__ __launch_bounds__(kMvThreads) void k_mv_mid(const DevBuild *__restrict__ table, uint32_t *__restrict__ dcnt,
-                                                       const uint64_t *__restrict__ list,
-                                                       const uint32_t *__restrict__ count) {
+constexpr uint32_t mid_words = NARROW ? kMvThreads * E * 3 / 4 + 1 : kMvThreads * E;  // NARROW: N keys, N + 1 head positions
+template <uint32_t E, bool NARROW>
+__device__ __forceinline__ void mid_item(const DevBuild *__restrict__ table, uint64_t item, uint64_t *xch, uint64_t *s_last,
+                                         uint32_t *tmp, uint32_t *__restrict__ dcnt) {
     constexpr uint32_t N = kMvThreads * E;
     static_assert(N + kKMaxAll <= 6 * N && N + 1 <= 4 * N && N <= 65535, "symbols and u16 head positions fit");
-    __shared__ uint64_t xch[NARROW ? N * 3 / 4 + 1 : N];  // NARROW: N keys and N + 1 head positions
+    const DevBuild &B = table[item >> 32];
+    const uint32_t g = static_cast<uint32_t>(item);
+    const uint64_t o = B.off[g];
+    const uint32_t len = static_cast<uint32_t>(B.off[g + 1] - o);
+    const uint32_t nw = len - B.k + 1;  // k_mv_wave queued this gene for nw <= kMvThreads * E
+    if (B.bits * B.k <= 32) {  // uniform per work-group
+        mid_gene<E, uint32_t, false, NARROW>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp, dcnt);
+    } else if (base20_keys(B)) {
+        mid_gene<E, uint32_t, true, NARROW>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp,
+                                    dcnt);
+    } else {
+        if constexpr (!NARROW) mid_gene<E, uint64_t, false, false>(B, B.gene_base + g, o, len, nw, xch, s_last, tmp, dcnt);
+    }
+}
+
+// The genes of up to 2048 windows (many, in a build of nucleotide genes).
+template <bool NARROW>
+__global__ __launch_bounds__(kMvThreads) void k_mv_mid(const DevBuild *__restrict__ table, uint32_t *__restrict__ dcnt,
+                                                       const uint64_t *__restrict__ list,
+                                                       const uint32_t *__restrict__ counters) {
+    __shared__ uint64_t xch[mid_words<8, NARROW>];
     __shared__ uint64_t s_last[kMvWaves];
     __shared__ uint32_t tmp[kMvWaves + 1];
-    const uint32_t n_items = *count;
-    for (uint32_t li = blockIdx.x; li < n_items; li += gridDim.x) {
-        const uint64_t item = list[li];
-        const DevBuild &B = table[item >> 32];
-        const uint32_t g = static_cast<uint32_t>(item);
-        const uint64_t o = B.off[g];
-        const uint32_t len = static_cast<uint32_t>(B.off[g + 1] - o);
-        const uint32_t nw = len - B.k + 1;  // k_mv_wave queued this gene for nw <= kMvThreads * E
-        if (B.bits * B.k <= 32) {  // uniform per work-group
-            mid_gene<E, uint32_t, false, NARROW>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp, dcnt);
-        } else if (base20_keys(B)) {
-            mid_gene<E, uint32_t, true, NARROW>(B, B.gene_base + g, o, len, nw, xch, reinterpret_cast<uint32_t *>(s_last), tmp,
-                                        dcnt);
-        } else {
-            if constexpr (!NARROW) mid_gene<E, uint64_t, false, false>(B, B.gene_base + g, o, len, nw, xch, s_last, tmp, dcnt);
-        }
-    }
+    const uint32_t n_items = counters[1];
+    for (uint32_t li = blockIdx.x; li < n_items; li += gridDim.x) mid_item<8, NARROW>(table, list[li], xch, s_last, tmp, dcnt);
 }
 
 // Genes with more windows than fit in LDS: same steps, codes sorted in global memory.
 template <bool NARROW>
-__global__ __launch_bounds__(kMvThreads) void k_mv_long(const DevBuild *__restrict__ table, uint32_t *__restrict__ dcnt,
+__device__ __forceinline__ void long_item(const DevBuild *__restrict__ table, uint64_t item, uint32_t *tmp,
+                                          uint32_t *__restrict__ dcnt) {
+    const uint32_t tid = threadIdx.x;
+    const DevBuild &B = table[item >> 32];
+    const uint32_t g = static_cast<uint32_t>(item);
+    const uint32_t k = B.k;
+    const uint64_t o = B.off[g];
+    const uint32_t nw = static_cast<uint32_t>(B.off[g + 1] - o - k + 1);
+    uint64_t *w = B.long_tmp + o;
+    for (uint64_t p = tid; p < nw + k - 1; p += kMvThreads)
+        if (sym_in(B.res[o + p], B.bits) == kInvalidSym) raise_status(B.status, PDP_E_ALPHABET, 0, o + p);
+    for (uint32_t p = tid; p < nw; p += kMvThreads) {
+        uint64_t c = 0;
+        for (uint32_t j = 0; j < k; ++j) {
+            uint32_t s = sym_in(B.res[o + p + j], B.bits);
+            c = (c << B.bits) | (s == kInvalidSym ? 0u : s);
+        }
+        w[p] = c;
+    }
+    __syncthreads();
+    wg_network_sort(nw, [&](uint32_t lo, uint32_t hi) {
+        const uint64_t a = w[lo], b = w[hi];
+        if (b < a) {
+            w[lo] = b;
+            w[hi] = a;
+        }
+    });
+    uint32_t base = 0;
+    for (uint32_t c0 = 0; c0 < nw; c0 += kMvThreads) {
+        const uint32_t i = c0 + tid;
+        const bool head = i < nw && (i == 0 || w[i] != w[i - 1]);
+        uint32_t total;
+        const uint32_t r = block_exclusive_scan<kMvThreads>(head ? 1u : 0u, tmp, &total);
+        if (head) {
+            const uint64_t c = w[i];
+            uint32_t end = i + 1;
+            while (end < nw && w[end] == c) ++end;
+            if constexpr (NARROW) reinterpret_cast<uint32_t *>(B.slot_code)[o + base + r] = code_to_key(B, c);
+            else B.slot_code[o + base + r] = c;
+            B.slot_cnt[o + base + r] = end - i;
+        }
+        base += total;
+    }
+    if (tid == 0) dcnt[B.gene_base + g] = base;
+    __syncthreads();
+}
+
+// The longer genes of all classes in one launch, the longest first (a launch per class cost small
+// builds 4.5 us each, and the classes of one nucleotide genome, 27 and 45 us, ran one after another).
+template <bool NARROW>
+__global__ __launch_bounds__(kMvThreads) void k_mv_rest(const DevBuild *__restrict__ table, uint32_t *__restrict__ dcnt,
+                                                        const uint64_t *__restrict__ mid_list, uint32_t stride,
                                                         const uint64_t *__restrict__ long_list,
                                                         const uint32_t *__restrict__ counters) {
-    __shared__ uint32_t tmp[kMvThreads / kWave + 1];
-    const uint32_t n_long = counters[0];
-    const uint32_t tid = threadIdx.x;
-    for (uint32_t li = blockIdx.x; li < n_long; li += gridDim.x) {
-        const uint64_t item = long_list[li];
-        const DevBuild &B = table[item >> 32];
-        const uint32_t g = static_cast<uint32_t>(item);
-        const uint32_t k = B.k;
-        const uint64_t o = B.off[g];
-        const uint32_t nw = static_cast<uint32_t>(B.off[g + 1] - o - k + 1);
-        uint64_t *w = B.long_tmp + o;
-        for (uint64_t p = tid; p < nw + k - 1; p += kMvThreads)
-            if (sym_in(B.res[o + p], B.bits) == kInvalidSym) raise_status(B.status, PDP_E_ALPHABET, 0, o + p);
-        for (uint32_t p = tid; p < nw; p += kMvThreads) {
-            uint64_t c = 0;
-            for (uint32_t j = 0; j < k; ++j) {
-                uint32_t s = sym_in(B.res[o + p + j], B.bits);
-                c = (c << B.bits) | (s == kInvalidSym ? 0u : s);
-            }
-            w[p] = c;
-        }
-        __syncthreads();
-        wg_network_sort(nw, [&](uint32_t lo, uint32_t hi) {
-            const uint64_t a = w[lo], b = w[hi];
-            if (b < a) {
-                w[lo] = b;
-                w[hi] = a;
-            }
-        });
-        uint32_t base = 0;
-        for (uint32_t c0 = 0; c0 < nw; c0 += kMvThreads) {
-            const uint32_t i = c0 + tid;
-            const bool head = i < nw && (i == 0 || w[i] != w[i - 1]);
-            uint32_t total;
-            const uint32_t r = block_exclusive_scan<kMvThreads>(head ? 1u : 0u, tmp, &total);
-            if (head) {
-                const uint64_t c = w[i];
-                uint32_t end = i + 1;
-                while (end < nw && w[end] == c) ++end;
-                if constexpr (NARROW) reinterpret_cast<uint32_t *>(B.slot_code)[o + base + r] = code_to_key(B, c);
-                else B.slot_code[o + base + r] = c;
-                B.slot_cnt[o + base + r] = end - i;
-            }
-            base += total;
-        }
-        if (tid == 0) dcnt[B.gene_base + g] = base;
-        __syncthreads();
+    __shared__ uint64_t xch[mid_words<32, NARROW>];
+    __shared__ uint64_t s_last[kMvWaves];
+    __shared__ uint32_t tmp[kMvWaves + 1];
+    const uint32_t n_long = counters[0], n32 = counters[3], n16 = counters[2];
+    for (uint32_t li = blockIdx.x; li < n_long + n32 + n16; li += gridDim.x) {  // uniform per work-group
+        if (li < n_long) long_item<NARROW>(table, long_list[li], tmp, dcnt);
+        else if (li < n_long + n32) mid_item<32, NARROW>(table, mid_list[2 * stride + li - n_long], xch, s_last, tmp, dcnt);
+        else mid_item<16, NARROW>(table, mid_list[stride + li - n_long - n32], xch, s_last, tmp, dcnt);
     }
 }
 
@@ -745,9 +761,11 @@ __device__ __forceinline__ uint32_t entry_bucket(const DevBuild &B, uint64_t c) 
 template <bool REC>
 __global__ __launch_bounds__(256) void k_ix_hist(const DevBuild *__restrict__ table, uint32_t n_genomes,
                                                  const uint32_t *__restrict__ gptr, const uint2 *__restrict__ ent_rec,
-                                                 uint32_t *__restrict__ bintot) {
+                                                 uint32_t *__restrict__ bintot, uint32_t total_bins,
+                                                 uint32_t *__restrict__ binoff, uint32_t *__restrict__ done) {
     extern __shared__ uint32_t h[];
-    __shared__ uint32_t s_t;
+    __shared__ uint32_t s_t, s_last;
+    __shared__ uint32_t s_tmp[256 / kWave + 1];
     if (threadIdx.x == 0) s_t = find_genome_by_block(table, n_genomes, blockIdx.x);
     __syncthreads();
     const DevBuild &B = table[s_t];
@@ -772,6 +790,35 @@ __global__ __launch_bounds__(256) void k_ix_hist(const DevBuild *__restrict__ ta
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < B.nh; i += blockDim.x)
         if (h[i]) atomicAdd(&bintot[B.bin_base + i], h[i]);
+    if (!binoff) return;
+    // few bins: the block that ends last scans the totals into every bin's range
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        s_last = atomicAdd(done, 1u) + 1u == gridDim.x ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    uint32_t carry = 0;
+    for (uint32_t b0 = 0; b0 < total_bins; b0 += 256 * 8) {
+        uint32_t v[8], sum = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) {
+            const uint32_t i = b0 + threadIdx.x * 8 + q;
+            v[q] = i < total_bins ? __hip_atomic_load(&bintot[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            sum += v[q];
+        }
+        uint32_t all;
+        uint32_t run = carry + block_exclusive_scan<256>(sum, s_tmp, &all);
+        carry += all;
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) {
+            const uint32_t i = b0 + threadIdx.x * 8 + q;
+            if (i < total_bins) binoff[i] = run;
+            run += v[q];
+        }
+    }
+    if (threadIdx.x == 0) binoff[total_bins] = carry;
 }
 
 __device__ __forceinline__ uint64_t rec_code(const uint4 &r) { return (static_cast<uint64_t>(r.y) << 32) | r.x; }
@@ -1156,7 +1203,7 @@ uint64_t build_ws_bytes(const BuildShape &s) {
     b += align_up(4 * (s.total_bins + 1), A);           // scanned bin offsets
     b += align_up(8 * (s.total_genes + 1), A);          // long_list
     b += align_up(3 * 8 * (s.total_genes + 1), A);      // mid_list: three size classes
-    b += align_up(4 * 4, A);                            // counters
+    b += align_up(4 * kBuildCounters, A);               // counters
     const uint64_t np = std::max<uint64_t>(scan_partials(s.total_genes), scan_partials(s.total_bins));
     b += align_up(4 * np, A);
     return b;
@@ -1197,7 +1244,7 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
     uint64_t *long_list = reinterpret_cast<uint64_t *>(take(8 * (sh.total_genes + 1)));
     uint64_t *mid_list = reinterpret_cast<uint64_t *>(take(3 * 8 * (sh.total_genes + 1)));
     const uint32_t stride = static_cast<uint32_t>(sh.total_genes + 1);
-    uint32_t *counters = reinterpret_cast<uint32_t *>(take(4 * 4));
+    uint32_t *counters = reinterpret_cast<uint32_t *>(take(4 * kBuildCounters));
     const uint64_t np = std::max<uint64_t>(scan_partials(sh.total_genes), scan_partials(sh.total_bins));
     uint32_t *partials = reinterpret_cast<uint32_t *>(take(4 * np));
 
@@ -1219,6 +1266,11 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
     uint32_t max_nh = 0;
 
     // descriptors, passed by value to a tiny kernel in chunks
+    uint32_t total_bins = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint32_t sh_i = bin_plan(d[i]->n_buckets, g[i].n_residues + 1, d[i]->k, d[i]->alphabet, target, slots).s;
+        total_bins += static_cast<uint32_t>((uint64_t(d[i]->n_buckets) + (1ull << sh_i) - 1) >> sh_i);
+    }
     uint64_t gene_base = 0, res_base = 0, blk_base = 0, bin_base = 0;
     for (uint32_t c0 = 0; c0 < n; c0 += kDescPerLaunch) {
         DescChunk ch{};
@@ -1268,17 +1320,14 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
             blk_base += B.nblk;
             bin_base += B.nh;
         }
-        hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(kDescPerLaunch), 0, s, table, ch);
+        const uint32_t init_grid = c0 ? 1u : std::min<uint32_t>(total_bins / 256 + 1, 1024);
+        hipLaunchKernelGGL(k_build_init, dim3(init_grid), dim3(256), 0, s, table, ch, counters, bintot, total_bins);
         PDP_TRY(hipGetLastError());
     }
     const uint32_t tg = static_cast<uint32_t>(sh.total_genes);
     uint2 *ent_rec = reinterpret_cast<uint2 *>(long_tmp);  // free once the multiplicity vectors are in their slots
-    const uint32_t total_bins = static_cast<uint32_t>(bin_base), total_blocks = static_cast<uint32_t>(blk_base);
+    const uint32_t total_blocks = static_cast<uint32_t>(blk_base);
     const uint32_t hist_lds = 4 * max_nh;
-    const uint64_t init_items = std::max<uint64_t>(std::max<uint64_t>(n, total_bins), 4);
-    hipLaunchKernelGGL(k_build_init, dim3(static_cast<uint32_t>(std::min<uint64_t>((init_items + 255) / 256, 1024))),
-                       dim3(256), 0, s, table, n, counters, bintot, total_bins);
-    PDP_TRY(hipGetLastError());
     if (tg > 0) {
         if (narrow)
             hipLaunchKernelGGL(k_mv_wave<true>, dim3((tg + kMvWaves - 1) / kMvWaves), dim3(kMvThreads), 0, s, table, n,
@@ -1287,34 +1336,19 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
             hipLaunchKernelGGL(k_mv_wave<false>, dim3((tg + kMvWaves - 1) / kMvWaves), dim3(kMvThreads), 0, s, table, n,
                                tg, dcnt, mid_list, long_list, stride, counters);
         PDP_TRY(hipGetLastError());
-        // a fixed grid per size class; work-groups past the class's gene count exit at once; the
-        // larger classes hold fewer genes and fewer work-groups fit a CU: smaller grids
-        const uint32_t mid_groups = tg < 2048 ? tg : 2048;
+        // fixed grids; work-groups past the queued genes exit at once
+        const dim3 mid_groups(std::min(tg, 2048u)), rest_groups(std::min(tg, 768u));
         if (narrow) {
-            hipLaunchKernelGGL((k_mv_mid<8, true>), dim3(mid_groups), dim3(kMvThreads), 0, s, table, dcnt, mid_list,
-                               counters + 1);
+            hipLaunchKernelGGL(k_mv_mid<true>, mid_groups, dim3(kMvThreads), 0, s, table, dcnt, mid_list, counters);
             PDP_TRY(hipGetLastError());
-            hipLaunchKernelGGL((k_mv_mid<16, true>), dim3(std::min(mid_groups, 1024u)), dim3(kMvThreads), 0, s, table,
-                               dcnt, mid_list + stride, counters + 2);
-            PDP_TRY(hipGetLastError());
-            hipLaunchKernelGGL((k_mv_mid<32, true>), dim3(std::min(mid_groups, 512u)), dim3(kMvThreads), 0, s, table,
-                               dcnt, mid_list + 2 * stride, counters + 3);
+            hipLaunchKernelGGL(k_mv_rest<true>, rest_groups, dim3(kMvThreads), 0, s, table, dcnt, mid_list, stride,
+                               long_list, counters);
         } else {
-            hipLaunchKernelGGL((k_mv_mid<8, false>), dim3(mid_groups), dim3(kMvThreads), 0, s, table, dcnt, mid_list,
-                               counters + 1);
+            hipLaunchKernelGGL(k_mv_mid<false>, mid_groups, dim3(kMvThreads), 0, s, table, dcnt, mid_list, counters);
             PDP_TRY(hipGetLastError());
-            hipLaunchKernelGGL((k_mv_mid<16, false>), dim3(std::min(mid_groups, 1024u)), dim3(kMvThreads), 0, s, table,
-                               dcnt, mid_list + stride, counters + 2);
-            PDP_TRY(hipGetLastError());
-            hipLaunchKernelGGL((k_mv_mid<32, false>), dim3(std::min(mid_groups, 512u)), dim3(kMvThreads), 0, s, table,
-                               dcnt, mid_list + 2 * stride, counters + 3);
+            hipLaunchKernelGGL(k_mv_rest<false>, rest_groups, dim3(kMvThreads), 0, s, table, dcnt, mid_list, stride,
+                               long_list, counters);
         }
-        PDP_TRY(hipGetLastError());
-        const uint32_t long_groups = tg < 64 ? tg : 64;
-        if (narrow)
-            hipLaunchKernelGGL(k_mv_long<true>, dim3(long_groups), dim3(kMvThreads), 0, s, table, dcnt, long_list, counters);
-        else
-            hipLaunchKernelGGL(k_mv_long<false>, dim3(long_groups), dim3(kMvThreads), 0, s, table, dcnt, long_list, counters);
         PDP_TRY(hipGetLastError());
     }
     PDP_TRY(launch_scan(dcnt, dcnt, tg, partials, s));  // in place: dcnt becomes the global offsets
@@ -1327,14 +1361,15 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
             hipLaunchKernelGGL((k_mv_compact<false, false>), dim3(tg), dim3(kWave), 0, s, table, n, dcnt, ent_gene, ent_rec);
         PDP_TRY(hipGetLastError());
     }
+    const bool few_bins = total_bins <= 8192;  // their scan by one work-group costs less than a launch
     if (narrow_rec)
         hipLaunchKernelGGL(k_ix_hist<true>, dim3(total_blocks), dim3(256), hist_lds, s, table, n,
-                           dcnt, ent_rec, bintot);
+                           dcnt, ent_rec, bintot, total_bins, few_bins ? binoff : nullptr, counters + 4);
     else
         hipLaunchKernelGGL(k_ix_hist<false>, dim3(total_blocks), dim3(256), hist_lds, s, table, n,
-                           dcnt, ent_rec, bintot);
+                           dcnt, ent_rec, bintot, total_bins, few_bins ? binoff : nullptr, counters + 4);
     PDP_TRY(hipGetLastError());
-    PDP_TRY(launch_scan(bintot, binoff, total_bins, partials, s));  // every bin's range
+    if (!few_bins) PDP_TRY(launch_scan(bintot, binoff, total_bins, partials, s));  // every bin's range
     auto place = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kIxPlaceThreads), hist_lds, s, table, n, dcnt, binoff, bintot,
                            ent_gene, ent_rec);
