@@ -293,13 +293,13 @@ static uint64_t bucket_code(const pdp_dict *d, uint64_t b) {
 // The group path's share of a plan: which tasks take it, and their tables (in_group[t] is set).  A
 // group is a connected component of the task graph, with at least a quarter of its pairs compared,
 // whose pair-by-pair join would search its entries kGroupGain times as often as the group path
-// reads them (all pairs of D genomes: (D - 1) / 2 times), and whose genes meet at most kGroupChance
-// genes of a target genome by chance.  Launch times without the builds, pair path against group
-// path: 5 x 3000 genes, k = 6: 144 / 167 us; 8 x 3000: 236 / 230; 12 x 3000: 445 / 405; chance
-// matches instead of family ones fill the tiles' tables: 12 x 1000 genes, k = 5 (36 by chance)
-// 336 / 428 us, k = 6 (2) 196 / 177.
+// reads them (all pairs of D genomes: (D - 1) / 2 times), and whose k-mers meet at most kGroupChance
+// k-mers of a target genome by chance.  Launch times without the builds, pair path against group
+// path: 5 x 3000 genes, k = 6: 144 / 167 us; 8 x 3000: 236 / 230; 12 x 3000: 445 / 405; every
+// chance match costs a descriptor, whatever the pair path spends on it: 12 x 1000 genes, k = 5 (0.1 by
+// chance) 329 / 375 us, k = 6 (0.005) 170 / 155; 10 x 3000 nucleotide genes, k = 13 (0.045) 811 / 750.
 constexpr uint64_t kGroupGainNum = 7, kGroupGainDen = 2;
-constexpr double kGroupChance = 12.0;  // expected chance matches per gene and target genome, at most
+constexpr double kGroupChance = 0.05;  // expected chance matches per k-mer and target genome, at most
 static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks, const std::vector<uint8_t> &is_long,
                             std::vector<uint8_t> &in_group) {
     std::vector<const pdp_dict *> dicts;
@@ -367,9 +367,9 @@ static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks
         if (searched * kGroupGainDen < cap * kGroupGainNum || ctasks[c].size() * 8 < uint64_t(D) * (D - 1)) continue;
         const pdp_dict *d0 = dicts[M[0]];
         const AlphaSpec al = alpha_spec(d0->alphabet);
-        const double chance = std::pow(double(al.sigma), -double(d0->k)) * (double(cap) / D) *
-                              (double(cap) / double(std::max<uint64_t>(genes, 1)));
-        if (chance > kGroupChance || entries + cap >= UINT32_MAX) continue;
+        const double per_kmer = std::pow(double(al.sigma), -double(d0->k)) * (double(cap) / D);
+        const double chance = per_kmer * (double(cap) / double(std::max<uint64_t>(genes, 1)));  // per gene
+        if (per_kmer > kGroupChance || entries + cap >= UINT32_MAX) continue;
         // directed edges: both directions as one edge whose columns give the other's best hits
         std::vector<uint8_t> map(uint64_t(D) * D, 255);
         std::vector<std::vector<DevGroupTgt>> out(D);
