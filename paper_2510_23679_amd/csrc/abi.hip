@@ -295,10 +295,11 @@ static uint64_t bucket_code(const pdp_dict *d, uint64_t b) {
 // whose pair-by-pair join would search its entries kGroupGain times as often as the group path
 // reads them (all pairs of D genomes: (D - 1) / 2 times), and whose k-mers meet at most kGroupChance
 // k-mers of a target genome by chance.  Launch times without the builds, pair path against group
-// path: 5 x 3000 genes, k = 6: 144 / 167 us; 8 x 3000: 236 / 230; 12 x 3000: 445 / 405; every
+// path: 6 x 3000 genes (2.5), k = 6: 137 / 150 us; 8 x 3000 (3.5): 211 / 206; 12 x 3000: 415 / 362; nine
+// genomes of 577 to 4377 genes (2.7), filters and families: 345 / 262; every
 // chance match costs a descriptor, whatever the pair path spends on it: 12 x 1000 genes, k = 5 (0.1 by
 // chance) 329 / 375 us, k = 6 (0.005) 170 / 155; 10 x 3000 nucleotide genes, k = 13 (0.045) 811 / 750.
-constexpr uint64_t kGroupGainNum = 7, kGroupGainDen = 2;
+constexpr uint64_t kGroupGainNum = 13, kGroupGainDen = 5;
 constexpr double kGroupChance = 0.05;  // expected chance matches per k-mer and target genome, at most
 static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks, const std::vector<uint8_t> &is_long,
                             std::vector<uint8_t> &in_group) {
