@@ -114,8 +114,14 @@ def source_hash() -> str:
 # ------------------------------------------------------------------ algorithmic bytes
 
 def input_bytes(pairs, entries) -> float:
-    """Per unordered genome pair (A, B), each genome's k-mer entries read once: a u64 code and a
-    u32 multiplicity, 12 bytes per entry (the join's share of the path)."""
+    """Each compared genome's k-mer entries read once per launch, a u64 code and a u32 multiplicity,
+    12 bytes per entry (the join's share of the path): what no method can do without.  The group
+    path reads each index once for all its pairs, so bytes counted per pair would exceed it."""
+    return float(sum(12 * entries[i] for i in {g for p in pairs for g in p}))
+
+
+def per_pair_input_bytes(pairs, entries) -> float:
+    """The same 12 bytes per entry, of both genomes of every pair: the method's per-pair model."""
     return float(sum(12 * (entries[i] + entries[j]) for i, j in pairs))
 
 
@@ -271,9 +277,9 @@ def calibrate_copy(mib: int = 1024) -> None:
 
 
 # kernel groups of the traffic table: the group's kernels by name prefix
-TRAFFIC_GROUPS = {"join": ("pdp::k_join_fused",),
-                  "tile_count": ("void pdp::k_tile_count",),
-                  "join_backup": ("void pdp::k_join_persistent", "void pdp::k_join<", "pdp::k_tile_ranges"),
+TRAFFIC_GROUPS = {"join": ("pdp::k_join_fused", "void pdp::k_group_join"),
+                  "tile_count": ("void pdp::k_tile_count", "void pdp::k_group_tile"),
+                  "join_backup": ("void pdp::k_join_persistent", "void pdp::k_join<"),
                   "dictionary_build": ("pdp::k_mv", "void pdp::k_mv", "pdp::k_ix", "void pdp::k_ix")}
 
 
@@ -802,7 +808,9 @@ def main():
     roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": kfrac,
                 "traffic": traffic, "kernel": args.kernel, "kernel_ms": round(avg_kernel_ms, 5),
                 "algorithmic_bytes": alg,
-                "bytes_scope": "join: 12 bytes per k-mer entry of both genomes of every pair (the input term)",
+                "bytes_scope": "join: 12 bytes per k-mer entry of every genome, each read once (the input term); "
+                               "per_pair_bytes counts both genomes of every pair",
+                "per_pair_bytes": per_pair_input_bytes(pairs, entries),
                 "launches_timed": kern_n, "join_layout": "two passes" if two_pass else "one pass",
                 "measured": measured,
                 "path": {"achieved": path_gbs, "frac": path_frac, "ms": round(path_ms, 4),

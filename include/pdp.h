@@ -238,7 +238,8 @@ typedef struct pdp_params {
     uint64_t inc_capacity;   /* shared-k-mer records the scratch can hold, below 2^32: one per shared
                                 (k-mer, gene a, gene b) and requested direction (0: from the dictionary sizes) */
     uint32_t tile_rows;      /* query genes per accumulation tile, 1..256, rounded down to a power of two
-                                (0: 64; raised when a task would have more than 1024 tiles).  Tasks of a
+                                (0: 64, for long genes 32, lower where the plan would leave the GPU partly
+                                idle; raised when a task would have more than 1024 tiles).  Tasks of a
                                 group (see pdp_plan_create) choose their own tiles and items */
     uint32_t join_entries;   /* index entries of the larger genome per join sub-range (1..1024) */
     uint32_t lds_budget;     /* LDS bytes of a tile work-group, at most 156 KiB (0 and anything below
@@ -355,7 +356,7 @@ int32_t pdp_plan_launch(const pdp_plan *plan, pdp_bh_out *bh, pdp_bbh_out *bbh, 
 #define PDP_KERNEL_BUCKET 1      /* between the count and the write pass of the two-pass join (the scan of the
                                     per-tile record totals ends the count pass: nothing in between) */
 #define PDP_KERNEL_TILE_COUNT 2  /* per tile: sort and sum of records, row maxima, tie counts */
-#define PDP_KERNEL_TILE_WRITE 3  /* best-hit output (slab copy, rows with many ties) */
+#define PDP_KERNEL_TILE_WRITE 3  /* best-hit output (rows from their slabs, rows with many ties) */
 #define PDP_KERNEL_BBH 4         /* BBH count and write passes together */
 #define PDP_KERNEL_ALL 5         /* the whole launch */
 #define PDP_KERNEL_JOIN_BACKUP 6 /* the two-pass join gated behind the one-pass join (empty unless a

@@ -274,10 +274,19 @@ static DevDict dev_dict(const pdp_dict *d) {
 // an eighth of the entries per direction covers the family workloads with room; more needs a
 // capacity retry.
 static uint64_t direction_estimate(const pdp_task &t) { return (t.a->capacity + t.b->capacity) / 8 + 4096; }
-// Room of a tile's record region over its rows' share of the estimate, in quarters: the fewer rows, the
-// further their lengths and their share lie from the average (a region that overflows costs the
-// two-pass join: two genomes of 1001 genes, tiles of 4 rows, 37 us of 90).
-static uint64_t tile_slack(uint32_t shift) { return shift >= 6 ? 4u : 4u + 3u * (6u - shift); }
+// Default tile height of a direction with rows of R: rows of long genes (over 512 letters on average,
+// e.g. nucleotide genes) go 32 to a tile.
+static uint32_t default_shift(const pdp_dict *R) {
+    return R->n_genes && R->capacity / R->n_genes > 512 ? kDefaultTileShift - 1 : kDefaultTileShift;
+}
+// Records expected of a direction whose tiles are `lower` halvings below their default height, with room:
+// the fewer rows, the further their lengths and their share lie from the average (a region that overflows
+// costs the two-pass join: two genomes of 1001 genes, tiles of 4 rows, 37 us of 90).
+static uint64_t with_slack(uint64_t dir_est, uint32_t lower) { return dir_est * (4 + 3 * uint64_t(lower)) / 4; }
+// Records of a direction, slack included, up to which its tiles may go lower by default: 16 MiB of
+// them, so that with its other tables (under 512 tiles) no plan of one direction comes near the 64 MiB
+// of pdp_bh_noalloc by it.  Two genomes of 5000 genes expect 0.4 million.
+constexpr uint64_t kLowTileRecords = 1u << 21;
 
 // Code of the first k-mer of bucket b.
 static uint64_t bucket_code(const pdp_dict *d, uint64_t b) {
@@ -506,12 +515,16 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             const uint32_t f = (tasks[t].flags & PDP_TASK_BBH) ? PDP_TASK_AB | PDP_TASK_BA : tasks[t].flags;
             all_rows += ((f & PDP_TASK_AB) ? tasks[t].a->n_genes : 0u) + ((f & PDP_TASK_BA) ? tasks[t].b->n_genes : 0u);
         }
+    // halvings of a direction's tiles below their default height (none where the caller chose it)
+    auto lowered = [&](const pdp_dict *R, uint32_t shift) {
+        return prm.tile_rows ? 0u : std::max(default_shift(R), shift) - shift;
+    };
     // Pass 1, in the caller's order: validation, output row layout, tile height per direction.
-    uint64_t bh_rows = 0, bbh_rows = 0, rec_est = 0;
+    uint64_t bh_rows = 0, bbh_rows = 0;
     // the sorted and hashed tile paths keep 8 bytes per record (12 with the filters' sums)
     uint32_t tile_lds = std::max<uint32_t>(lds_budget, (filt ? 12 : 8) * kTileCap);
     std::vector<DevTask> caller(n_tasks);
-    std::vector<uint64_t> cost(n_tasks);
+    std::vector<uint64_t> cost(n_tasks), task_est(n_tasks, 0);  // join cost, expected records
     std::vector<uint8_t> is_long(n_tasks, 0);  // the task takes the long-gene path
     for (uint32_t t = 0; t < n_tasks; ++t) {
         const pdp_task &tk = tasks[t];
@@ -583,8 +596,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             if (dense > kMaxTileLds)
                 return bail(fail(PDP_E_LIMIT, "task %u: %u target genes do not fit an LDS tile", t, C->n_genes));
             tile_lds = std::max<uint32_t>(tile_lds, static_cast<uint32_t>(dense));
-            // Unless the caller fixed the height: rows of long genes (over 512 letters on average, e.g.
-            // nucleotide genes) go 32 to a tile, and to fill the chip a plan with under 256 tiles takes
+            // Unless the caller fixed the height: to fill the chip a plan with under 256 tiles takes
             // lower ones, or under 512 where a tile's records (a row meets columns by chance, `met`) then
             // fit its hash table in one pass, down to 4 rows and up to 128 tiles per direction (two
             // genomes of 200 genes, k = 4: four tiles of 64 rows each way take 108 us, tiles of 4 rows
@@ -595,12 +607,13 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
                 const double met = 8.0 + len * double(C->capacity) *
                                              std::pow(double(alpha_spec(R->alphabet).sigma), -double(R->k));
                 uint32_t &sh = d.tile_shift[dir];
-                if (R->capacity / R->n_genes > 512) --sh;
+                sh = default_shift(R);
                 while (sh > 2 && (R->n_genes >> (sh - 1)) <= 128 &&
+                       with_slack(dir_est, default_shift(R) - (sh - 1)) <= kLowTileRecords &&
                        ((all_rows >> sh) < 256 || ((all_rows >> sh) < 512 && double(1u << (sh - 1)) * met <= kHashMax)))
                     --sh;
             }
-            rec_est += dir_est * tile_slack(d.tile_shift[dir]) / 4;
+            task_est[t] += with_slack(dir_est, lowered(R, d.tile_shift[dir]));
             d.tiles_n[dir] = static_cast<uint32_t>((uint64_t(R->n_genes) + (1u << d.tile_shift[dir]) - 1) >>
                                                    d.tile_shift[dir]);
         }
@@ -639,8 +652,15 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             d.row_base[0] = P->ab_row[t];
             d.row_base[1] = P->ba_row[t];
             any_colmax = true;
+            // no records, but candidates (16 bytes for a record's 8): pairs at a column's running
+            // maximum, at most the pairs that share anything, so half of one direction's estimate
+            // holds some forty a gene and keeps the scratch at the pair path's size (50 genomes of
+            // 4000 genes: 5.4 GB, 7.6 by pairs)
+            task_est[t] = direction_estimate(tasks[t]) / 2;
         }
     }
+    uint64_t rec_est = 0;
+    for (uint64_t e : task_est) rec_est += e;
     // Pass 2, largest tasks first: join items and tiles are numbered in this order, so work-groups
     // (and the persistent kernels' counters) take the long items early.
     // each tile's expected records, the estimate rec_est sums: a region of the one-pass join each
@@ -679,6 +699,8 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             }
             const uint32_t nrows = dir == 0 ? d.a.n_genes : d.b.n_genes;
             const uint32_t T = 1u << d.tile_shift[dir];
+            const pdp_task &tk = tasks[t];
+            const uint32_t lower = lowered((dir == 0) != ((d.flags & kTaskSwapped) != 0) ? tk.a : tk.b, d.tile_shift[dir]);
             for (uint32_t r0 = 0; r0 < nrows; r0 += T, ++tile_local) {
                 DevTile tl;
                 tl.task = i;
@@ -689,7 +711,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
                 tl.rcap = 0;
                 P->tiles.push_back(tl);
                 // the direction's estimate split by rows (a direction without genes expects none)
-                tile_est.push_back(nrows ? dir_est * tile_slack(d.tile_shift[dir]) / 4 * tl.nrows / nrows : 0);
+                tile_est.push_back(nrows ? with_slack(dir_est, lower) * tl.nrows / nrows : 0);
             }
         }
         join_tiles = std::max(join_tiles, tile_local);

@@ -24,10 +24,10 @@
 //     it, keeping the first few per row (ties kept; a row without shared
 //     k-mers has no best hit), following Eq. best_hit and the per-row work of
 //     Alg. 2.  A tile with more records than the table holds goes in groups of
-//     rows, and a row alone past it is summed densely.  The slab copy orders
+//     rows, and a row alone past it is summed densely.  k_rows_slab orders
 //     each row's hits by column; k_tile_write recomputes tiles with a row of
 //     more ties (sorted in LDS, or densely) and writes them in column order.
-//  5. k_bbh: each best hit (a, b) is kept when a is among b's best hits
+//  5. k_bbh_count, k_bbh_write: each best hit (a, b) is kept when a is among b's best hits
 //     (Eq. bidirectional_best_hit, the cross-check of Alg. 3).
 // With PDP_PARAM_COLMAX a task asking for both directions writes records for its
 // a-rows only; b's best hits are the rows at each column's maximum (Alg. 3): the AB
@@ -36,6 +36,8 @@
 // maximum become b's best hits.
 // Every output is written in a canonical order, so results do not depend on
 // scheduling.
+// Sets of genomes that are mostly compared with each other take group.hip's kernels in place of
+// 1 to 4; the row output (k_rows_slab, column candidates) and BBH below serve both.
 #include <algorithm>
 #include <type_traits>
 
@@ -1263,7 +1265,7 @@ __device__ __forceinline__ void tile_dense(const DevTile &tl, const DevTask &T, 
 // window count is gathered (one round trip for the whole table), d = n_row + n_col - m,
 // and the row maximum of m/d is kept as (m, d) by an exact compare-and-swap loop
 // (64-bit cross-multiplication).  A second sweep counts the columns at the maximum
-// (ties) and puts the first kSlab of them, unordered, in the row's slab; the slab copy
+// (ties) and puts the first kSlab of them, unordered, in the row's slab; k_rows_slab
 // orders them by column.
 template <bool CM>
 __device__ __forceinline__ void tile_hashed(const DevTile &tl, const DevTask &T, const uint2 *recs, uint64_t rb,
@@ -1884,7 +1886,7 @@ __global__ __launch_bounds__(NT) void k_long_rows(const DevTask *__restrict__ ta
         const uint32_t row = lr - sg.first;
         const uint32_t grow = T.row_base[sg.dir] + row;
         const uint32_t pos0 = WRITE ? bh_ptr[grow] : 0u;
-        if (WRITE && bh_ptr[grow + 1] - pos0 <= kSlab) continue;  // the slab copy placed this row
+        if (WRITE && bh_ptr[grow + 1] - pos0 <= kSlab) continue;  // k_rows_slab placed this row
         const uint32_t e0 = load_global(R.mv_ptr + row), e1 = load_global(R.mv_ptr + row + 1);
         if (NT != kLongThreadsBig && e1 - e0 > kLongRowEntries) continue;  // the other launch's row
         const bool filt = T.theta_d || T.tau_d;
@@ -2105,6 +2107,14 @@ static uint64_t pair_partials(const PlanShape &p) {
     return std::max({uint64_t(scan_partials(p.total_tiles)), row_groups(p.bh_rows), row_groups(p.bbh_rows)}) + 1;
 }
 
+// Row sums and listed rows come after the join, so they lie in its cells (one word per item and tile,
+// dead by then) where these hold them: a plan takes no more scratch for them.  Groups and long genes
+// have no cells.
+static uint64_t row_words(const PlanShape &p) {
+    return align_up(pair_partials(p), 64) + align_up(pair_partials(p) / 4096 + 2, 64) + (p.colmax ? uint64_t(p.bh_rows) + 1 : 0);
+}
+static bool rows_in_cells(const PlanShape &p) { return row_words(p) <= p.total_cells; }
+
 uint64_t pair_ws_bytes(const PlanShape &p) {
     const uint64_t A = 256;
     uint64_t s = 0;
@@ -2121,13 +2131,14 @@ uint64_t pair_ws_bytes(const PlanShape &p) {
     s += align_up(8 * (uint64_t(p.total_tiles) + 1), A);  // record range of each tile
     s += align_up(16 * kSlab * (uint64_t(p.bh_rows) + 1), A);
     s += align_up(4 * (uint64_t(p.total_tiles) + 1), A);
-    s += align_up(4 * pair_partials(p), A) + align_up(4 * (pair_partials(p) / 4096 + 2), A);
-    const uint64_t colrows = p.colmax ? uint64_t(p.bh_rows) + 1 : 1;
-    s += align_up(8 * colrows, A);                                  // column keys
-    s += align_up(4 * colrows, A);                                  // big-row cursors
-    s += align_up(4 * colrows, A);                                  // big rows
-    s += align_up(16 * std::max<uint64_t>(p.colmax ? p.cand_cap : 0, 1), A);  // candidates
-    s += align_up(sizeof(DevLongSeg) * std::max<uint64_t>(p.n_long_segs, 1), A);
+    if (!rows_in_cells(p)) s += align_up(4 * row_words(p), A);
+    if (p.colmax) {
+        const uint64_t colrows = uint64_t(p.bh_rows) + 1;
+        s += align_up(8 * colrows, A);                              // column keys
+        s += align_up(4 * colrows, A);                              // big-row cursors
+        s += align_up(16 * std::max<uint64_t>(p.cand_cap, 1), A);   // candidates
+    }
+    s += align_up(sizeof(DevLongSeg) * uint64_t(p.n_long_segs), A);
     if (p.n_gdicts) {
         s += align_up(sizeof(DevGroupDict) * uint64_t(p.n_gdicts), A) + align_up(sizeof(DevGroupTgt) * uint64_t(p.n_gtgts), A);
         s += align_up(sizeof(DevGroupItem) * (uint64_t(p.n_gitems) + p.n_gitems_wide), A);
@@ -2166,17 +2177,22 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
     w.next_fused = reinterpret_cast<uint32_t *>(w.counters) + 8;
     w.slab = reinterpret_cast<uint4 *>(take(16 * kSlab * (uint64_t(p.bh_rows) + 1)));
     w.overflow_tiles = reinterpret_cast<uint32_t *>(take(4 * (uint64_t(p.total_tiles) + 1)));
-    w.partials = reinterpret_cast<uint32_t *>(take(4 * pair_partials(p)));
-    w.partials2 = reinterpret_cast<uint32_t *>(take(4 * (pair_partials(p) / 4096 + 2)));
+    w.partials = rows_in_cells(p) ? w.cells : reinterpret_cast<uint32_t *>(take(4 * row_words(p)));
+    w.partials2 = w.partials + align_up(pair_partials(p), 64);
+    w.big_rows = w.partials2 + align_up(pair_partials(p) / 4096 + 2, 64);
     w.join_done = reinterpret_cast<uint32_t *>(w.counters) + 16;
     w.n_big = reinterpret_cast<uint32_t *>(w.counters) + 17;
-    const uint64_t colrows = p.colmax ? uint64_t(p.bh_rows) + 1 : 1;
-    w.colkey = reinterpret_cast<unsigned long long *>(take(8 * colrows));
-    w.colcursor = reinterpret_cast<uint32_t *>(take(4 * colrows));
-    w.big_rows = reinterpret_cast<uint32_t *>(take(4 * colrows));
-    w.cands = reinterpret_cast<uint4 *>(take(16 * std::max<uint64_t>(p.colmax ? p.cand_cap : 0, 1)));
+    w.colkey = nullptr;
+    w.colcursor = nullptr;
+    w.cands = nullptr;
+    if (p.colmax) {
+        const uint64_t colrows = uint64_t(p.bh_rows) + 1;
+        w.colkey = reinterpret_cast<unsigned long long *>(take(8 * colrows));
+        w.colcursor = reinterpret_cast<uint32_t *>(take(4 * colrows));
+        w.cands = reinterpret_cast<uint4 *>(take(16 * std::max<uint64_t>(p.cand_cap, 1)));
+    }
     w.cand_count = reinterpret_cast<uint32_t *>(w.counters) + 6;
-    w.long_segs = reinterpret_cast<DevLongSeg *>(take(sizeof(DevLongSeg) * std::max<uint64_t>(p.n_long_segs, 1)));
+    w.long_segs = reinterpret_cast<DevLongSeg *>(take(sizeof(DevLongSeg) * uint64_t(p.n_long_segs)));
     w.gdicts = nullptr;
     if (p.n_gdicts) {
         w.gdicts = reinterpret_cast<DevGroupDict *>(take(sizeof(DevGroupDict) * uint64_t(p.n_gdicts)));

@@ -214,13 +214,14 @@ uint64_t footprint(pdp_server *S, ServeRequest *r, uint64_t *plan_ws) {
 }
 
 // Creates the request's plan from its (not yet built) dictionary descriptor.
-int32_t make_plan(pdp_server *S, ServeRequest *r) {
+int32_t make_plan(pdp_server *S, ServeRequest *r, bool default_tiles) {
     if (r->plan) pdp_plan_destroy(r->plan);
     r->plan = nullptr;
     std::vector<pdp_task> tasks(S->residents.size());
     for (size_t i = 0; i < tasks.size(); ++i) tasks[i] = {&r->dict, &S->residents[i], PDP_TASK_BBH, 0};
     pdp_params p = S->cfg.params;
     p.inc_capacity = r->inc_cap;
+    if (default_tiles && !p.tile_rows) p.tile_rows = 1u << kDefaultTileShift;
     return pdp_plan_create(tasks.data(), static_cast<uint32_t>(tasks.size()), &p, &r->plan);
 }
 
@@ -235,8 +236,12 @@ int32_t prepare_plan(pdp_server *S, ServeRequest *r) {
     if (rc == PDP_OK)
         rc = pdp_dict_bind(reinterpret_cast<void *>(uintptr_t(256)), dict_bytes, r->n_genes, r->n_res, S->cfg.k,
                            S->cfg.alphabet, r->dict_flags, &r->dict);
-    if (rc == PDP_OK) rc = make_plan(S, r);
-    if (rc == PDP_OK) r->foot_bytes = footprint(S, r, &r->foot_plan_ws);
+    // the lower tiles that a small plan takes by itself cost scratch: not where they alone pass the budget
+    for (const bool default_tiles : {false, true}) {
+        if (rc == PDP_OK) rc = make_plan(S, r, default_tiles);
+        if (rc == PDP_OK) r->foot_bytes = footprint(S, r, &r->foot_plan_ws);
+        if (rc != PDP_OK || S->cfg.params.tile_rows || r->foot_bytes <= S->arena->size()) break;
+    }
     r->planned = rc == PDP_OK;
     return rc;
 }
@@ -279,7 +284,7 @@ int32_t launch_request(pdp_server *S, ServeSlot &slot, ServeRequest *r, uint64_t
     const pdp_dict placeholder = r->dict;
     int32_t rc = pdp_dict_bind(dict_mem, arena, r->n_genes, r->n_res, S->cfg.k, S->cfg.alphabet, r->dict_flags, &r->dict);
     if (rc) return rc;
-    rc = r->plan ? plan_rebind(r->plan, &placeholder, &r->dict) : make_plan(S, r);
+    rc = r->plan ? plan_rebind(r->plan, &placeholder, &r->dict) : make_plan(S, r, false);
     if (rc) return rc;
     // host input -> pinned staging -> device; pinned output staging sized for the results
     const uint64_t in_bytes = r->n_res + 8 * (uint64_t(r->n_genes) + 1);
