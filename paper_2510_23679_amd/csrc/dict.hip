@@ -846,14 +846,18 @@ constexpr uint32_t kIxPlaceThreads = 1024;  // a placement work-group: its block
 // and writes each entry at its run start plus its rank, in the record form R the bin sort
 // keeps (8 bytes when the build allows it, so the scattered stores and the sort's loads move
 // half the bytes).  The order inside a bin depends on scheduling; k_ix_sort_bin sorts every
-// bin completely.
-template <typename R, uint32_t kIxPerThread>
+// bin completely.  STAGE: the block's records go through LDS in the order of their bins first
+// (128 KB, so one work-group of 16 waves per CU instead of two), so that a wave's store covers the few
+// lines of its runs instead of 64 partial ones, which bound it: 1.53 GB written for 0.55 GB of records on
+// 50 genomes.  450 -> 295 us there, 10 x 3000 genes 81 -> 60, nucleotides 292 -> 169, one nucleotide
+// genome of 220 blocks 47 -> 32.  (With bins of 512 entries, runs of 6.5 records, it lost.)
+template <typename R, uint32_t kIxPerThread, bool STAGE>
 __global__ __launch_bounds__(kIxPlaceThreads) void k_ix_place(const DevBuild *__restrict__ table, uint32_t n_genomes,
                                                   const uint32_t *__restrict__ gptr, const uint32_t *__restrict__ binoff,
                                                   uint32_t *__restrict__ bintot, const uint32_t *__restrict__ ent_gene,
                                                   const uint2 *__restrict__ ent_rec) {
     constexpr bool REC = sizeof(R) == 8;
-    extern __shared__ uint32_t cur[];
+    extern __shared__ __align__(8) uint32_t cur[];
     __shared__ uint32_t s_t;
     if (threadIdx.x == 0) s_t = find_genome_by_block(table, n_genomes, blockIdx.x);
     __syncthreads();
@@ -884,6 +888,42 @@ __global__ __launch_bounds__(kIxPlaceThreads) void k_ix_place(const DevBuild *__
         if (e0 + q * kIxPlaceThreads + threadIdx.x < e1) rank[q] = atomicAdd(&cur[entry_bucket<REC>(B, c[q]) >> B.hshift], 1u);
     __syncthreads();
     const uint32_t gstart = binoff[B.bin_base];  // the genome's first entry in the scanned order
+    if constexpr (STAGE) {
+        static_assert(REC, "staged records are words");
+        __shared__ uint32_t s_tmp[kIxPlaceThreads / kWave + 1];
+        uint64_t *rec = reinterpret_cast<uint64_t *>(cur + ((B.nh + 1) & ~1u));
+        const uint32_t per = (B.nh + kIxPlaceThreads - 1) / kIxPlaceThreads, b0 = threadIdx.x * per;
+        uint32_t sum = 0, total;
+        for (uint32_t b = 0; b < per && b0 + b < B.nh; ++b) sum += cur[b0 + b];
+        uint32_t at = block_exclusive_scan<kIxPlaceThreads>(sum, s_tmp, &total);  // contains barriers
+        uint32_t run[kIxMaxBins / kIxPlaceThreads];  // from a place in the block to its place in the genome
+#pragma unroll
+        for (uint32_t b = 0; b < kIxMaxBins / kIxPlaceThreads; ++b) {
+            if (b >= per || b0 + b >= B.nh) continue;
+            const uint32_t i = b0 + b, n = cur[i];
+            cur[i] = at;
+            run[b] = n ? binoff[B.bin_base + i] - gstart + atomicSub(&bintot[B.bin_base + i], n) - n - at : 0u;
+            at += n;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < kIxPerThread; ++q)
+            if (e0 + q * kIxPlaceThreads + threadIdx.x < e1)
+                rec[cur[entry_bucket<REC>(B, c[q]) >> B.hshift] + rank[q]] = (static_cast<uint64_t>(second[q]) << 32) | c[q];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t b = 0; b < kIxMaxBins / kIxPlaceThreads; ++b)
+            if (b < per && b0 + b < B.nh) cur[b0 + b] = run[b];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < kIxPerThread; ++q) {
+            const uint32_t i = q * kIxPlaceThreads + threadIdx.x;
+            if (i >= e1 - e0) continue;
+            const uint64_t r = rec[i];
+            store_global(reinterpret_cast<uint64_t *>(B.ix_tmp) + (cur[entry_bucket<REC>(B, static_cast<uint32_t>(r)) >> B.hshift] + i), r);
+        }
+        return;
+    }
     for (uint32_t i = threadIdx.x; i < B.nh; i += blockDim.x) {
         const uint32_t n = cur[i];
         if (n) cur[i] = binoff[B.bin_base + i] - gstart + atomicSub(&bintot[B.bin_base + i], n) - n;
@@ -1370,17 +1410,25 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
                            dcnt, ent_rec, bintot, total_bins, few_bins ? binoff : nullptr, counters + 4);
     PDP_TRY(hipGetLastError());
     if (!few_bins) PDP_TRY(launch_scan(bintot, binoff, total_bins, partials, s));  // every bin's range
-    auto place = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kIxPlaceThreads), hist_lds, s, table, n, dcnt, binoff, bintot,
+    auto place = [&](auto kernel, uint32_t lds) {
+        hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kIxPlaceThreads), lds, s, table, n, dcnt, binoff, bintot,
                            ent_gene, ent_rec);
     };
     constexpr uint32_t kPer = kIxBlock / kIxPlaceThreads, kPerSmall = kIxBlockSmall / kIxPlaceThreads;
+    const uint32_t stage_lds = 4 * ((max_nh + 1) & ~1u) + 8 * kIxBlock;
     if (narrow_rec) {
-        if (small) place(k_ix_place<uint2, kPerSmall>);
-        else place(k_ix_place<uint2, kPer>);
+        if (small) {
+            place(k_ix_place<uint2, kPerSmall, false>, hist_lds);
+        } else if (stage_lds <= kMaxTileLds) {
+            PDP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(k_ix_place<uint2, kPer, true>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(stage_lds)));
+            place(k_ix_place<uint2, kPer, true>, stage_lds);
+        } else {
+            place(k_ix_place<uint2, kPer, false>, hist_lds);
+        }
     } else {
-        if (small) place(k_ix_place<uint4, kPerSmall>);
-        else place(k_ix_place<uint4, kPer>);
+        if (small) place(k_ix_place<uint4, kPerSmall, false>, hist_lds);
+        else place(k_ix_place<uint4, kPer, false>, hist_lds);
     }
     PDP_TRY(hipGetLastError());
     if (narrow_rec)
