@@ -1420,8 +1420,9 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
         if (small) {
             place(k_ix_place<uint2, kPerSmall, false>, hist_lds);
         } else if (stage_lds <= kMaxTileLds) {
+            // the limit, not this build's size: another thread may be building with more bins
             PDP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(k_ix_place<uint2, kPer, true>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(stage_lds)));
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kMaxTileLds)));
             place(k_ix_place<uint2, kPer, true>, stage_lds);
         } else {
             place(k_ix_place<uint2, kPer, false>, hist_lds);
