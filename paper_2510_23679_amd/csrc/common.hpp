@@ -138,6 +138,22 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t *t
     return r;
 }
 
+// Counts this work-group as ended in *done (zero before the launch); true, for all its threads, in the
+// one that ends last, which then sees every global write and atomic of the launch.  Every thread
+// fences before the barrier: the barrier is a release at work-group scope only, which leaves the
+// other waves' atomics without return value in flight, and a fence waits for its own wave's alone.
+// flag: a word of LDS.  Contains barriers; every thread of the work-group must call it.
+__device__ __forceinline__ bool last_group(uint32_t *done, uint32_t *flag) {
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        *flag = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x ? 1u : 0u;
+    __syncthreads();
+    if (!*flag) return false;
+    __threadfence();
+    return true;
+}
+
 // Comparator network sort of n items by one work-group, ascending, for any n.
 // It is the bitonic network in its "flip" form: every comparator (lo, hi) with
 // lo < hi leaves the smaller item at lo, so the missing items past n act as +inf

@@ -792,13 +792,7 @@ __global__ __launch_bounds__(256) void k_ix_hist(const DevBuild *__restrict__ ta
         if (h[i]) atomicAdd(&bintot[B.bin_base + i], h[i]);
     if (!binoff) return;
     // few bins: the block that ends last scans the totals into every bin's range
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        s_last = atomicAdd(done, 1u) + 1u == gridDim.x ? 1u : 0u;
-    }
-    __syncthreads();
-    if (!s_last) return;
+    if (!last_group(done, &s_last)) return;
     uint32_t carry = 0;
     for (uint32_t b0 = 0; b0 < total_bins; b0 += 256 * 8) {
         uint32_t v[8], sum = 0;

@@ -466,13 +466,7 @@ __device__ __forceinline__ void ranges_filled(const TileRanges &R) {
 __device__ __forceinline__ void ranges_counted(const TileRanges &R, const uint32_t *tile_tot,
                                                const unsigned long long *total_ptr, uint64_t rec_cap, uint32_t *scan,
                                                uint32_t *last) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        *last = atomicAdd(R.done, 1u) + 1u == gridDim.x ? 1u : 0u;
-    }
-    __syncthreads();
-    if (!*last) return;
+    if (!last_group(R.done, last)) return;
     const uint64_t total = __hip_atomic_load(total_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool refit = R.fill != nullptr && total <= rec_cap && total > 0;
     const uint64_t slack = refit ? rec_cap - total : 0;
