@@ -359,8 +359,8 @@ static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks
     // small plans: smaller items and tiles, so that the chip's work-group slots are filled once
     const uint64_t target = std::min<uint64_t>(kGroupTarget, std::max<uint64_t>(256, all_cap / 1024));
     const double fill_rows = std::max(16.0, double(all_rows) / 1536.0);
-    struct Run {  // the items of one group: buckets in steps of nb
-        uint32_t dict0, n_dicts, nb, n_buckets;
+    struct Run {  // the items of one group: buckets in steps of nb, from every multiple of unit on
+        uint32_t dict0, n_dicts, nb, n_buckets, unit;
         bool wide;
     };
     std::vector<Run> runs;
@@ -411,25 +411,34 @@ static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks
         }
         if (!ok) continue;
         // items: buckets holding about kGroupTarget entries; a k-mer's identity there is its code's
-        // low word when the codes of every item span less than 2^32
+        // low word when the codes of every item span less than 2^32.  Codes jump where a leading
+        // letter changes (5 bits for 20 letters), so items then end at every multiple of `unit`
+        // buckets, unit a power of the letters: at most twice the items.  Where that does not do,
+        // the whole code is the identity; items of a few buckets instead would keep the narrow one but
+        // be mostly empty (10 x 3000 genes, k = 10: 160000 items, 1018 us, 209 so; the
+        // pair path 325.  k = 25 nucleotides, 10 x 3000: 262144 items, 1552 us, 353 so; the pair path 615).
         const uint64_t nbk = d0->n_buckets;
-        uint64_t nb = std::min<uint64_t>(nbk, std::max<uint64_t>(1, target * nbk / std::max<uint64_t>(cap, 1)));
+        const uint64_t nb = std::min<uint64_t>(nbk, std::max<uint64_t>(1, target * nbk / std::max<uint64_t>(cap, 1)));
         const uint32_t tail = al.bits * (d0->k - d0->lead);
-        auto narrow = [&](uint64_t n) {
+        auto narrow = [&](uint64_t unit) {
             if (al.bits * d0->k <= 32) return true;
             if (tail > 32) return false;
-            for (uint64_t b = 0; b < nbk; b += n) {
-                const uint64_t last = std::min(nbk, b + n) - 1;
-                if (bucket_code(d0, last) - bucket_code(d0, b) + (1ull << tail) > (1ull << 32)) return false;
-            }
+            for (uint64_t u = 0; u < nbk; u += unit)
+                for (uint64_t b = u; b < std::min(nbk, u + unit); b += nb) {
+                    const uint64_t last = std::min({nbk, u + unit, b + nb}) - 1;
+                    if (bucket_code(d0, last) - bucket_code(d0, b) + (1ull << tail) > (1ull << 32)) return false;
+                }
             return true;
         };
-        bool is_narrow = narrow(nb);
-        if (!is_narrow && nb > 1 && narrow(1)) {  // smaller items keep the narrow identity
-            while (!(is_narrow = narrow(nb))) nb = std::max<uint64_t>(1, nb / 2);
+        uint64_t unit = nbk;
+        bool is_narrow = narrow(unit);
+        while (!is_narrow && unit / al.sigma >= nb) {
+            unit /= al.sigma;
+            is_narrow = narrow(unit);
         }
+        if (!is_narrow) unit = nbk;
         runs.push_back({static_cast<uint32_t>(P->gdicts.size()), D, static_cast<uint32_t>(nb), static_cast<uint32_t>(nbk),
-                        !is_narrow});
+                        static_cast<uint32_t>(unit), !is_narrow});
         // a tile's rows share one table: fewer rows where rows meet many columns by chance
         const double want = std::min(std::min<double>(kGroupTileRows, fill_rows), 1100.0 / (chance + 2.0));
         for (uint32_t i = 0; i < D; ++i) {
@@ -467,10 +476,13 @@ static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks
     // items of all groups by bucket range (as a fraction of the group's buckets)
     std::vector<std::pair<double, DevGroupItem>> order[2];
     for (const Run &r : runs)
-        for (uint64_t b = 0; b < r.n_buckets; b += r.nb)
-            order[r.wide].push_back({double(b) / r.n_buckets,
-                                     DevGroupItem{r.dict0, r.n_dicts, static_cast<uint32_t>(b),
-                                                  static_cast<uint32_t>(std::min<uint64_t>(r.nb, r.n_buckets - b))}});
+        for (uint64_t u = 0; u < r.n_buckets; u += r.unit) {
+            const uint64_t end = std::min<uint64_t>(r.n_buckets, u + r.unit);
+            for (uint64_t b = u; b < end; b += r.nb)
+                order[r.wide].push_back({double(b) / r.n_buckets,
+                                         DevGroupItem{r.dict0, r.n_dicts, static_cast<uint32_t>(b),
+                                                      static_cast<uint32_t>(std::min<uint64_t>(r.nb, end - b))}});
+        }
     for (int w = 0; w < 2; ++w) {
         if (runs.size() > 1)
             std::stable_sort(order[w].begin(), order[w].end(), [](const auto &x, const auto &y) { return x.first < y.first; });

@@ -1,0 +1,42 @@
+"""Work items of the group path (host side, no GPU): an item holds a fair share of a group's index
+entries whatever the k-mer length, so that plan tables, launches and host time stay in proportion."""
+import ctypes as C
+
+import pytest
+
+import paper_2510_23679_amd as pdp
+from paper_2510_23679_amd import binding as B
+
+
+def _dicts(n, genes, per, k, alphabet):
+    out, base = [], 256
+    for _ in range(n):
+        arena, _ = pdp.dict_size(genes, genes * per, k, alphabet)
+        d = B.pdp_dict()
+        B.check(pdp.lib().pdp_dict_bind(base, arena, genes, genes * per, k, B.alphabet_id(alphabet), 0, C.byref(d)), "bind")
+        base += (arena + 4095) // 4096 * 4096
+        out.append(d)
+    return out
+
+
+def _items(dicts):
+    n = len(dicts)
+    tasks = (B.pdp_task * (n * (n - 1) // 2))()
+    for t, (i, j) in zip(tasks, [(i, j) for i in range(n) for j in range(i)]):
+        t.a, t.b, t.flags = C.pointer(dicts[i]), C.pointer(dicts[j]), pdp.PDP_TASK_BBH
+    h, info = B.vp(), B.pdp_plan_info()
+    B.check(pdp.lib().pdp_plan_create(tasks, len(tasks), None, C.byref(h)), "plan")
+    B.check(pdp.lib().pdp_plan_info_get(h, C.byref(info)), "info")
+    pdp.lib().pdp_plan_destroy(h)
+    return info.join_groups
+
+
+@pytest.mark.parametrize("alphabet,k", [("aa", k) for k in range(6, 13)] + [("nt", k) for k in (15, 17, 21, 23, 24, 25, 26, 31)])
+@pytest.mark.parametrize("n,genes", [(12, 200), (12, 1270), (10, 3000), (40, 4000)])
+def test_items_are_in_proportion_to_the_entries(n, genes, alphabet, k):
+    per = 300 if alphabet == "aa" else 900
+    buckets = 160000 if alphabet == "aa" else 262144
+    entries = n * (genes * per + 1)
+    # about 1536 entries an item (fewer in small plans: at least 256), half of that for a narrow
+    # identity, and whole buckets: an item's share is rounded down by at most half
+    assert _items(_dicts(n, genes, per, k, alphabet)) <= min(buckets, 4 * max(entries // 1536, min(1024, entries // 256)) + 8)
