@@ -937,6 +937,7 @@ int32_t pdp_plan_launch(const pdp_plan *plan, pdp_bh_out *bh, pdp_bbh_out *bbh, 
     PlanShape shape = plan->shape;
     if (!plan->device_ready) {
         hipError_t e = allow_tile_lds(plan->shape.tile_lds);
+        if (e == hipSuccess && plan->shape.n_gtiles) e = allow_group_lds();
         if (e != hipSuccess) return hip_fail(e, "pdp_plan_launch");
         if (plan->persistent) {
             plan->join_grid = plan->shape.fused ? persistent_fused_grid(plan->shape.join_tiles) : persistent_join_grid();

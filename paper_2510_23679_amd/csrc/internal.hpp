@@ -151,7 +151,6 @@ constexpr uint32_t kGroupTarget = 1536;      // entries the plan aims at per ite
 constexpr uint32_t kGroupTileRows = 256;     // (gene, target) rows per tile at most (8-bit row field)
 constexpr uint32_t kGroupCursorStride = 16;  // words between two tiles' cursors: atomics on one line queue up
 constexpr uint32_t kGroupHashBits = 11;      // LDS hash table of a tile: 2^11 (row, column) sums
-constexpr uint32_t kGroupHashSlots = 1u << kGroupHashBits;
 
 // A dictionary of a group.  As a source it owns best-hit rows: n_tgt targets (entries tgt_base..
 // of the target table), its genes in tiles of 2^gshift.
@@ -270,6 +269,9 @@ struct PairWs {
     DevGroupItem *gitems;         // narrow items (32-bit identities), then wide ones
     DevGroupTile *gtiles;
     uint8_t *tmap;
+    uint2 *gbig;                  // pieces of items past the grouping kernel's LDS: narrow ones, then wide ones
+    uint2 *gbig_tiles;            // tiles past the tile kernel's table: (tile, first row)
+    uint32_t *n_gbig;             // counters words 18 to 20: how many of each
     uint32_t *gcursor;            // per group tile: end of its descriptors, start of its inline ones
     uint2 *gdesc;                 // shared k-mers of each tile's genes
     uint32_t *gpost;              // postings of the shared k-mers, and their aux words
@@ -307,6 +309,8 @@ int32_t plan_rebind(pdp_plan *plan, const pdp_dict *from, const pdp_dict *to);
 uint32_t persistent_fused_grid(uint32_t join_tiles);
 uint32_t persistent_tile_grid(uint32_t tile_lds);
 hipError_t allow_tile_lds(uint32_t tile_lds);
+// Pieces of oversized items past one per item, at most (k_group_join).
+inline uint64_t group_pieces(const PlanShape &p) { return 4 * p.gentries / kGroupCap; }
 uint64_t pair_ws_bytes(const PlanShape &p);
 PairWs pair_ws_carve(void *ws, const PlanShape &p);
 // Optional events recorded around one kernel of a launch (kernel < 0: none).
@@ -317,6 +321,7 @@ struct KernelTimer {
 hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp_bbh_out *bbh,
                         pdp_status *st, hipStream_t s, const KernelTimer *timer);
 // The group path's part of a launch: k_group_join (timed as the join) and k_group_tile.
+hipError_t allow_group_lds();
 hipError_t launch_group_join(const PlanShape &p, const PairWs &w, hipStream_t s);
 hipError_t launch_group_tiles(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, hipStream_t s);
 // Families (connected components of the BBH network) into labels[n_nodes].

@@ -2136,7 +2136,9 @@ uint64_t pair_ws_bytes(const PlanShape &p) {
     if (p.n_gdicts) {
         s += align_up(sizeof(DevGroupDict) * uint64_t(p.n_gdicts), A) + align_up(sizeof(DevGroupTgt) * uint64_t(p.n_gtgts), A);
         s += align_up(sizeof(DevGroupItem) * (uint64_t(p.n_gitems) + p.n_gitems_wide), A);
+        s += align_up(8 * (uint64_t(p.n_gitems) + p.n_gitems_wide + 2 * group_pieces(p)), A);
         s += align_up(sizeof(DevGroupTile) * std::max<uint64_t>(p.n_gtiles, 1), A) + align_up(p.n_tmap, A);
+        s += align_up(8 * std::max<uint64_t>(p.n_gtiles, 1), A);
         s += align_up(4 * kGroupCursorStride * (uint64_t(p.n_gtiles) + 1), A);
         s += align_up(8 * p.gentries, A) + 2 * align_up(4 * p.gentries, A);
     }
@@ -2176,6 +2178,7 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
     w.big_rows = w.partials2 + align_up(pair_partials(p) / 4096 + 2, 64);
     w.join_done = reinterpret_cast<uint32_t *>(w.counters) + 16;
     w.n_big = reinterpret_cast<uint32_t *>(w.counters) + 17;
+    w.n_gbig = reinterpret_cast<uint32_t *>(w.counters) + 18;
     w.colkey = nullptr;
     w.colcursor = nullptr;
     w.cands = nullptr;
@@ -2192,8 +2195,10 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
         w.gdicts = reinterpret_cast<DevGroupDict *>(take(sizeof(DevGroupDict) * uint64_t(p.n_gdicts)));
         w.gtgts = reinterpret_cast<DevGroupTgt *>(take(sizeof(DevGroupTgt) * uint64_t(p.n_gtgts)));
         w.gitems = reinterpret_cast<DevGroupItem *>(take(sizeof(DevGroupItem) * (uint64_t(p.n_gitems) + p.n_gitems_wide)));
+        w.gbig = reinterpret_cast<uint2 *>(take(8 * (uint64_t(p.n_gitems) + p.n_gitems_wide + 2 * group_pieces(p))));
         w.gtiles = reinterpret_cast<DevGroupTile *>(take(sizeof(DevGroupTile) * std::max<uint64_t>(p.n_gtiles, 1)));
         w.tmap = reinterpret_cast<uint8_t *>(take(p.n_tmap));
+        w.gbig_tiles = reinterpret_cast<uint2 *>(take(8 * std::max<uint64_t>(p.n_gtiles, 1)));
         w.gcursor = reinterpret_cast<uint32_t *>(take(4 * kGroupCursorStride * (uint64_t(p.n_gtiles) + 1)));
         w.gdesc = reinterpret_cast<uint2 *>(take(8 * p.gentries));
         w.gpost = reinterpret_cast<uint32_t *>(take(4 * p.gentries));
