@@ -1026,6 +1026,7 @@ __device__ __forceinline__ void sort_recs(R *r, uint32_t n) {
 
 constexpr uint32_t kIxSmallBucket = 32;   // slots up to this size are ranked entry by entry
 constexpr uint32_t kIxBigList = 64;       // larger slots a bin sorts one by one with the work-group
+constexpr uint32_t kIxCuts = 32;          // parts of a bin past LDS that are laid out at a time
 // A bin sort's work-group: LDS for 4096 records of 8 bytes or 1024 of 16, and twice as many slots.
 template <typename R>
 struct BinSort {
@@ -1034,6 +1035,7 @@ struct BinSort {
     static constexpr uint32_t kLds = kThreads * kPer;      // entries of a bin sorted in LDS
     static constexpr uint32_t kSlots = 2 * kLds;           // counting-sort slots of a bin (buckets x sub-slots)
     static constexpr uint32_t kWords = kSlots / 2 / kThreads;  // 16-bit slot counters, words per thread
+    static constexpr uint32_t kWavesPerSimd = sizeof(R) == 8 ? 6 : 7;  // what the LDS allows
 };
 
 // Counting-sort slot of a code inside the bin starting at bucket b0: the bucket, then the
@@ -1057,26 +1059,218 @@ __device__ __forceinline__ uint32_t rec_slot(const DevBuild &B, const uint2 &r, 
 
 __device__ __forceinline__ uint32_t slot16(const uint32_t *w, uint32_t s) { return (w[s >> 1] >> ((s & 1u) * 16u)) & 0xFFFFu; }
 
-// One work-group per coarse bin: its entries ordered by (code, gene) and the bin's part of
-// the bucket directory.  Usual case (the bin fits LDS and its slots fit kSlots): a counting sort
-// by slot (LDS histogram, scan, scatter), whose offsets at the first slot of every bucket are the
-// directory; then every entry finds its rank among its slot's entries and goes straight to its
-// place.  Slots past kIxSmallBucket entries are sorted by the work-group first.  Otherwise the
-// whole bin is sorted in LDS, or in place in global memory when it does not fit.
-// Bins of 1350 to 2700 8-byte records on average (50 genomes of 3000 to 5000 genes: 2176): sort 0.44 ms,
-// placement 0.45 ms.  With half of that 0.56 and 0.55 ms, with a quarter 0.87 and 0.70 ms: the
-// placement's runs per (block, bin) get shorter and the work-groups emptier.
+// LDS of a bin sort's work-group.
 template <typename R>
-__global__ __launch_bounds__(BinSort<R>::kThreads) void k_ix_sort_bin(const DevBuild *__restrict__ table,
+struct BinLds {
+    R rec[BinSort<R>::kLds];
+    uint32_t slot[BinSort<R>::kSlots / 2 + 1];  // two 16-bit counters, then starts, per word
+    uint32_t big[kIxBigList];
+    uint32_t tmp[BinSort<R>::kThreads / kWave + 1];
+    uint32_t cut[kIxCuts + 1], pos[kIxCuts + 1];  // parts of a bin past LDS: first slot, entries before it
+    uint32_t nbig, n, ncuts;
+};
+
+// The m records in registers (record q * kThreads + tid in r[q]), all of slots [c0, c0 + kSlots) of the bin from
+// bucket b0 on, to the index from entry lo on, ordered by (code, gene): a counting sort by slot (LDS
+// histogram, scan, scatter), then every entry finds its rank among its slot's entries and goes
+// straight to its place.  Slots past kIxSmallBucket entries are sorted by the work-group first.
+// L.slot (left holding the slots' starts) and L.nbig are zero before, with a barrier in between.
+template <typename R>
+__device__ __forceinline__ void bin_part(const DevBuild &B, const R (&r)[BinSort<R>::kPer], uint32_t m, uint32_t b0,
+                                         uint32_t c0, uint32_t lo, BinLds<R> &L) {
+    using S = BinSort<R>;
+    constexpr uint32_t NT = S::kThreads, kIxPer = S::kPer;
+    const uint32_t tid = threadIdx.x;
+    uint32_t rank[kIxPer], bk[kIxPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kIxPer; ++q) {
+        if (q * NT + tid >= m) continue;
+        const uint32_t b = rec_slot(B, r[q], b0) - c0, sh = (b & 1u) * 16u;
+        bk[q] = b;
+        rank[q] = (atomicAdd(&L.slot[b >> 1], 1u << sh) >> sh) & 0xFFFFu;
+    }
+    __syncthreads();
+    {  // exclusive scan of the slot sizes
+        uint32_t w[S::kWords], sum = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < S::kWords; ++q) {
+            w[q] = L.slot[tid * S::kWords + q];
+            sum += (w[q] & 0xFFFFu) + (w[q] >> 16);
+        }
+        uint32_t total;
+        uint32_t run = block_exclusive_scan<NT>(sum, L.tmp, &total);
+#pragma unroll
+        for (uint32_t q = 0; q < S::kWords; ++q) {
+            const uint32_t b = (tid * S::kWords + q) * 2, n0 = w[q] & 0xFFFFu, n1 = w[q] >> 16;
+            L.slot[tid * S::kWords + q] = run | ((run + n0) << 16);
+            run += n0 + n1;
+            for (uint32_t x = 0; x < 2; ++x)
+                if ((x ? n1 : n0) > kIxSmallBucket) {
+                    const uint32_t idx = atomicAdd(&L.nbig, 1u);
+                    if (idx < kIxBigList) L.big[idx] = b + x;
+                }
+        }
+        if (tid == 0) L.slot[S::kSlots / 2] = m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < kIxPer; ++q)
+        if (q * NT + tid < m) L.rec[slot16(L.slot, bk[q]) + rank[q]] = r[q];
+    __syncthreads();
+    const uint32_t nbig = L.nbig;
+    if (nbig > kIxBigList) {
+        sort_recs(L.rec, m);
+    } else {
+        for (uint32_t j = 0; j < nbig; ++j) {  // uniform loop
+            const uint32_t a = slot16(L.slot, L.big[j]);
+            sort_recs(L.rec + a, slot16(L.slot, L.big[j] + 1) - a);
+        }
+    }
+    for (uint32_t p = tid; p < m; p += NT) {
+        const R v = L.rec[p];
+        uint32_t at = p;
+        const uint32_t b = rec_slot(B, v, b0) - c0, a = slot16(L.slot, b), e = slot16(L.slot, b + 1);
+        if (e - a <= kIxSmallBucket && nbig <= kIxBigList) {
+            at = a;
+            for (uint32_t x = a; x < e; ++x) at += rec_less(L.rec[x], v);
+        }
+        put_entry(B, lo + at, v);
+    }
+}
+
+// A record of the placement, through a global (not flat) load.
+__device__ __forceinline__ uint2 load_rec(const uint2 *p) {
+    const uint64_t w = load_global(reinterpret_cast<const uint64_t *>(p));
+    return uint2{static_cast<uint32_t>(w), static_cast<uint32_t>(w >> 32)};
+}
+__device__ __forceinline__ uint4 load_rec(const uint4 *p) { return *p; }
+
+// Slots [c, end) of a bin: end the largest so that their entries fit LDS, or c + 1 (start[x]: entries before
+// slot x of nslot, n in all).
+__device__ __forceinline__ uint32_t part_end(const uint32_t *start, uint32_t c, uint32_t nslot, uint32_t n, uint32_t cap) {
+    uint32_t l = c + 1, h = nslot;
+    while (l < h) {
+        const uint32_t mid = (l + h + 1) >> 1;
+        if ((mid < nslot ? start[mid] : n) - start[c] <= cap) l = mid;
+        else h = mid - 1;
+    }
+    return l;
+}
+
+// A bin past LDS: its slots are counted (32-bit counters over the record array) and it goes through LDS in
+// ranges of slots that fit, each picked out of the whole bin; only a single slot past LDS (equal k-mers in
+// more genes than LDS holds) is sorted in place in global memory.
+template <typename R>
+__device__ __forceinline__ void bin_in_parts(const DevBuild &B, const R *tmp, uint32_t n, uint32_t lo, uint32_t b0, uint32_t nbb,
+                                             BinLds<R> &L) {
+    using S = BinSort<R>;
+    constexpr uint32_t NT = S::kThreads, kPerScan = S::kSlots / NT;
+    static_assert(S::kSlots * sizeof(uint32_t) <= sizeof(L.rec), "the counters fit the record array");
+    const uint32_t tid = threadIdx.x, nslot = nbb << B.xb;
+    uint32_t *start = reinterpret_cast<uint32_t *>(L.rec);
+    for (uint32_t from = 0; from < nslot;) {  // kIxCuts parts at a time; uniform
+        for (uint32_t i = tid; i < S::kSlots; i += NT) start[i] = 0;
+        __syncthreads();
+        for (uint32_t i = tid; i < n; i += NT) atomicAdd(&start[rec_slot(B, load_rec(tmp + i), b0)], 1u);
+        __syncthreads();
+        uint32_t c[kPerScan], sum = 0, total;
+#pragma unroll
+        for (uint32_t q = 0; q < kPerScan; ++q) {
+            c[q] = start[tid * kPerScan + q];
+            sum += c[q];
+        }
+        uint32_t run = block_exclusive_scan<NT>(sum, L.tmp, &total);  // contains barriers
+#pragma unroll
+        for (uint32_t q = 0; q < kPerScan; ++q) {
+            start[tid * kPerScan + q] = run;
+            run += c[q];
+        }
+        __syncthreads();
+        if (from == 0)
+            for (uint32_t b = tid; b < nbb; b += NT) store_global(B.ix_dir + b0 + b, lo + start[b << B.xb]);
+        if (tid == 0) {
+            uint32_t k = 0, x = from;
+            for (; k < kIxCuts && x < nslot; ++k) {
+                L.cut[k] = x;
+                L.pos[k] = start[x];
+                x = part_end(start, x, nslot, n, S::kLds);
+            }
+            L.cut[k] = x;
+            L.pos[k] = x < nslot ? start[x] : n;
+            L.ncuts = k;
+        }
+        __syncthreads();
+        const uint32_t ncuts = L.ncuts;
+        for (uint32_t k = 0; k < ncuts; ++k) {
+            const uint32_t c0 = L.cut[k], c1 = L.cut[k + 1], at0 = lo + L.pos[k], m = L.pos[k + 1] - L.pos[k];
+            const bool fits = m <= S::kLds;  // uniform
+            if (m == 0) continue;
+            __syncthreads();  // the record array is read before it takes the part
+            if (tid == 0) {
+                L.n = 0;
+                L.nbig = 0;
+            }
+            for (uint32_t i = tid; i <= S::kSlots / 2; i += NT) L.slot[i] = 0;
+            __syncthreads();
+            for (uint32_t i0 = 0; i0 < n; i0 += NT) {
+                R v{};
+                bool in = i0 + tid < n;
+                if (in) {
+                    v = load_rec(tmp + i0 + tid);
+                    const uint32_t x = rec_slot(B, v, b0);
+                    in = x >= c0 && x < c1;
+                }
+                const uint64_t mask = __ballot(in);
+                uint32_t at = 0;
+                if (lane_id() == 0 && mask) at = atomicAdd(&L.n, static_cast<uint32_t>(__popcll(mask)));
+                at = __shfl(at, 0, kWave) + mask_below(mask);
+                if (!in) continue;
+                if (fits) {
+                    L.rec[at] = v;
+                } else {
+                    B.ix_code[at0 + at] = rec_code5(B, v);
+                    B.ix_gene[at0 + at] = rec_gene(v);
+                    B.ix_cnt[at0 + at] = rec_cnt(v);
+                }
+            }
+            __syncthreads();
+            if (fits) {
+                R r[S::kPer];
+#pragma unroll
+                for (uint32_t q = 0; q < S::kPer; ++q) {
+                    const uint32_t i = q * NT + tid;
+                    r[q] = i < m ? L.rec[i] : R{};
+                }
+                __syncthreads();
+                bin_part<R>(B, r, m, b0, c0, at0, L);
+            } else {
+                sort_entries(B.ix_code + at0, B.ix_gene + at0, B.ix_cnt + at0, m);
+                if (B.key_shift)
+                    for (uint32_t i = tid; i < m; i += NT)
+                        B.ix_key[at0 + i] = entry_key(B, B.ix_code[at0 + i], B.ix_gene[at0 + i]);
+            }
+        }
+        from = L.cut[ncuts];
+        __syncthreads();
+    }
+}
+
+// One work-group per coarse bin: its entries ordered by (code, gene) and the bin's part of
+// the bucket directory.  Usual case: the bin fits LDS and its slots fit kSlots (bin_part, whose slot
+// starts at the first slot of every bucket are the directory).  Letters are not used evenly, so some bins
+// of large builds do not fit (bin_in_parts).  A bin of too many slots (tiny genomes) is sorted in LDS, or in
+// place in global memory when it does not fit either.
+// Bins of 1350 to 2700 8-byte records on average (50 genomes of 3000 to 5000 genes: 2176): sort 0.44 ms,
+// placement 0.30 ms (0.45 before its records were staged).  With half of that 0.56 and 0.55 ms, with a
+// quarter 0.87 and 0.70 ms, unstaged: the placement's runs per (block, bin) get shorter and the work-groups
+// emptier.
+template <typename R>
+__global__ __launch_bounds__(BinSort<R>::kThreads, BinSort<R>::kWavesPerSimd) void k_ix_sort_bin(const DevBuild *__restrict__ table,
                                                                       uint32_t n_genomes,
                                                                       const uint32_t *__restrict__ off) {
     using S = BinSort<R>;
     constexpr uint32_t NT = S::kThreads, kIxPer = S::kPer;
-    __shared__ R s_rec[S::kLds];
-    __shared__ uint32_t s_slot[S::kSlots / 2 + 1];  // two 16-bit counters, then starts, per word
-    __shared__ uint32_t s_big[kIxBigList];
-    __shared__ uint32_t s_tmp[NT / kWave + 1];
-    __shared__ uint32_t s_nbig;
+    __shared__ BinLds<R> L;
     const uint32_t tid = threadIdx.x;
     const DevBuild &B = table[find_genome_by_bin(table, n_genomes, blockIdx.x)];
     const uint32_t h = blockIdx.x - B.bin_base;
@@ -1088,88 +1282,31 @@ __global__ __launch_bounds__(BinSort<R>::kThreads) void k_ix_sort_bin(const DevB
     const uint32_t b1 = min(B.nb, (h + 1) << B.hshift);
     const uint32_t nbb = b1 - b0;
     const uint32_t nslot = nbb << B.xb;
-    const R *tmp = reinterpret_cast<const R *>(B.ix_tmp);  // the placement wrote R records
+    const R *tmp = reinterpret_cast<const R *>(B.ix_tmp) + lo;  // the placement wrote R records
     if (n <= S::kLds && nslot <= S::kSlots) {
-        for (uint32_t i = tid; i <= S::kSlots / 2; i += NT) s_slot[i] = 0;
-        if (tid == 0) s_nbig = 0;
+        for (uint32_t i = tid; i <= S::kSlots / 2; i += NT) L.slot[i] = 0;
+        if (tid == 0) L.nbig = 0;
         R r[kIxPer];
-        uint32_t rank[kIxPer], bk[kIxPer];
 #pragma unroll
         for (uint32_t q = 0; q < kIxPer; ++q) {  // every load issued before the first atomic
             const uint32_t i = q * NT + tid;
-            if constexpr (sizeof(R) == 8) {  // one 64-bit word, through a global (not flat) load
-                const uint64_t w = i < n ? load_global(reinterpret_cast<const uint64_t *>(tmp) + lo + i) : 0ull;
-                r[q] = R{static_cast<uint32_t>(w), static_cast<uint32_t>(w >> 32)};
-            } else {
-                r[q] = i < n ? tmp[lo + i] : R{};
-            }
+            r[q] = i < n ? load_rec(tmp + i) : R{};
         }
         __syncthreads();
-#pragma unroll
-        for (uint32_t q = 0; q < kIxPer; ++q) {
-            if (q * NT + tid >= n) continue;
-            const uint32_t b = rec_slot(B, r[q], b0), sh = (b & 1u) * 16u;
-            bk[q] = b;
-            rank[q] = (atomicAdd(&s_slot[b >> 1], 1u << sh) >> sh) & 0xFFFFu;
-        }
-        __syncthreads();
-        {  // exclusive scan of the slot sizes
-            uint32_t w[S::kWords], sum = 0;
-#pragma unroll
-            for (uint32_t q = 0; q < S::kWords; ++q) {
-                w[q] = s_slot[tid * S::kWords + q];
-                sum += (w[q] & 0xFFFFu) + (w[q] >> 16);
-            }
-            uint32_t total;
-            uint32_t run = block_exclusive_scan<NT>(sum, s_tmp, &total);
-#pragma unroll
-            for (uint32_t q = 0; q < S::kWords; ++q) {
-                const uint32_t b = (tid * S::kWords + q) * 2, c0 = w[q] & 0xFFFFu, c1 = w[q] >> 16;
-                s_slot[tid * S::kWords + q] = run | ((run + c0) << 16);
-                run += c0 + c1;
-                for (uint32_t x = 0; x < 2; ++x)
-                    if ((x ? c1 : c0) > kIxSmallBucket) {
-                        const uint32_t idx = atomicAdd(&s_nbig, 1u);
-                        if (idx < kIxBigList) s_big[idx] = b + x;
-                    }
-            }
-            if (tid == 0) s_slot[S::kSlots / 2] = n;
-        }
-        __syncthreads();
-#pragma unroll
-        for (uint32_t q = 0; q < kIxPer; ++q)
-            if (q * NT + tid < n) s_rec[slot16(s_slot, bk[q]) + rank[q]] = r[q];
-        for (uint32_t b = tid; b < nbb; b += NT) store_global(B.ix_dir + b0 + b, lo + slot16(s_slot, b << B.xb));
-        __syncthreads();
-        const uint32_t nbig = s_nbig;
-        if (nbig > kIxBigList) {
-            sort_recs(s_rec, n);
-        } else {
-            for (uint32_t j = 0; j < nbig; ++j) {  // uniform loop
-                const uint32_t a = slot16(s_slot, s_big[j]);
-                sort_recs(s_rec + a, slot16(s_slot, s_big[j] + 1) - a);
-            }
-        }
-        for (uint32_t p = tid; p < n; p += NT) {
-            const R v = s_rec[p];
-            uint32_t at = p;
-            const uint32_t b = rec_slot(B, v, b0), a = slot16(s_slot, b), e = slot16(s_slot, b + 1);
-            if (e - a <= kIxSmallBucket && nbig <= kIxBigList) {
-                at = a;
-                for (uint32_t x = a; x < e; ++x) at += rec_less(s_rec[x], v);
-            }
-            put_entry(B, lo + at, v);
-        }
+        bin_part<R>(B, r, n, b0, 0, lo, L);
+        for (uint32_t b = tid; b < nbb; b += NT) store_global(B.ix_dir + b0 + b, lo + slot16(L.slot, b << B.xb));
     } else if (n <= S::kLds) {
-        for (uint32_t i = tid; i < n; i += NT) s_rec[i] = tmp[lo + i];
+        for (uint32_t i = tid; i < n; i += NT) L.rec[i] = tmp[i];
         __syncthreads();
-        sort_recs(s_rec, n);
-        for (uint32_t i = tid; i < n; i += NT) put_entry(B, lo + i, s_rec[i]);
+        sort_recs(L.rec, n);
+        for (uint32_t i = tid; i < n; i += NT) put_entry(B, lo + i, L.rec[i]);
         __syncthreads();
         bin_directory(B, B.ix_code + lo, n, lo, b0, b1);
+    } else if (nslot <= S::kSlots) {
+        bin_in_parts<R>(B, tmp, n, lo, b0, nbb, L);
     } else {
         for (uint32_t i = tid; i < n; i += NT) {
-            const R v = tmp[lo + i];
+            const R v = tmp[i];
             B.ix_code[lo + i] = rec_code5(B, v);
             B.ix_gene[lo + i] = rec_gene(v);
             B.ix_cnt[lo + i] = rec_cnt(v);

@@ -1,0 +1,79 @@
+"""GPU parity of the dictionary build where the index partition is uneven: genomes of a few letters, or of
+letters as often as in proteins, whose bins do not fit LDS (few parts, more parts than are laid out at a
+time, single slots past LDS), and bins as many as the staged placement takes and more.  Every array is
+compared with the oracle's."""
+import statistics
+
+import numpy as np
+import pytest
+
+import oracle
+from helpers import check_dictionary
+from synth import genome_from_strings
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - CPU collection
+    pytest.skip("needs the GPU", allow_module_level=True)
+
+import paper_2510_23679_amd as pdp  # noqa: E402
+
+AA = "ACDEFGHIKLMNPQRSTVWY"
+# letters as often as in an average protein, in tenths of a percent
+PROTEIN = [83, 14, 55, 67, 39, 71, 23, 59, 58, 97, 24, 41, 47, 39, 55, 67, 54, 69, 11, 29]
+
+
+def _genome(seed, genes, length, letters, weights=None, alphabet="aa", head=""):
+    rng = np.random.default_rng(seed)
+    p = None if weights is None else np.asarray(weights) / np.sum(weights)
+    x = np.frombuffer(letters.encode(), np.uint8)[rng.choice(len(letters), (genes, length), p=p)]
+    if head:
+        x[:, :len(head)] = np.frombuffer(head.encode(), np.uint8)
+    g = genome_from_strings(["A"], alphabet=alphabet)
+    g.residues, g.offsets = x.reshape(-1).copy(), np.arange(genes + 1, dtype=np.uint64) * np.uint64(length)
+    return g
+
+
+CASES = {
+    "protein letters, 8-byte records": (lambda: _genome(1, 4300, 500, AA, PROTEIN), 6),
+    "protein letters, base-20 keys": (lambda: _genome(2, 4300, 500, AA, PROTEIN), 7),
+    "protein letters, 16-byte records": (lambda: _genome(3, 4300, 500, AA, PROTEIN), 8),
+    "four letters: more parts than one layout": (lambda: _genome(4, 6000, 400, "ACDE"), 6),
+    "four letters, 16-byte records": (lambda: _genome(5, 2000, 400, "ACDE"), 9),
+    "slots past LDS": (lambda: _genome(6, 9000, 250, AA, PROTEIN, head="WWWWWWWWWW"), 6),
+    "slots past LDS, 16-byte records": (lambda: _genome(7, 9000, 250, AA, PROTEIN, head="WWWWWWWWWWWW"), 9),
+    "5000 bins, staged placement": (lambda: _genome(8, 13600, 500, AA), 6),
+    "8192 bins, placement without staging": (lambda: _genome(9, 11200, 1000, "ACGT", alphabet="nt"), 13),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_uneven_bins(name):
+    make, k = CASES[name]
+    genome = make()
+    print("[case]", name, "genes", genome.n_genes, "letters", genome.n_residues, "k", k, flush=True)
+    d = pdp.Dictionary.build_from(genome, k)
+    d.check_status()
+    check_dictionary(d.host(), oracle.OracleGenome(genome, k))
+
+
+def _build_us(weights):
+    batch = pdp.DictionaryBatch([pdp.DeviceGenome.of(_genome(20 + i, 4900, 340, AA, weights)) for i in range(10)], 6)
+    batch.build()
+    times = []
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        batch.build()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(1e3 * a.elapsed_time(b))
+    return statistics.median(times)
+
+
+def test_protein_letters_do_not_slow_the_build_down():
+    # the bins past LDS, sorted in global memory, made this build four times as long as that of even letters
+    even, protein = _build_us(None), _build_us(PROTEIN)
+    print("[case] build", even, protein, "us", flush=True)
+    assert protein < 2 * even
