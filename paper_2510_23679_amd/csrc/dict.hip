@@ -1332,15 +1332,20 @@ static uint32_t bin_shift(uint32_t nb, uint64_t cap, uint32_t target) {
 
 // Bin shift s and sub-slot bits xb of one genome: a bin's counting sort goes by bucket and,
 // where the slots still fit, the next letter (amino acids, 5 bits) or two (nucleotides, 4 bits), so
-// that a slot holds about one entry.
+// that a slot holds about one entry.  Bins above kIxBinTargetWide entries are halved for these slots to fit
+// where buckets alone hold over two entries on average, and far more of the frequent letters (2000 genes
+// with the letters of proteins: 221 us by buckets, 113 so, even letters 117 and 109; six genomes of 1000
+// genes: 185 and 169, even letters 152 and 167; below, of 700 genes: 144 and 157, 141 and 157).
 struct BinPlan {
     uint32_t s, xb;
 };
 static BinPlan bin_plan(uint32_t nb, uint64_t cap, uint32_t k, uint32_t alphabet, uint32_t target, uint32_t slots) {
     const AlphaSpec a = alpha_spec(alphabet);
-    const uint32_t s = bin_shift(nb, cap, target);
+    uint32_t s = bin_shift(nb, cap, target);
+    const uint32_t least = bin_shift(nb, cap, kIxBinTargetWide);  // the most bins the workspace holds
     const uint32_t rest = k - lead_letters(k, alphabet);
     uint32_t xb = a.bits * std::min<uint32_t>(rest, a.bits == 2 ? 2u : 1u);
+    while (xb && s > least && cap > 2ull * nb && (1ull << (s + xb)) > slots) --s;
     while (xb && (1ull << (s + xb)) > slots) xb -= a.bits;
     return {s, xb};
 }
@@ -1427,10 +1432,11 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
         narrow_rec &= g[i].n_genes <= 65536 && !(d[i]->flags & PDP_DICT_LONG_GENES);
     }
     narrow_rec &= narrow;
-    // entries per placement block and per bin: large ones give each (block, bin) a longer run; where
-    // the chip is not filled, small blocks and bins (one genome of 1503 genes: histogram
-    // 13 -> 8 us, placement 16 -> 14 us with blocks of 2048 instead of 16384)
-    const bool small = sh.total_residues <= 512ull * kIxBlock / 4;
+    // entries per placement block and per bin: large ones give each (block, bin) a longer run; builds
+    // that leave the chip mostly idle take small blocks and bins.  One genome, small against large: 340,000
+    // letters (1000 genes) 92 / 98 us, 510,000 108 / 104, 680,000 136 / 112, 1.46 million 227 / 132; k = 8
+    // 111 / 119, 135 / 131, 157 / 141, 259 / 184; nucleotides 119 / 127, 130 / 129, 157 / 134, 260 / 182.
+    const bool small = sh.total_residues <= 32ull * kIxBlock;
     const uint32_t blk = small ? kIxBlockSmall : kIxBlock;
     const uint32_t target = narrow_rec && !small ? kIxBinTarget : kIxBinTargetWide;
     const uint32_t slots = narrow_rec ? BinSort<uint2>::kSlots : BinSort<uint4>::kSlots;

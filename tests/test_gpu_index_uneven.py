@@ -77,3 +77,52 @@ def test_protein_letters_do_not_slow_the_build_down():
     even, protein = _build_us(None), _build_us(PROTEIN)
     print("[case] build", even, protein, "us", flush=True)
     assert protein < 2 * even
+
+
+@pytest.mark.parametrize("k", [6, 7, 8])
+@pytest.mark.parametrize("letters", [524287, 524288])
+def test_around_the_small_builds(letters, k):
+    # a build's letters and one entry per genome: up to 32 blocks of 16384 take the small forms
+    genome = _genome(30, 1, letters % 1000 or 1000, AA, PROTEIN)
+    rest = _genome(31, letters // 1000, 1000, AA, PROTEIN)
+    genome.residues = np.concatenate([rest.residues, genome.residues])[:letters]
+    genome.offsets = np.append(rest.offsets, np.uint64(letters)) if letters % 1000 else rest.offsets
+    print("[case] small builds,", letters, "letters, k", k, flush=True)
+    d = pdp.Dictionary.build_from(genome, k)
+    d.check_status()
+    check_dictionary(d.host(), oracle.OracleGenome(genome, k))
+
+
+def test_around_two_entries_a_bucket():
+    # 160000 buckets: genomes of 319,998 to 320,004 letters beside one that makes the build large
+    genomes = [_genome(32 + i, 2, 159999 + i, "ACDEFGHIKL") for i in range(4)]
+    for g in genomes:  # genes of ordinary length
+        n = g.n_residues
+        g.offsets = np.append(np.arange(0, n, 400, dtype=np.uint64), np.uint64(n))
+    genomes.append(_genome(40, 1000, 500, AA))
+    print("[case] two entries a bucket", [g.n_residues for g in genomes], flush=True)
+    batch = pdp.DictionaryBatch([pdp.DeviceGenome.of(g) for g in genomes], 6)
+    batch.build()
+    batch.check_status()
+    for d, g in zip(batch.dicts, genomes):
+        check_dictionary(d.host(), oracle.OracleGenome(g, 6))
+
+
+def test_a_genome_of_ordinary_size_takes_the_large_forms():
+    # with small blocks and bins 1.46 million letters took 2.5 times as long as 0.34 million, with large ones 1.4
+    def build(genes):
+        batch = pdp.DictionaryBatch([pdp.DeviceGenome.of(_genome(50, genes, 340, AA))], 6)
+        batch.build()
+        times = []
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            batch.build()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(1e3 * a.elapsed_time(b))
+        return statistics.median(times)
+
+    few, many = build(1000), build(4300)
+    print("[case] build", few, many, "us", flush=True)
+    assert many < 1.9 * few
