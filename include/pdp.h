@@ -320,8 +320,12 @@ typedef struct pdp_plan_info {
  * of dictionaries (a group, e.g. all pairs of eight genomes or more) are joined
  * together: their shared k-mers are found in one pass over the group's indexes
  * and kept with bounds known from the dictionaries, both directions of a task
- * come from one (column maxima, whose candidates share the record capacity),
- * and join_groups and tiles count the group's items and tiles.  A plan with
+ * come from one (column maxima), and join_groups and tiles count the group's
+ * items and tiles.  What a group has to fit into the record capacity is its
+ * hits from column maxima and from rows of more than four ties, at most its
+ * shared k-mers' records (with PDP_PARAM_COLMAX: twice the capacity, since a
+ * record then stands for a hit each way); their number, and needed, is the
+ * same in every launch.  A plan with
  * PDP_PARAM_PERSISTENT or PDP_PARAM_TWO_PASS joins every pair on its own.
  * Results are identical either way.  Host only.
  * Errors: PDP_E_INVAL (null, k or alphabet mismatch, BBH without AB|BA), PDP_E_LIMIT. */

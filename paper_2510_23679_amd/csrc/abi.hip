@@ -510,7 +510,6 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         }
     if (prm.flags & ~(PDP_PARAM_PERSISTENT | PDP_PARAM_COLMAX | PDP_PARAM_TWO_PASS))
         return fail(PDP_E_INVAL, "unknown parameter flags 0x%x", prm.flags);
-    bool any_colmax = false;
     if (prm.theta_den && prm.theta_num > prm.theta_den) return fail(PDP_E_INVAL, "theta above 1");
     const bool filt = prm.theta_den || prm.tau_den;
 
@@ -566,7 +565,6 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         // column maxima: b's best hits from the AB tiles' columns, records for one direction
         const bool colmax =
             !long_task && (prm.flags & PDP_PARAM_COLMAX) && (flags & PDP_TASK_AB) && (flags & PDP_TASK_BA);
-        any_colmax |= colmax;
         d.flags = (colmax ? (dflags & ~PDP_TASK_BA) | kTaskColmax : dflags) | (swap ? kTaskSwapped : 0u);
         d.theta_n = prm.theta_num;
         d.theta_d = prm.theta_den;
@@ -651,6 +649,8 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
     // Tasks of a group leave the pair path: no join items and no tiles of their own.
     std::memset(&P->shape, 0, sizeof(P->shape));
     std::vector<uint8_t> in_group(n_tasks, 0);
+    uint64_t group_est = 0;
+    bool pair_colmax = false;
     if (n_tasks >= 3 && !(prm.flags & (PDP_PARAM_PERSISTENT | PDP_PARAM_TWO_PASS))) {
         P->shape.gentries = plan_groups(P, tasks, n_tasks, is_long, in_group);
         for (uint32_t t = 0; t < n_tasks; ++t) {
@@ -663,16 +663,19 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             d.tiles_n[0] = d.tiles_n[1] = 0;
             d.row_base[0] = P->ab_row[t];
             d.row_base[1] = P->ba_row[t];
-            any_colmax = true;
-            // no records, but candidates (16 bytes for a record's 8): pairs at a column's running
-            // maximum, at most the pairs that share anything, so half of one direction's estimate
-            // holds some forty a gene and keeps the scratch at the pair path's size (50 genomes of
-            // 4000 genes: 5.4 GB, 7.6 by pairs)
-            task_est[t] = direction_estimate(tasks[t]) / 2;
+            group_est += direction_estimate(tasks[t]);
         }
     }
-    uint64_t rec_est = 0;
-    for (uint64_t e : task_est) rec_est += e;
+    // The group path keeps no records; its hits (best hits from column maxima, and ties of rows past the
+    // slab) count against the capacity instead: each belongs to a pair of genes that share a k-mer,
+    // of which the pair path keeps a record per direction at least, or, with PDP_PARAM_COLMAX, one for
+    // at most two hits.  So what fits by pairs fits here.
+    uint64_t rec_est = 0, pair_est = 0;
+    for (uint32_t t = 0; t < n_tasks; ++t) {
+        rec_est += task_est[t];
+        if (!in_group[t]) pair_est += task_est[t];
+        pair_colmax |= !in_group[t] && (caller[t].flags & kTaskColmax) != 0;
+    }
     // Pass 2, largest tasks first: join items and tiles are numbered in this order, so work-groups
     // (and the persistent kernels' counters) take the long items early.
     // each tile's expected records, the estimate rec_est sums: a region of the one-pass join each
@@ -785,7 +788,8 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
     P->shape.bh_rows = static_cast<uint32_t>(bh_rows);
     P->shape.bbh_rows = static_cast<uint32_t>(bbh_rows);
     P->shape.tile_lds = static_cast<uint32_t>(align_up(tile_lds, 16));
-    P->shape.rec_cap = prm.inc_capacity ? prm.inc_capacity : std::min<uint64_t>(rec_est, UINT32_MAX);
+    P->shape.inc_cap = prm.inc_capacity ? prm.inc_capacity : std::min<uint64_t>(rec_est, UINT32_MAX);
+    P->shape.rec_cap = prm.inc_capacity ? prm.inc_capacity : std::min<uint64_t>(pair_est, UINT32_MAX);
     P->shape.fused = (prm.flags & PDP_PARAM_TWO_PASS) ? 0u : 1u;
     P->shape.join_tiles = join_tiles;
     P->shape.fallback_grid = 0;
@@ -804,8 +808,16 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
     }
     P->shape.join_grid = 0;
     P->shape.tile_grid = 0;
-    P->shape.colmax = any_colmax ? 1u : 0u;
-    P->shape.cand_cap = any_colmax ? P->shape.rec_cap : 0;
+    P->shape.colmax = pair_colmax || P->shape.n_gdicts ? 1u : 0u;
+    P->shape.cand_cap = pair_colmax ? P->shape.rec_cap : 0;
+    if (P->shape.n_gdicts) {
+        // listed candidates (16 bytes): pairs at a column's running maximum, whose number depends on the order
+        // of the tiles; half of one direction's estimate holds some forty a gene and keeps the scratch
+        // at the pair path's size (50 genomes of 4000 genes: 5.4 GB, 7.6 by pairs).  Past them the tiles are
+        // replayed against the final maxima, and the hits themselves have to fit.
+        P->shape.ghit_cap = P->shape.inc_cap * ((prm.flags & PDP_PARAM_COLMAX) ? 2 : 1);
+        P->shape.gcand_cap = std::min<uint64_t>({P->shape.ghit_cap, std::max<uint64_t>(group_est / 2, 1), INT32_MAX});
+    }
     P->shape.n_long_segs = static_cast<uint32_t>(P->long_segs.size());
     P->shape.long_rows = static_cast<uint32_t>(long_rows);  // at most the best-hit rows, below 2^32
     P->shape.long_lds = (filt ? 3u : 1u) * kLongCols * 4u;
@@ -855,7 +867,7 @@ extern "C" {
 int32_t pdp_plan_info_get(const pdp_plan *plan, pdp_plan_info *info) {
     if (!plan || !info) return fail(PDP_E_INVAL, "pdp_plan_info_get: null pointer");
     info->ws_bytes = plan->ws_bytes;
-    info->inc_capacity = plan->shape.rec_cap;
+    info->inc_capacity = plan->shape.inc_cap;
     info->bh_rows = plan->shape.bh_rows;
     info->bbh_rows = plan->shape.bbh_rows;
     info->n_tasks = plan->shape.n_tasks;

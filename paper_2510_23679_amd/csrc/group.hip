@@ -585,7 +585,16 @@ struct GtLds {
     uint8_t tmap[kGroupMaxDicts + 1];         // group dictionary -> target, 255: none
     uint8_t vr[kGroupTileRows], vt[kGroupTileRows];  // gene and target of each row
     uint8_t mark[NT / kWave][kWave];                 // gt_walk
-    uint32_t over, cand_n, cand_base, many;
+    unsigned long long cand_base;
+    uint32_t over, cand_n, many;
+};
+
+// Column maxima of the group's tiles (see ColWs; their candidates may number more than 32 bits hold).
+struct GtCols {
+    unsigned long long *key;
+    uint4 *cands;
+    unsigned long long *count;
+    uint64_t cap;
 };
 
 // A tile's descriptors: [d0, d0 + nd) with postings, [i0, i0 + ni) inline.
@@ -674,18 +683,30 @@ __device__ __forceinline__ void gt_walk(const GtList &T, uint32_t g0, uint32_t g
 }
 
 // One (gene, target) row with more columns than the table holds: its sums in direct-addressed
-// blocks of column genes, each swept for the maximum, then for the ties.
+// blocks of column genes.
 template <typename SH>
-__device__ void gt_dense_row(uint32_t v, const GtList &T, uint32_t n_tgt, uint32_t row0, const CandFilter &cf, uint32_t *lds,
-                             GtLds<SH::NT> &S, uint32_t *__restrict__ bh_ptr, uint4 *__restrict__ slab, const ColWs &cmx) {
-    constexpr bool FILT = SH::kFilt;
-    constexpr uint32_t NT = SH::NT, kCols = SH::kWords / (FILT ? 3 : 1);  // columns per block (FILT: three arrays)
-    uint32_t *acc = lds, *asr = lds + kCols, *asc = lds + 2 * kCols;
-    const uint32_t g = v / n_tgt, t = v % n_tgt, ncols = S.tn[t], nr = S.nr[g];
-    const uint32_t grow = S.trow[t] + row0 + g, col = S.tcol[t];
-    const uint32_t *cw = S.tw[t];
-    const uint32_t nblk = (ncols + kCols - 1) / kCols;
-    auto fill = [&](uint32_t c0) {
+struct GtDense {
+    static constexpr bool FILT = SH::kFilt;
+    static constexpr uint32_t NT = SH::NT, kCols = SH::kWords / (FILT ? 3 : 1);  // columns per block (FILT: three arrays)
+    const GtList &T;
+    const CandFilter &cf;
+    uint32_t *acc;
+    GtLds<SH::NT> &S;
+    uint32_t g, t, ncols, nr, nblk;
+    const uint32_t *cw;
+
+    __device__ __forceinline__ GtDense(uint32_t v, const GtList &T_, uint32_t n_tgt, const CandFilter &cf_, uint32_t *lds,
+                                       GtLds<SH::NT> &S_)
+        : T(T_), cf(cf_), acc(lds), S(S_) {
+        g = v / n_tgt;
+        t = v % n_tgt;
+        ncols = S.tn[t];
+        nr = S.nr[g];
+        cw = S.tw[t];
+        nblk = (ncols + kCols - 1) / kCols;
+    }
+    // The sums of columns c0 on; S.over stays zero.  Contains barriers.
+    __device__ __forceinline__ void fill(uint32_t c0) {
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < (FILT ? 3 : 1) * kCols; i += NT) acc[i] = 0;
         if (threadIdx.x == 0) S.many = 0;
@@ -694,37 +715,48 @@ __device__ void gt_dense_row(uint32_t v, const GtList &T, uint32_t n_tgt, uint32
             if (S.tmap[x] != t || c - c0 >= kCols) return;
             atomicAdd(&acc[c - c0], min(rc, pc));
             if (FILT) {
-                atomicAdd(&asr[c - c0], rc);
-                atomicAdd(&asc[c - c0], pc);
+                atomicAdd(&acc[kCols + c - c0], rc);
+                atomicAdd(&acc[2 * kCols + c - c0], pc);
             }
         });
         __syncthreads();
-    };
-    auto value = [&](uint32_t c0, uint32_t i, uint32_t *m, uint32_t *d) {
+    }
+    // Sum of minima (0: no candidate) and of maxima of column c0 + i.
+    __device__ __forceinline__ void value(uint32_t c0, uint32_t i, uint32_t *m, uint32_t *d) const {
         *m = c0 + i < ncols ? acc[i] : 0u;
         *d = 0;
         if (!*m) return;
         const uint32_t nc = load_global(cw + c0 + i);
-        if (FILT && !candidate(cf, nr, nc, asr[i], asc[i])) {
+        if (FILT && !candidate(cf, nr, nc, acc[kCols + i], acc[2 * kCols + i])) {
             *m = 0;
             return;
         }
         *d = nr + nc - *m;
-    };
+    }
+};
+
+// Such a row, each block swept for the maximum, then for the ties.
+template <typename SH>
+__device__ void gt_dense_row(uint32_t v, const GtList &T, uint32_t n_tgt, uint32_t row0, const CandFilter &cf, uint32_t *lds,
+                             GtLds<SH::NT> &S, uint32_t *__restrict__ bh_ptr, uint4 *__restrict__ slab, const GtCols &cmx) {
+    using Dense = GtDense<SH>;
+    constexpr uint32_t NT = SH::NT, kCols = Dense::kCols;
+    Dense D(v, T, n_tgt, cf, lds, S);
+    const uint32_t grow = S.trow[D.t] + row0 + D.g, col = S.tcol[D.t], nblk = D.nblk;
     if (threadIdx.x == 0) {
         S.best[v] = 0;
         S.cand_n = 0;
         S.over = 0;
     }
     for (uint32_t b = 0; b < nblk; ++b) {
-        fill(b * kCols);
+        D.fill(b * kCols);
         for (uint32_t i = threadIdx.x; i < kCols; i += NT) {
             uint32_t m, d;
-            value(b * kCols, i, &m, &d);
+            D.value(b * kCols, i, &m, &d);
             if (!m) continue;
-            if (col != UINT32_MAX && colmax_raise(cmx, col + b * kCols + i, m, d)) {
-                const uint32_t idx = atomicAdd(cmx.count, 1u);
-                if (idx < cmx.cap) cmx.cands[idx] = make_uint4(col + b * kCols + i, row0 + g, m, d);
+            if (col != UINT32_MAX && colmax_raise(cmx.key, col + b * kCols + i, m, d)) {
+                const uint64_t idx = atomicAdd(cmx.count, 1ull);
+                if (idx < cmx.cap) cmx.cands[idx] = make_uint4(col + b * kCols + i, row0 + D.g, m, d);
             }
             const unsigned long long want = (static_cast<unsigned long long>(m) << 32) | d;
             unsigned long long cur = S.best[v];
@@ -743,16 +775,16 @@ __device__ void gt_dense_row(uint32_t v, const GtList &T, uint32_t n_tgt, uint32
         for (uint32_t pass = 0; pass < 2; ++pass) {  // ties to the slab, or all of them to the candidates
             if (pass && S.cand_n <= kSlab) break;   // uniform: read after a barrier
             for (uint32_t b = 0; b < nblk; ++b) {
-                if (nblk > 1) fill(b * kCols);  // a single block still holds its sums
+                if (nblk > 1) D.fill(b * kCols);  // a single block still holds its sums
                 for (uint32_t i = threadIdx.x; i < kCols; i += NT) {
                     uint32_t m, d;
-                    value(b * kCols, i, &m, &d);
+                    D.value(b * kCols, i, &m, &d);
                     if (!m || !j_equal(m, d, bm, bd)) continue;
                     if (!pass) {
                         const uint32_t n = atomicAdd(&S.cand_n, 1u);
                         if (n < kSlab) slab[static_cast<uint64_t>(grow) * kSlab + n] = make_uint4(b * kCols + i, m, d, 0);
                     } else {
-                        const uint32_t idx = atomicAdd(cmx.count, 1u);
+                        const uint64_t idx = atomicAdd(cmx.count, 1ull);
                         if (idx < cmx.cap) cmx.cands[idx] = make_uint4(grow, b * kCols + i, m, d);
                     }
                 }
@@ -768,11 +800,11 @@ __device__ void gt_dense_row(uint32_t v, const GtList &T, uint32_t n_tgt, uint32
     __syncthreads();
 }
 
-// Rows [v0, v1) summed in the hash table; false (uniform) when it is too small for them.
+// Rows [v0, v1) summed in the hash table, their best values and tie counts cleared; false (uniform) when
+// it is too small for them.
 template <typename SH>
-__device__ __forceinline__ bool gt_hashed(uint32_t v0, uint32_t v1, const GtList &T, uint32_t n_tgt,
-                                          uint32_t row0, const CandFilter &cf, uint32_t *lds, GtLds<SH::NT> &S,
-                                          uint32_t *__restrict__ bh_ptr, uint4 *__restrict__ slab, const ColWs &cmx) {
+__device__ __forceinline__ bool gt_sum(uint32_t v0, uint32_t v1, const GtList &T, uint32_t n_tgt, uint32_t *lds,
+                                       GtLds<SH::NT> &S) {
     constexpr bool FILT = SH::kFilt;
     constexpr uint32_t NT = SH::NT;
     uint32_t *hk = lds, *hv = lds + SH::kSlots, *hs = lds + 2 * SH::kSlots;
@@ -813,7 +845,19 @@ __device__ __forceinline__ bool gt_hashed(uint32_t v0, uint32_t v1, const GtList
     }
     if (tid == 0) S.many = 0;
     __syncthreads();  // every thread has read the flag before the next call clears it
-    if (over) return false;
+    return !over;
+}
+
+// Rows [v0, v1) through the hash table; false (uniform) when it is too small for them.
+template <typename SH>
+__device__ __forceinline__ bool gt_hashed(uint32_t v0, uint32_t v1, const GtList &T, uint32_t n_tgt,
+                                          uint32_t row0, const CandFilter &cf, uint32_t *lds, GtLds<SH::NT> &S,
+                                          uint32_t *__restrict__ bh_ptr, uint4 *__restrict__ slab, const GtCols &cmx) {
+    constexpr bool FILT = SH::kFilt;
+    constexpr uint32_t NT = SH::NT;
+    uint32_t *hk = lds, *hv = lds + SH::kSlots, *hs = lds + 2 * SH::kSlots;
+    const uint32_t tid = threadIdx.x;
+    if (!gt_sum<SH>(v0, v1, T, n_tgt, lds, S)) return false;
     uint32_t ncw[SH::kPer], app = 0;
 #pragma unroll
     for (uint32_t q = 0; q < SH::kPer; ++q) {  // the columns' window counts, gathered together
@@ -835,7 +879,7 @@ __device__ __forceinline__ bool gt_hashed(uint32_t v0, uint32_t v1, const GtList
         hv[sl] = m | (nc << 16);
         if (!m) continue;
         const uint32_t d = nr + nc - m, col = S.tcol[S.vt[v]];
-        if (col != UINT32_MAX && colmax_raise(cmx, col + ((key - 1) & 0xFFFFFFu), m, d)) app |= 1u << q;
+        if (col != UINT32_MAX && colmax_raise(cmx.key, col + ((key - 1) & 0xFFFFFFu), m, d)) app |= 1u << q;
         const unsigned long long want = (static_cast<unsigned long long>(m) << 32) | d;
         unsigned long long cur = S.best[v];
         for (;;) {
@@ -882,7 +926,7 @@ __device__ __forceinline__ bool gt_hashed(uint32_t v0, uint32_t v1, const GtList
     const uint32_t mine = __popc(app) + __popc(big);
     uint32_t off = mine ? atomicAdd(&S.cand_n, mine) : 0u;
     __syncthreads();
-    if (tid == 0 && S.cand_n) S.cand_base = atomicAdd(cmx.count, S.cand_n);
+    if (tid == 0 && S.cand_n) S.cand_base = atomicAdd(cmx.count, static_cast<unsigned long long>(S.cand_n));
     __syncthreads();
     if (mine) {
 #pragma unroll
@@ -892,11 +936,11 @@ __device__ __forceinline__ bool gt_hashed(uint32_t v0, uint32_t v1, const GtList
             const uint32_t key = hk[sl], c = (key - 1) & 0xFFFFFFu, v = (key - 1) >> 24, m = hv[sl] & 0xFFFFu;
             const uint32_t g = S.vr[v], t = S.vt[v], d = S.nr[g] + (hv[sl] >> 16) - m;
             if ((app >> q) & 1u) {
-                const uint64_t idx = uint64_t(S.cand_base) + off++;
+                const uint64_t idx = S.cand_base + off++;
                 if (idx < cmx.cap) cmx.cands[idx] = make_uint4(S.tcol[t] + c, row0 + g, m, d);
             }
             if ((big >> q) & 1u) {
-                const uint64_t idx = uint64_t(S.cand_base) + off++;
+                const uint64_t idx = S.cand_base + off++;
                 if (idx < cmx.cap) cmx.cands[idx] = make_uint4(S.trow[t] + row0 + g, c, m, d);
             }
         }
@@ -919,23 +963,26 @@ struct GtArgs {
     CandFilter cf;
     uint32_t *__restrict__ bh_ptr;
     uint4 *__restrict__ slab;
-    ColWs cmx;
+    GtCols cmx;
     uint2 *__restrict__ big;       // tiles left to the big kernel: (tile, first row)
     uint32_t *__restrict__ n_big;
 };
 
-// One tile from its row v on (rows count (gene, target) pairs).  The small shape gives up on a tile whose
-// rows do not fit its table after one halving and lists what is left.
-template <typename SH, bool LAST>
-__device__ __forceinline__ void gt_tile(const GtArgs &A, uint32_t tile, uint32_t v, uint32_t *lds, GtLds<SH::NT> &S) {
-    constexpr uint32_t NT = SH::NT;
+// A tile: its descriptors, rows ((gene, target) pairs), targets per gene, first gene.
+struct GtTile {
+    GtList T;
+    uint32_t rows, n_tgt, g0;
+    CandFilter cf;
+};
+// Ends with a barrier.
+template <uint32_t NT>
+__device__ __forceinline__ GtTile gt_open(const GtArgs &A, uint32_t tile, GtLds<NT> &S) {
     const uint32_t tid = threadIdx.x;
     const DevGroupTile tl = A.tiles[tile];
     const DevGroupDict &d = A.dicts[tl.dict];
-    const uint32_t n_tgt = d.n_tgt, rows = tl.ng * n_tgt;
-    CandFilter cf = A.cf;
-    cf.k = d.k;
-    for (uint32_t t = tid; t < n_tgt; t += NT) {
+    GtTile R{GtList{A.desc, A.post, A.aux, A.gene_bits, 0, 0, 0, 0}, tl.ng * d.n_tgt, d.n_tgt, tl.g0, A.cf};
+    R.cf.k = d.k;
+    for (uint32_t t = tid; t < R.n_tgt; t += NT) {
         const DevGroupTgt g = A.tgts[d.tgt_base + t];
         S.tw[t] = g.nwin;
         S.tn[t] = g.n_genes;
@@ -944,35 +991,90 @@ __device__ __forceinline__ void gt_tile(const GtArgs &A, uint32_t tile, uint32_t
     }
     for (uint32_t x = tid; x < d.n_dicts; x += NT) S.tmap[x] = A.tmap[d.tmap_base + x];
     for (uint32_t g = tid; g < tl.ng; g += NT) S.nr[g] = load_global(d.nwin + tl.g0 + g);
-    for (uint32_t r = tid; r < rows; r += NT) {
-        S.vr[r] = static_cast<uint8_t>(r / n_tgt);
-        S.vt[r] = static_cast<uint8_t>(r % n_tgt);
+    for (uint32_t r = tid; r < R.rows; r += NT) {
+        S.vr[r] = static_cast<uint8_t>(r / R.n_tgt);
+        S.vt[r] = static_cast<uint8_t>(r % R.n_tgt);
     }
-    GtList T{A.desc, A.post, A.aux, A.gene_bits, 0, 0, 0, 0};
-    T.d0 = d.desc_base + load_global(d.mv_ptr + tl.g0);
-    T.nd = A.cursor[static_cast<uint64_t>(tile) * kGroupCursorStride] - T.d0;
-    T.i0 = A.cursor[static_cast<uint64_t>(tile) * kGroupCursorStride + 1];
-    T.ni = d.desc_base + load_global(d.mv_ptr + tl.g0 + tl.ng) - T.i0;
+    R.T.d0 = d.desc_base + load_global(d.mv_ptr + tl.g0);
+    R.T.nd = A.cursor[static_cast<uint64_t>(tile) * kGroupCursorStride] - R.T.d0;
+    R.T.i0 = A.cursor[static_cast<uint64_t>(tile) * kGroupCursorStride + 1];
+    R.T.ni = d.desc_base + load_global(d.mv_ptr + tl.g0 + tl.ng) - R.T.i0;
     __syncthreads();
-    if (T.nd + T.ni == 0) {  // the genes share no k-mer with any target
-        for (uint32_t r = tid; r < rows; r += NT) A.bh_ptr[S.trow[S.vt[r]] + tl.g0 + S.vr[r]] = 0;
+    return R;
+}
+
+// One tile from its row v on.  The small shape gives up on a tile whose rows do not fit its table after one
+// halving and lists what is left.
+template <typename SH, bool LAST>
+__device__ __forceinline__ void gt_tile(const GtArgs &A, uint32_t tile, uint32_t v, uint32_t *lds, GtLds<SH::NT> &S) {
+    const uint32_t tid = threadIdx.x;
+    const GtTile R = gt_open<SH::NT>(A, tile, S);
+    if (R.T.nd + R.T.ni == 0) {  // the genes share no k-mer with any target
+        for (uint32_t r = tid; r < R.rows; r += SH::NT) A.bh_ptr[S.trow[S.vt[r]] + R.g0 + S.vr[r]] = 0;
         return;
     }
-    uint32_t step = rows;
-    while (v < rows) {
-        const uint32_t v1 = min(rows, v + step);
-        if (gt_hashed<SH>(v, v1, T, n_tgt, tl.g0, cf, lds, S, A.bh_ptr, A.slab, A.cmx)) {
+    uint32_t step = R.rows;
+    while (v < R.rows) {
+        const uint32_t v1 = min(R.rows, v + step);
+        if (gt_hashed<SH>(v, v1, R.T, R.n_tgt, R.g0, R.cf, lds, S, A.bh_ptr, A.slab, A.cmx)) {
             v = v1;
-            if (LAST) step = min(2 * step, rows);  // a gene of many columns holds up its own rows only
-        } else if (!LAST && step < rows) {
+            if (LAST) step = min(2 * step, R.rows);  // a gene of many columns holds up its own rows only
+        } else if (!LAST && step < R.rows) {
             if (tid == 0) A.big[atomicAdd(A.n_big, 1u)] = make_uint2(tile, v);
             return;
         } else if (v1 - v > 1) {
             step = (v1 - v + 1) / 2;
         } else {
-            gt_dense_row<SH>(v, T, n_tgt, tl.g0, cf, lds, S, A.bh_ptr, A.slab, A.cmx);
+            gt_dense_row<SH>(v, R.T, R.n_tgt, R.g0, R.cf, lds, S, A.bh_ptr, A.slab, A.cmx);
             ++v;
         }
+    }
+}
+
+// Calls f(row, column, m, d) for every pair of a tile whose value is the final maximum of its column's
+// best-hit row (column maxima) or of its own row (rows with ties past the slab, whose key is set).
+template <typename SH, typename F>
+__device__ __forceinline__ void gt_replay(const GtArgs &A, uint32_t tile, uint32_t *lds, GtLds<SH::NT> &S, F f) {
+    using Dense = GtDense<SH>;
+    const GtTile R = gt_open<SH::NT>(A, tile, S);
+    if (R.T.nd + R.T.ni == 0) return;
+    auto pair = [&](uint32_t g, uint32_t t, uint32_t c, uint32_t m, uint32_t d) {
+        const unsigned long long key = colmax_key(m, d);
+        const uint32_t grow = S.trow[t] + R.g0 + g;
+        if (A.cmx.key[grow] == key) f(grow, c, m, d);
+        if (S.tcol[t] != UINT32_MAX && A.cmx.key[S.tcol[t] + c] == key) f(S.tcol[t] + c, R.g0 + g, m, d);
+    };
+    uint32_t step = R.rows;
+    for (uint32_t v = 0; v < R.rows;) {
+        const uint32_t v1 = min(R.rows, v + step);
+        if (gt_sum<SH>(v, v1, R.T, R.n_tgt, lds, S)) {
+            const uint32_t *hk = lds, *hv = lds + SH::kSlots, *hs = lds + 2 * SH::kSlots;
+            for (uint32_t sl = threadIdx.x; sl < SH::kSlots; sl += SH::NT) {
+                const uint32_t key = hk[sl];
+                if (!key) continue;
+                const uint32_t r = (key - 1) >> 24, c = (key - 1) & 0xFFFFFFu, g = S.vr[r], t = S.vt[r], nr = S.nr[g], m = hv[sl];
+                const uint32_t nc = c < S.tn[t] ? load_global(S.tw[t] + c) : 0u;
+                if (SH::kFilt && !candidate(R.cf, nr, nc, hs[sl] & 0xFFFFu, hs[sl] >> 16)) continue;
+                if (m && nc) pair(g, t, c, m, nr + nc - m);
+            }
+            v = v1;
+            step = min(2 * step, R.rows);
+        } else if (v1 - v > 1) {
+            step = (v1 - v + 1) / 2;
+        } else {
+            Dense D(v, R.T, R.n_tgt, R.cf, lds, S);
+            if (threadIdx.x == 0) S.over = 0;
+            for (uint32_t b = 0; b < D.nblk; ++b) {
+                D.fill(b * Dense::kCols);
+                for (uint32_t i = threadIdx.x; i < Dense::kCols; i += SH::NT) {
+                    uint32_t m, d;
+                    D.value(b * Dense::kCols, i, &m, &d);
+                    if (m) pair(D.g, D.t, b * Dense::kCols + i, m, d);
+                }
+            }
+            ++v;
+        }
+        __syncthreads();  // the table takes the next rows
     }
 }
 
@@ -998,6 +1100,63 @@ __global__ __launch_bounds__(kGtThreadsBig) void k_group_tile_big(GtArgs A) {
     for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {  // uniform
         const uint2 job = A.big[i];
         gt_tile<SH, true>(A, job.x, job.y, gt_dyn, S);
+        __syncthreads();
+    }
+}
+
+// Hits from the group tiles' candidates, as k_colmax_rows: every listed pair still at its row's final
+// maximum.  How many pairs are listed on the way there depends on the order of the tiles; when there were
+// more than the list holds, the tiles are replayed with the final maxima instead, which lists nothing.  The
+// number of hits is then what the caller's capacity has to hold (it is below the list's otherwise): a plan
+// fails on the same inputs every time or never, and needed is exact.
+template <bool FILT>
+__global__ __launch_bounds__(kGtThreads) void k_group_rows(GtArgs A, uint32_t n_tiles, ColRows R, unsigned long long *n_hits,
+                                                           uint64_t hit_cap, pdp_status *st) {
+    using SH = GtSmall<FILT>;
+    const uint64_t n = *A.cmx.count;
+    if (n <= A.cmx.cap) {
+        for (uint64_t i = blockIdx.x * uint64_t(kGtThreads) + threadIdx.x; i < n; i += gridDim.x * uint64_t(kGtThreads)) {
+            const uint4 c = A.cmx.cands[i];
+            if (colmax_key(c.z, c.w) == A.cmx.key[c.x]) colmax_count(R, c.x, c.y, c.z, c.w);
+        }
+        return;
+    }
+    __shared__ __align__(16) uint32_t lds[SH::kWords];
+    __shared__ GtLds<SH::NT> S;
+    uint32_t hits = 0;
+    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        gt_replay<SH>(A, tile, lds, S, [&](uint32_t row, uint32_t col, uint32_t m, uint32_t d) {
+            colmax_count(R, row, col, m, d);
+            ++hits;
+        });
+        __syncthreads();
+    }
+    hits = wave_sum(hits);
+    if (lane_id() == 0 && hits) {
+        const unsigned long long so_far = atomicAdd(n_hits, static_cast<unsigned long long>(hits)) + hits;
+        if (so_far > hit_cap) raise_status(st, PDP_E_CAPACITY, so_far, 0);  // the last one's is the total
+    }
+}
+
+// After the row pointers, as k_colmax_big: hits of rows with more than kSlab of them.
+template <bool FILT>
+__global__ __launch_bounds__(kGtThreads) void k_group_big(GtArgs A, uint32_t n_tiles, const uint32_t *__restrict__ n_big,
+                                                          ColCsr C) {
+    using SH = GtSmall<FILT>;
+    if (*n_big == 0u) return;
+    const uint64_t n = *A.cmx.count;
+    if (n <= A.cmx.cap) {
+        for (uint64_t i = blockIdx.x * uint64_t(kGtThreads) + threadIdx.x; i < n; i += gridDim.x * uint64_t(kGtThreads)) {
+            const uint4 c = A.cmx.cands[i];
+            if (colmax_key(c.z, c.w) == A.cmx.key[c.x]) colmax_write(C, c.x, c.y, c.z, c.w);
+        }
+        return;
+    }
+    __shared__ __align__(16) uint32_t lds[SH::kWords];
+    __shared__ GtLds<SH::NT> S;
+    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        gt_replay<SH>(A, tile, lds, S,
+                      [&](uint32_t row, uint32_t col, uint32_t m, uint32_t d) { colmax_write(C, row, col, m, d); });
         __syncthreads();
     }
 }
@@ -1045,13 +1204,45 @@ static hipError_t group_tiles(const PlanShape &p, const GtArgs &A, hipStream_t s
     return hipGetLastError();
 }
 
+static GtArgs group_args(const PlanShape &p, const PairWs &w, pdp_bh_out *bh) {
+    const GtCols cmx{w.colkey, w.cands + p.cand_cap, w.gcand_count, p.gcand_cap};
+    const CandFilter cf{0, p.theta_n, p.theta_d, p.tau_n, p.tau_d};
+    return GtArgs{w.gdicts, w.gtgts, w.tmap, w.gtiles, w.gcursor, w.gdesc, w.gpost, w.gaux, p.gene_bits, cf, bh->ptr, w.slab, cmx,
+                  w.gbig_tiles, w.n_gbig + 2};
+}
+
 hipError_t launch_group_tiles(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, hipStream_t s) {
     if (!p.n_gtiles) return hipSuccess;
-    const ColWs cmx{w.colkey, w.cands, w.cand_count, p.cand_cap};
-    const CandFilter cf{0, p.theta_n, p.theta_d, p.tau_n, p.tau_d};
-    const GtArgs A{w.gdicts, w.gtgts, w.tmap, w.gtiles, w.gcursor, w.gdesc, w.gpost, w.gaux, p.gene_bits, cf, bh->ptr, w.slab, cmx,
-                   w.gbig_tiles, w.n_gbig + 2};
+    const GtArgs A = group_args(p, w, bh);
     return p.theta_d || p.tau_d ? group_tiles<true>(p, A, s) : group_tiles<false>(p, A, s);
+}
+
+static dim3 group_rows_grid(const PlanShape &p) {
+    return dim3(static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(2048, (p.gcand_cap + kGtThreads - 1) / kGtThreads))));
+}
+
+hipError_t launch_group_rows(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp_status *st, hipStream_t s) {
+    if (!p.n_gtiles) return hipSuccess;
+    const GtArgs A = group_args(p, w, bh);
+    const ColRows R{bh->ptr, w.slab, w.colcursor, w.big_rows, w.n_big};
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, group_rows_grid(p), dim3(kGtThreads), 0, s, A, p.n_gtiles, R, w.n_ghits, p.ghit_cap, st);
+    };
+    if (p.theta_d || p.tau_d) launch(k_group_rows<true>);
+    else launch(k_group_rows<false>);
+    return hipGetLastError();
+}
+
+hipError_t launch_group_big(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, hipStream_t s) {
+    if (!p.n_gtiles) return hipSuccess;
+    const GtArgs A = group_args(p, w, bh);
+    const ColCsr C{bh->ptr, bh->col, bh->num, bh->den, bh->capacity, w.colcursor};
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, group_rows_grid(p), dim3(kGtThreads), 0, s, A, p.n_gtiles, w.n_big, C);
+    };
+    if (p.theta_d || p.tau_d) launch(k_group_big<true>);
+    else launch(k_group_big<false>);
+    return hipGetLastError();
 }
 
 }  // namespace pdp

@@ -272,6 +272,8 @@ struct PairWs {
     uint2 *gbig;                  // pieces of items past the grouping kernel's LDS: narrow ones, then wide ones
     uint2 *gbig_tiles;            // tiles past the tile kernel's table: (tile, first row)
     uint32_t *n_gbig;             // counters words 18 to 20: how many of each
+    unsigned long long *gcand_count;  // counters words 24 and 25: listed candidates (after cands' first cand_cap)
+    unsigned long long *n_ghits;      // counters words 22 and 23: hits counted by a replay
     uint32_t *gcursor;            // per group tile: end of its descriptors, start of its inline ones
     uint2 *gdesc;                 // shared k-mers of each tile's genes
     uint32_t *gpost;              // postings of the shared k-mers, and their aux words
@@ -281,12 +283,15 @@ struct PairWs {
 struct PlanShape {
     uint32_t n_tasks, total_chunks, total_tiles, total_cells, bh_rows, bbh_rows, tile_lds;
     uint64_t rec_cap;               // records the scratch holds
+    uint64_t inc_cap;               // the plan's capacity as the caller sees it
     uint32_t join_grid, tile_grid;  // persistent grids (0: one work-group per item)
     uint32_t colmax;                // some task takes its BA best hits from column maxima
     uint32_t fused;                 // one-pass join into per-tile regions (else count pass + write pass)
     uint32_t join_tiles;            // most tiles of one task: LDS counters of the one-pass join
     uint32_t fallback_grid;         // work-groups of the two-pass join when it backs up the one-pass join
-    uint64_t cand_cap;              // column candidates the scratch holds (colmax: rec_cap)
+    uint64_t cand_cap;              // column candidates of the pair path (rec_cap, 0: none of its tasks has them)
+    uint64_t gcand_cap;             // candidates the group path lists, and hits it may have when they overflow that
+    uint64_t ghit_cap;
     uint32_t n_long_segs;           // long-gene path: segments and rows
     uint32_t long_rows;
     uint32_t long_lds;              // long-gene path: LDS bytes of a work-group (one or three sums per column)
@@ -324,6 +329,9 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
 hipError_t allow_group_lds();
 hipError_t launch_group_join(const PlanShape &p, const PairWs &w, hipStream_t s);
 hipError_t launch_group_tiles(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, hipStream_t s);
+// Their hits from the candidates: counted, then (after the row pointers) those of rows past the slab written.
+hipError_t launch_group_rows(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp_status *st, hipStream_t s);
+hipError_t launch_group_big(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, hipStream_t s);
 // Families (connected components of the BBH network) into labels[n_nodes].
 hipError_t launch_families(const PlanShape &p, const PairWs &w, const pdp_bbh_out *bbh, const uint32_t *node_a,
                            const uint32_t *node_b, uint32_t n_nodes, uint32_t *labels, pdp_status *st, hipStream_t s);

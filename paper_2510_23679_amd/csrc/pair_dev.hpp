@@ -68,9 +68,49 @@ __device__ __forceinline__ unsigned long long colmax_key(uint32_t m, uint32_t d)
 
 // Raises the column's running maximum by the pair's key; true when the pair is at or above
 // the maximum so far (the final maximum is never below it, so no final best hit is missed).
-__device__ __forceinline__ bool colmax_raise(const ColWs &cw, uint32_t ba_row, uint32_t m, uint32_t d) {
+__device__ __forceinline__ bool colmax_raise(unsigned long long *key, uint32_t ba_row, uint32_t m, uint32_t d) {
     const unsigned long long k = colmax_key(m, d);
-    return k >= atomicMax(&cw.key[ba_row], k);
+    return k >= atomicMax(&key[ba_row], k);
+}
+
+// The rows that get their hits from column maxima.
+struct ColRows {
+    uint32_t *bh_ptr;
+    uint4 *slab;
+    uint32_t *cursor;  // per row with more than kSlab hits: hits placed so far
+    uint32_t *big;     // those rows
+    uint32_t *n_big;
+};
+
+// Counts a hit (column, m, d) of a row, the first kSlab of them into its slab.
+__device__ __forceinline__ void colmax_count(const ColRows &R, uint32_t row, uint32_t col, uint32_t m, uint32_t d) {
+    const uint32_t t = atomicAdd(&R.bh_ptr[row], 1u);
+    if (t < kSlab) {
+        R.slab[static_cast<uint64_t>(row) * kSlab + t] = make_uint4(col, m, d, 0);
+    } else if (t == kSlab) {  // one thread per row: the row is listed, its cursor cleared
+        R.cursor[row] = 0;
+        R.big[atomicAdd(R.n_big, 1u)] = row;
+    }
+}
+
+// The best-hit output, after bh_ptr became row pointers.
+struct ColCsr {
+    const uint32_t *bh_ptr;
+    uint32_t *col, *num, *den;
+    uint64_t cap;
+    uint32_t *cursor;
+};
+
+// Puts a hit of a row with more than kSlab of them into the output, in any order.
+__device__ __forceinline__ void colmax_write(const ColCsr &C, uint32_t row, uint32_t col, uint32_t m, uint32_t d) {
+    const uint32_t p = C.bh_ptr[row];
+    if (C.bh_ptr[row + 1] - p <= kSlab) return;
+    const uint64_t pos = uint64_t(p) + atomicAdd(&C.cursor[row], 1u);
+    if (pos < C.cap) {
+        C.col[pos] = col;
+        C.num[pos] = m;
+        C.den[pos] = d;
+    }
 }
 
 }  // namespace pdp

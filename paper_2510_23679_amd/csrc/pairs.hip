@@ -1185,7 +1185,7 @@ __device__ __forceinline__ void tile_dense(const DevTile &tl, const DevTask &T, 
                             bd = d;
                         }
                         // column maxima (rows past the hash table are rare: one global slot each)
-                        if (colmax && colmax_raise(*cmx, T.row_base[1] + 2 * wd + h, m, d)) {
+                        if (colmax && colmax_raise(cmx->key, T.row_base[1] + 2 * wd + h, m, d)) {
                             const uint32_t idx = atomicAdd(cmx->count, 1u);
                             if (idx < cmx->cap) cmx->cands[idx] = make_uint4(T.row_base[1] + 2 * wd + h, row, m, d);
                         }
@@ -1329,7 +1329,7 @@ __device__ __forceinline__ void tile_hashed(const DevTile &tl, const DevTask &T,
         hv[sl] = m | (nc << 16);
         if (!m) continue;
         const uint32_t d = S.nr[rl] + nc - m;
-        if (colmax && colmax_raise(cmx, T.row_base[1] + ((key - 1) & 0xFFFFFFu), m, d)) app |= 1u << q;
+        if (colmax && colmax_raise(cmx.key, T.row_base[1] + ((key - 1) & 0xFFFFFFu), m, d)) app |= 1u << q;
         const unsigned long long want = (static_cast<unsigned long long>(m) << 32) | d;
         unsigned long long cur = S.best[rl];
         for (;;) {
@@ -1577,46 +1577,25 @@ __global__ __launch_bounds__(kRowThreads) void k_rows_slab(uint32_t bh_rows, uin
 // Column maxima, after the AB tiles: every listed pair still at its column's final maximum
 // is a best hit of the column's gene (Alg. 3's test S[l,k] = max_r S[r,k]).  The count goes
 // to the BA row's bh_ptr and the first kSlab hits to its slab, as the tiles do for AB rows.
-__global__ __launch_bounds__(256) void k_colmax_rows(ColWs cmx, uint32_t *__restrict__ bh_ptr, uint4 *__restrict__ slab,
-                                                     uint32_t *__restrict__ cursor, uint32_t *__restrict__ big,
-                                                     uint32_t *__restrict__ n_big, pdp_status *st) {
+__global__ __launch_bounds__(256) void k_colmax_rows(ColWs cmx, ColRows R, pdp_status *st) {
     const uint32_t n = *cmx.count;
     if (blockIdx.x == 0 && threadIdx.x == 0 && n > cmx.cap) raise_status(st, PDP_E_CAPACITY, n, 0);
     const uint64_t lim = min(static_cast<uint64_t>(n), cmx.cap);
     for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < lim; i += gridDim.x * 256ull) {
         const uint4 c = cmx.cands[i];
-        if (colmax_key(c.z, c.w) != cmx.key[c.x]) continue;
-        const uint32_t t = atomicAdd(&bh_ptr[c.x], 1u);
-        if (t < kSlab) {
-            slab[static_cast<uint64_t>(c.x) * kSlab + t] = make_uint4(c.y, c.z, c.w, 0);
-        } else if (t == kSlab) {  // one thread per row: the row is listed, its cursor cleared
-            cursor[c.x] = 0;
-            big[atomicAdd(n_big, 1u)] = c.x;
-        }
+        if (colmax_key(c.z, c.w) == cmx.key[c.x]) colmax_count(R, c.x, c.y, c.z, c.w);
     }
 }
 
 // After the scan: hits of listed rows, those with more than kSlab of them, go straight to the CSR
 // (in any order; k_colmax_sort orders those rows), slots taken from a per-row cursor.  Mostly there
 // are none, and nothing is read.
-__global__ __launch_bounds__(256) void k_colmax_big(ColWs cmx, uint32_t *__restrict__ cursor,
-                                                    const uint32_t *__restrict__ n_big,
-                                                    const uint32_t *__restrict__ bh_ptr, uint32_t *__restrict__ bh_col,
-                                                    uint32_t *__restrict__ bh_num, uint32_t *__restrict__ bh_den,
-                                                    uint64_t bh_cap) {
+__global__ __launch_bounds__(256) void k_colmax_big(ColWs cmx, const uint32_t *__restrict__ n_big, ColCsr C) {
     if (*n_big == 0u) return;
     const uint64_t lim = min(static_cast<uint64_t>(*cmx.count), cmx.cap);
     for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < lim; i += gridDim.x * 256ull) {
         const uint4 c = cmx.cands[i];
-        if (colmax_key(c.z, c.w) != cmx.key[c.x]) continue;
-        const uint32_t p = bh_ptr[c.x];
-        if (bh_ptr[c.x + 1] - p <= kSlab) continue;
-        const uint64_t pos = uint64_t(p) + atomicAdd(&cursor[c.x], 1u);
-        if (pos < bh_cap) {
-            bh_col[pos] = c.y;
-            bh_num[pos] = c.z;
-            bh_den[pos] = c.w;
-        }
+        if (colmax_key(c.z, c.w) == cmx.key[c.x]) colmax_write(C, c.x, c.y, c.z, c.w);
     }
 }
 
@@ -2130,7 +2109,7 @@ uint64_t pair_ws_bytes(const PlanShape &p) {
         const uint64_t colrows = uint64_t(p.bh_rows) + 1;
         s += align_up(8 * colrows, A);                              // column keys
         s += align_up(4 * colrows, A);                              // big-row cursors
-        s += align_up(16 * std::max<uint64_t>(p.cand_cap, 1), A);   // candidates
+        s += align_up(16 * std::max<uint64_t>(p.cand_cap + p.gcand_cap, 1), A);   // candidates
     }
     s += align_up(sizeof(DevLongSeg) * uint64_t(p.n_long_segs), A);
     if (p.n_gdicts) {
@@ -2179,6 +2158,8 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
     w.join_done = reinterpret_cast<uint32_t *>(w.counters) + 16;
     w.n_big = reinterpret_cast<uint32_t *>(w.counters) + 17;
     w.n_gbig = reinterpret_cast<uint32_t *>(w.counters) + 18;
+    w.gcand_count = w.counters + 12;
+    w.n_ghits = w.counters + 11;
     w.colkey = nullptr;
     w.colcursor = nullptr;
     w.cands = nullptr;
@@ -2186,7 +2167,7 @@ PairWs pair_ws_carve(void *ws, const PlanShape &p) {
         const uint64_t colrows = uint64_t(p.bh_rows) + 1;
         w.colkey = reinterpret_cast<unsigned long long *>(take(8 * colrows));
         w.colcursor = reinterpret_cast<uint32_t *>(take(4 * colrows));
-        w.cands = reinterpret_cast<uint4 *>(take(16 * std::max<uint64_t>(p.cand_cap, 1)));
+        w.cands = reinterpret_cast<uint4 *>(take(16 * std::max<uint64_t>(p.cand_cap + p.gcand_cap, 1)));
     }
     w.cand_count = reinterpret_cast<uint32_t *>(w.counters) + 6;
     w.long_segs = reinterpret_cast<DevLongSeg *>(take(sizeof(DevLongSeg) * uint64_t(p.n_long_segs)));
@@ -2223,7 +2204,7 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
                        s, st, reinterpret_cast<uint32_t *>(w.counters), w.tile_tot, w.fill, p.total_tiles, bh->ptr, w.colkey,
                        key_rows, w.gdicts, w.gtiles, p.n_gdicts ? p.n_gtiles : 0u, w.gcursor);
     PDP_TRY(hipGetLastError());
-    const ColWs cmx{w.colkey, w.cands, w.cand_count, p.colmax ? p.cand_cap : 0};
+    const ColWs cmx{w.colkey, w.cands, w.cand_count, p.cand_cap};
     if (p.n_gdicts) {  // the group path's join; timed as the join with the pair path's, when a plan has both
         PDP_TRY(mark(PDP_KERNEL_JOIN, true));
         PDP_TRY(launch_group_join(p, w, s));
@@ -2310,11 +2291,12 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
     }
     PDP_TRY(launch_group_tiles(p, w, bh, s));
     const uint32_t col_grid = std::max<uint32_t>(1, std::min<uint32_t>(2048, static_cast<uint32_t>((p.cand_cap + 255) / 256)));
-    if (p.colmax) {
-        hipLaunchKernelGGL(k_colmax_rows, dim3(col_grid), dim3(256), 0, s, cmx, bh->ptr, w.slab, w.colcursor, w.big_rows,
-                           w.n_big, st);
+    const ColRows rows{bh->ptr, w.slab, w.colcursor, w.big_rows, w.n_big};
+    if (p.cand_cap) {
+        hipLaunchKernelGGL(k_colmax_rows, dim3(col_grid), dim3(256), 0, s, cmx, rows, st);
         PDP_TRY(hipGetLastError());
     }
+    PDP_TRY(launch_group_rows(p, w, bh, st, s));
     const dim3 long_grid(std::min(p.long_rows, kLongGrid));
     const dim3 long_grid_big(std::min((p.long_rows + 3) / 4, 1024u));
     if (p.long_rows) {
@@ -2364,9 +2346,12 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
         PDP_TRY(hipGetLastError());
     }
     if (p.colmax && p.bh_rows) {
-        hipLaunchKernelGGL(k_colmax_big, dim3(col_grid), dim3(256), 0, s, cmx, w.colcursor, w.n_big, bh->ptr, bh->col,
-                           bh->num, bh->den, bh->capacity);
-        PDP_TRY(hipGetLastError());
+        if (p.cand_cap) {
+            hipLaunchKernelGGL(k_colmax_big, dim3(col_grid), dim3(256), 0, s, cmx, w.n_big,
+                               ColCsr{bh->ptr, bh->col, bh->num, bh->den, bh->capacity, w.colcursor});
+            PDP_TRY(hipGetLastError());
+        }
+        PDP_TRY(launch_group_big(p, w, bh, s));
         hipLaunchKernelGGL(k_colmax_sort, dim3(std::min<uint32_t>(p.bh_rows, 1024)), dim3(kWave), 0, s, w.big_rows, w.n_big,
                            bh->ptr, bh->col, bh->num, bh->den, bh->capacity);
         PDP_TRY(hipGetLastError());
