@@ -301,17 +301,24 @@ static uint64_t bucket_code(const pdp_dict *d, uint64_t b) {
 
 // The group path's share of a plan: which tasks take it, and their tables (in_group[t] is set).  A
 // group is a connected component of the task graph, with at least a quarter of its pairs compared,
-// whose pair-by-pair join would search its entries kGroupGain times as often as the group path
-// reads them (all pairs of D genomes: (D - 1) / 2 times), and whose k-mers meet at most kGroupChance
-// k-mers of a target genome by chance.  Launch times without the builds, pair path against group
-// path: 6 x 3000 genes (2.5), k = 6: 137 / 150 us; 8 x 3000 (3.5): 211 / 206; 12 x 3000: 415 / 362; nine
-// genomes of 577 to 4377 genes (2.7), filters and families: 345 / 262; every
-// chance match costs a descriptor, whatever the pair path spends on it: 12 x 1000 genes, k = 5 (0.1 by
-// chance) 329 / 375 us, k = 6 (0.005) 170 / 155; 10 x 3000 nucleotide genes, k = 13 (0.045) 811 / 750.
-constexpr uint64_t kGroupGainNum = 13, kGroupGainDen = 5;
+// whose pair-by-pair join would search its entries often enough (gain: searched entries by those the
+// group path reads, (D - 1) / 2 for all pairs of D genomes), and whose k-mers meet at most kGroupChance
+// k-mers of a target genome by chance.  The gain that pays falls with the group's size, whose passes fill
+// the chip, and with filters, which cost the pair path more.  Launch times without the builds, pair path
+// against group path, k = 6, even letters; in brackets with filters:
+//   1000 genes: 8 genomes (3.5) 107 / 136 [107 / 116], 10 (4.5) 138 / 159 [150 / 137], 12 (5.5) 178 / 173 [199 / 157]
+//   2000 genes: 6 (2.5) 110 / 149 [114 / 130], 8 (3.5) 158 / 186 [174 / 160], 10 (4.5) 222 / 223 [244 / 196]
+//   4000 genes: 6 (2.5) 180 / 215 [194 / 187], 8 (3.5) 297 / 288 [311 / 256], 10 (4.5) 466 / 400 [503 / 359]
+// with the letters of proteins 8 x 4000 553 / 522, near-identical genomes 883 / 713, 1333 nucleotide genes
+// 243 / 215.  Under a million entries both take mostly launches (9 x 300 genes 81 / 89 us [89 / 75]).
+// Every chance match costs a descriptor, whatever the pair path spends on it: 12 x 1000 genes, k = 5 (0.1
+// by chance) 329 / 375 us, k = 6 (0.005) 170 / 155; 10 x 3000 nucleotide genes, k = 13 (0.045) 811 / 750.
+constexpr uint64_t kGroupSmall = 1000000;      // entries of a plan up to which a gain of kGroupGain is enough
+constexpr double kGroupGain = 2.6, kGroupGainFilt = 1.8;
+constexpr double kGroupFixed = 7e6, kGroupFixedFilt = 4e6;  // searched entries past that which a larger plan has to save
 constexpr double kGroupChance = 0.05;  // expected chance matches per k-mer and target genome, at most
 static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks, const std::vector<uint8_t> &is_long,
-                            std::vector<uint8_t> &in_group) {
+                            bool filt, std::vector<uint8_t> &in_group) {
     std::vector<const pdp_dict *> dicts;
     std::vector<uint32_t> ta(n_tasks, UINT32_MAX), tb(n_tasks, UINT32_MAX);
     {
@@ -374,7 +381,11 @@ static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks
             genes += dicts[i]->n_genes;
         }
         for (uint32_t t : ctasks[c]) searched += std::min(tasks[t].a->capacity, tasks[t].b->capacity);
-        if (searched * kGroupGainDen < cap * kGroupGainNum || ctasks[c].size() * 8 < uint64_t(D) * (D - 1)) continue;
+        const double share = double(cap) / double(all_cap);  // several groups fill the chip together
+        const double pays = all_cap <= kGroupSmall ? kGroupGain * double(cap)
+                                                   : (filt ? kGroupGainFilt * double(cap) + kGroupFixedFilt * share
+                                                           : kGroupGain * double(cap) + kGroupFixed * share);
+        if (double(searched) < pays || ctasks[c].size() * 8 < uint64_t(D) * (D - 1)) continue;
         const pdp_dict *d0 = dicts[M[0]];
         const AlphaSpec al = alpha_spec(d0->alphabet);
         const double per_kmer = std::pow(double(al.sigma), -double(d0->k)) * (double(cap) / D);
@@ -652,7 +663,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
     uint64_t group_est = 0;
     bool pair_colmax = false;
     if (n_tasks >= 3 && !(prm.flags & (PDP_PARAM_PERSISTENT | PDP_PARAM_TWO_PASS))) {
-        P->shape.gentries = plan_groups(P, tasks, n_tasks, is_long, in_group);
+        P->shape.gentries = plan_groups(P, tasks, n_tasks, is_long, filt, in_group);
         for (uint32_t t = 0; t < n_tasks; ++t) {
             if (!in_group[t]) continue;
             DevTask &d = caller[t];

@@ -1,5 +1,6 @@
-"""Work items of the group path (host side, no GPU): an item holds a fair share of a group's index
-entries whatever the k-mer length, so that plan tables, launches and host time stay in proportion."""
+"""Plans of the group path (host side, no GPU): a work item holds a fair share of a group's index entries
+whatever the k-mer length, so that plan tables, launches and host time stay in proportion; and a plan takes
+the path where the measurements say that it pays."""
 import ctypes as C
 
 import pytest
@@ -19,20 +20,21 @@ def _dicts(n, genes, per, k, alphabet):
     return out
 
 
-def _items(dicts):
+def _items(dicts, **prm):
     n = len(dicts)
+    prm = pdp.params(**prm)
     tasks = (B.pdp_task * (n * (n - 1) // 2))()
     for t, (i, j) in zip(tasks, [(i, j) for i in range(n) for j in range(i)]):
         t.a, t.b, t.flags = C.pointer(dicts[i]), C.pointer(dicts[j]), pdp.PDP_TASK_BBH
     h, info = B.vp(), B.pdp_plan_info()
-    B.check(pdp.lib().pdp_plan_create(tasks, len(tasks), None, C.byref(h)), "plan")
+    B.check(pdp.lib().pdp_plan_create(tasks, len(tasks), C.byref(prm), C.byref(h)), "plan")
     B.check(pdp.lib().pdp_plan_info_get(h, C.byref(info)), "info")
     pdp.lib().pdp_plan_destroy(h)
     return info.join_groups
 
 
 @pytest.mark.parametrize("alphabet,k", [("aa", k) for k in range(6, 13)] + [("nt", k) for k in (15, 17, 21, 23, 24, 25, 26, 31)])
-@pytest.mark.parametrize("n,genes", [(12, 200), (12, 1270), (10, 3000), (40, 4000)])
+@pytest.mark.parametrize("n,genes", [(16, 200), (12, 1270), (10, 3000), (40, 4000)])
 def test_items_are_in_proportion_to_the_entries(n, genes, alphabet, k):
     per = 300 if alphabet == "aa" else 900
     buckets = 160000 if alphabet == "aa" else 262144
@@ -40,3 +42,16 @@ def test_items_are_in_proportion_to_the_entries(n, genes, alphabet, k):
     # about 1536 entries an item (fewer in small plans: at least 256), half of that for a narrow
     # identity, and whole buckets: an item's share is rounded down by at most half
     assert _items(_dicts(n, genes, per, k, alphabet)) <= min(buckets, 4 * max(entries // 1536, min(1024, entries // 256)) + 8)
+
+
+@pytest.mark.parametrize("n,genes,filters,grouped", [
+    (9, 300, False, True), (7, 300, True, True), (6, 300, False, False),       # launches either way
+    (7, 1000, False, False), (10, 1000, False, False), (12, 1000, False, True),
+    (7, 1000, True, False), (10, 1000, True, True),
+    (8, 2000, False, False), (10, 2000, False, True), (6, 2000, True, False), (8, 2000, True, True),
+    (6, 4000, False, False), (8, 4000, False, True), (5, 4000, True, False), (7, 4000, True, True),
+    (50, 4000, False, True)])
+def test_a_group_is_taken_where_it_pays(n, genes, filters, grouped):
+    prm = {"theta": (1, 2), "tau": (1, 6)} if filters else {}
+    dicts = _dicts(n, genes, 340, 6, "aa")
+    assert (_items(dicts, **prm) != _items(dicts, persistent=True, **prm)) == grouped
