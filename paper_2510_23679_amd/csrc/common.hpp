@@ -139,19 +139,19 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t *t
 }
 
 // Counts this work-group as ended in *done (zero before the launch); true, for all its threads, in the
-// one that ends last, which then sees every global write and atomic of the launch.  Every thread
-// fences before the barrier: the barrier is a release at work-group scope only, which leaves the
-// other waves' atomics without return value in flight, and a fence waits for its own wave's alone.
+// one that ends last: every device-scope atomic of the launch is then complete, for atomic loads at device
+// scope to read.  Every wave waits for its own before the barrier, which is a release at work-group
+// scope only and leaves atomics without return value in flight.  Nothing else is read, so nothing is
+// written back: with fences instead the bin histogram of 10 genomes of 4300 genes took 131 us for 44, the
+// two-pass join's count pass of five near-identical ones 277 for 148.
 // flag: a word of LDS.  Contains barriers; every thread of the work-group must call it.
 __device__ __forceinline__ bool last_group(uint32_t *done, uint32_t *flag) {
-    __threadfence();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0)
-        *flag = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x ? 1u : 0u;
+        *flag = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x ? 1u : 0u;
     __syncthreads();
-    if (!*flag) return false;
-    __threadfence();
-    return true;
+    return *flag != 0u;
 }
 
 // Comparator network sort of n items by one work-group, ascending, for any n.
