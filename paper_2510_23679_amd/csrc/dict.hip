@@ -1434,9 +1434,10 @@ hipError_t launch_dict_build_many(const pdp_genome *g, pdp_dict *const *d, uint3
     narrow_rec &= narrow;
     // entries per placement block and per bin: large ones give each (block, bin) a longer run; builds
     // that leave the chip mostly idle take small blocks and bins.  One genome, small against large: 340,000
-    // letters (1000 genes) 92 / 98 us, 510,000 108 / 104, 680,000 136 / 112, 1.46 million 227 / 132; k = 8
-    // 111 / 119, 135 / 131, 157 / 141, 259 / 184; nucleotides 119 / 127, 130 / 129, 157 / 134, 260 / 182.
-    const bool small = sh.total_residues <= 32ull * kIxBlock;
+    // letters (1000 genes) 84 / 98 us, 510,000 94 / 104, 680,000 117 / 109, 1.46 million 187 / 129; k = 8
+    // 102 / 119, 122 / 129, 137 / 143, 216 / 185; nucleotides 111 / 130, 121 / 130, 140 / 135, 223 / 180; six
+    // genomes 79 / 101, 93 / 110, 98 / 113, 140 / 133.
+    const bool small = sh.total_residues <= 40ull * kIxBlock;
     const uint32_t blk = small ? kIxBlockSmall : kIxBlock;
     const uint32_t target = narrow_rec && !small ? kIxBinTarget : kIxBinTargetWide;
     const uint32_t slots = narrow_rec ? BinSort<uint2>::kSlots : BinSort<uint4>::kSlots;

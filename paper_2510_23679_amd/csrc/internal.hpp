@@ -20,7 +20,7 @@ constexpr uint32_t kScanItems = 4096;        // elements per scan work-group (25
 constexpr uint32_t kMvSortCap = 8192;        // windows a gene may have to be sorted in LDS
 constexpr uint32_t kKMaxAll = PDP_K_MAX_NT > PDP_K_MAX ? PDP_K_MAX_NT : PDP_K_MAX;  // k bound over alphabets
 constexpr uint32_t kIxBlock = 16384;         // index entries per placement block (large builds)
-constexpr uint32_t kIxBlockSmall = 2048;     // the same in builds of up to 32 of those blocks
+constexpr uint32_t kIxBlockSmall = 2048;     // the same in builds of up to 40 of those blocks
 constexpr uint32_t kIxBinTarget = 2700;      // index entries per coarse bin, at most on average (8-byte records)
 constexpr uint32_t kIxBinTargetWide = 512;   // the same for 16-byte records, and small builds
 constexpr uint32_t kIxMaxBins = 8192;        // coarse bins per genome at most (LDS histogram)

@@ -80,9 +80,9 @@ def test_protein_letters_do_not_slow_the_build_down():
 
 
 @pytest.mark.parametrize("k", [6, 7, 8])
-@pytest.mark.parametrize("letters", [524287, 524288])
+@pytest.mark.parametrize("letters", [655359, 655360])
 def test_around_the_small_builds(letters, k):
-    # a build's letters and one entry per genome: up to 32 blocks of 16384 take the small forms
+    # a build's letters and one entry per genome: up to 40 blocks of 16384 take the small forms
     genome = _genome(30, 1, letters % 1000 or 1000, AA, PROTEIN)
     rest = _genome(31, letters // 1000, 1000, AA, PROTEIN)
     genome.residues = np.concatenate([rest.residues, genome.residues])[:letters]
@@ -99,7 +99,7 @@ def test_around_two_entries_a_bucket():
     for g in genomes:  # genes of ordinary length
         n = g.n_residues
         g.offsets = np.append(np.arange(0, n, 400, dtype=np.uint64), np.uint64(n))
-    genomes.append(_genome(40, 1000, 500, AA))
+    genomes.append(_genome(40, 1000, 700, AA))
     print("[case] two entries a bucket", [g.n_residues for g in genomes], flush=True)
     batch = pdp.DictionaryBatch([pdp.DeviceGenome.of(g) for g in genomes], 6)
     batch.build()
