@@ -441,7 +441,8 @@ def run_batched(args):
                 tuned = {"tile_rows": int(best.tile_rows), "join_entries": int(best.join_entries),
                          "persistent": bool(best.flags & B.PDP_PARAM_PERSISTENT),
                          "column_maxima": bool(best.flags & B.PDP_PARAM_COLMAX), "candidates": int(tres.tried),
-                         "best_ms": round(tres.best_ms, 3), "first_ms": round(tres.first_ms, 3)}
+                         "best_ms": round(tres.best_ms, 3), "first_ms": round(tres.first_ms, 3),
+                         "group_path": best.tile_rows == 0}
             prm = (pdp.params(persistent=True) if args.persistent else
                    pdp.params(tile_rows=tuned["tile_rows"], join_entries=tuned["join_entries"],
                               persistent=tuned["persistent"], colmax=tuned["column_maxima"]))
@@ -714,7 +715,9 @@ def main():
         tuned = {"autotuned": True, "tile_rows": int(best.tile_rows), "join_entries": int(best.join_entries),
                  "persistent": bool(best.flags & B.PDP_PARAM_PERSISTENT),
                  "column_maxima": bool(best.flags & B.PDP_PARAM_COLMAX), "best_ms": round(tres.best_ms, 4),
-                 "first_ms": round(tres.first_ms, 4), "candidates": int(tres.tried)}
+                 "first_ms": round(tres.first_ms, 4), "candidates": int(tres.tried),
+                 # the tasks form a group: the library sizes its items and tiles, both directions come from one
+                 "group_path": best.tile_rows == 0}
         say(f"autotuner: {tuned}")
     runner = pdp.PairRunner(tasks, prm)
     runner.run()  # sizes the scratch and outputs

@@ -417,7 +417,9 @@ void pdp_graph_destroy(pdp_graph *graph);
  * two HIP events; the fastest candidate whose runs end with a clean status is
  * returned.  candidates NULL: a built-in grid of tile heights (32, 64, 128
  * rows), join sub-range sizes (256, 512, 768, 1024 entries), persistent on/off and
- * column maxima on/off (PDP_PARAM_COLMAX).  bh/bbh/status as
+ * column maxima on/off (PDP_PARAM_COLMAX).  Candidates whose tasks all form groups
+ * (see pdp_plan_create) launch the same kernels: one of them is timed, and as the
+ * best one has tile_rows, join_entries and lds_budget 0.  bh/bbh/status as
  * for pdp_plan_launch (their rows do not depend on the parameters); ws of
  * pdp_autotune_ws_size bytes.  Synchronises the stream.
  * Errors: PDP_E_INVAL, PDP_E_HIP, PDP_E_LIMIT (no candidate ran cleanly). */
@@ -425,7 +427,7 @@ typedef struct pdp_tune_result {
     pdp_params best;
     double best_ms;   /* average milliseconds per launch of the best candidate */
     double first_ms;  /* the same for the first candidate that ran */
-    uint32_t tried;   /* candidates that ran cleanly */
+    uint32_t tried;   /* candidates that were timed and ran cleanly */
     uint32_t reserved;
 } pdp_tune_result;
 int32_t pdp_autotune_ws_size(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *candidates,

@@ -841,6 +841,8 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
 }  // extern "C"
 
 namespace pdp {
+bool plan_all_grouped(const pdp_plan *P) { return P->shape.n_gdicts && !P->shape.total_chunks && !P->shape.long_rows; }
+
 int32_t plan_rebind(pdp_plan *P, const pdp_dict *from, const pdp_dict *to) {
     if (!P || !from || !to) return PDP_E_INVAL;
     if (from->n_genes != to->n_genes || from->capacity != to->capacity || from->k != to->k ||

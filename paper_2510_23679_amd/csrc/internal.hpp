@@ -311,6 +311,8 @@ uint32_t persistent_join_grid();
 // elsewhere (so a plan made before a dictionary's memory is placed serves it afterwards).
 // PDP_E_INVAL when the two differ in anything but their addresses.
 int32_t plan_rebind(pdp_plan *plan, const pdp_dict *from, const pdp_dict *to);
+// Whether all of a plan's tasks take the group path, whose launch shape the tuning parameters do not change.
+bool plan_all_grouped(const pdp_plan *plan);
 uint32_t persistent_fused_grid(uint32_t join_tiles);
 uint32_t persistent_tile_grid(uint32_t tile_lds);
 hipError_t allow_tile_lds(uint32_t tile_lds);

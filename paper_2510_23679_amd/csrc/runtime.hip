@@ -112,10 +112,17 @@ int32_t pdp_autotune(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *
     }
     std::memset(out, 0, sizeof(*out));
     double best = -1;
+    const pdp_params *grouped = nullptr;  // a candidate on the group path that was timed: others launch the same
     int32_t rc = PDP_OK;
     for (size_t i = 0; i < c.size(); ++i) {
         pdp_plan *P = nullptr;
         if (pdp_plan_create(tasks, n_tasks, &c[i], &P) != PDP_OK) continue;
+        const bool group = plan_all_grouped(P);
+        if (group && grouped && c[i].theta_num == grouped->theta_num && c[i].theta_den == grouped->theta_den &&
+            c[i].tau_num == grouped->tau_num && c[i].tau_den == grouped->tau_den) {
+            pdp_plan_destroy(P);
+            continue;
+        }
         pdp_plan_info info;
         pdp_plan_info_get(P, &info);
         bool ok = info.ws_bytes <= ws_bytes && pdp_plan_upload(P, ws, ws_bytes, stream) == PDP_OK &&
@@ -135,9 +142,11 @@ int32_t pdp_autotune(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *
         const double avg = ms / reps;
         if (out->tried == 0) out->first_ms = avg;
         out->tried++;
+        if (group) grouped = &c[i];
         if (best < 0 || avg < best) {
             best = avg;
             out->best = c[i];
+            if (group) out->best.tile_rows = out->best.join_entries = out->best.lds_budget = 0;  // not what ran
             out->best_ms = avg;
         }
     }
