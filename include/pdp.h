@@ -357,8 +357,8 @@ int32_t pdp_plan_launch(const pdp_plan *plan, pdp_bh_out *bh, pdp_bbh_out *bbh, 
 /* Kernels of a plan launch, for pdp_plan_timer_start. */
 #define PDP_KERNEL_JOIN 0        /* shared-k-mer join: the one-pass kernel (with PDP_PARAM_TWO_PASS: count
                                     pass, scan of the counts, write pass) */
-#define PDP_KERNEL_BUCKET 1      /* between the count and the write pass of the two-pass join (the scan of the
-                                    per-tile record totals ends the count pass: nothing in between) */
+#define PDP_KERNEL_BUCKET 1      /* the scan of the per-tile record totals: part of the two-pass join's count
+                                    pass, so always zero */
 #define PDP_KERNEL_TILE_COUNT 2  /* per tile: sort and sum of records, row maxima, tie counts */
 #define PDP_KERNEL_TILE_WRITE 3  /* best-hit output (rows from their slabs, rows with many ties) */
 #define PDP_KERNEL_BBH 4         /* BBH count and write passes together */

@@ -66,6 +66,7 @@ struct pdp_plan {
     // measurement hook: event pairs owned by the plan, one per timed launch
     mutable int32_t timer_kernel = -1;
     mutable uint32_t timer_used = 0;
+    uint32_t timer_max = 0;
     mutable std::vector<std::pair<hipEvent_t, hipEvent_t>> timer_events;
 
     void timer_release() const {
@@ -849,6 +850,8 @@ int32_t plan_rebind(pdp_plan *P, const pdp_dict *from, const pdp_dict *to) {
         from->alphabet != to->alphabet || from->n_buckets != to->n_buckets || from->key_shift != to->key_shift ||
         from->flags != to->flags || (from->ix_key == nullptr) != (to->ix_key == nullptr))
         return PDP_E_INVAL;
+    // served requests compare one genome with all residents, which searches no entry of it often enough for a group
+    if (!P->gdicts.empty()) return PDP_E_INVAL;
     const DevDict nd = dev_dict(to);
     const uint32_t *lo = from->ix_dir, *hi = from->ix_dir + from->n_buckets + 1;
     auto move = [&](const uint32_t *p) { return p >= lo && p < hi ? to->ix_dir + (p - lo) : p; };
@@ -856,17 +859,6 @@ int32_t plan_rebind(pdp_plan *P, const pdp_dict *from, const pdp_dict *to) {
         if (t.a.ix_dir == from->ix_dir) t.a = nd;
         if (t.b.ix_dir == from->ix_dir) t.b = nd;
     }
-    for (DevGroupDict &g : P->gdicts)
-        if (g.ix_dir == from->ix_dir) {
-            g.ix_code = to->ix_code;
-            g.ix_gene = to->ix_gene;
-            g.ix_cnt = to->ix_cnt;
-            g.ix_dir = to->ix_dir;
-            g.nwin = to->nwin;
-            g.mv_ptr = to->mv_ptr;
-        }
-    for (DevGroupTgt &g : P->gtgts)
-        if (g.nwin == from->nwin) g.nwin = to->nwin;
     for (DevItem &it : P->items) {
         it.adir = move(it.adir);
         it.bdir = move(it.bdir);
@@ -975,7 +967,9 @@ int32_t pdp_plan_launch(const pdp_plan *plan, pdp_bh_out *bh, pdp_bbh_out *bbh, 
     shape.tile_grid = plan->tile_grid;
     shape.fallback_grid = plan->fallback_grid;
     KernelTimer timer{-1, nullptr, nullptr};
-    if (plan->timer_kernel >= 0 && plan->timer_used < plan->timer_events.size()) {
+    if (plan->timer_kernel == PDP_KERNEL_BUCKET) {  // no kernel of its own
+        if (plan->timer_used < plan->timer_max) plan->timer_used++;
+    } else if (plan->timer_kernel >= 0 && plan->timer_used < plan->timer_events.size()) {
         timer.kernel = plan->timer_kernel;
         timer.start = plan->timer_events[plan->timer_used].first;
         timer.stop = plan->timer_events[plan->timer_used].second;
@@ -1007,7 +1001,7 @@ int32_t pdp_plan_timer_start(pdp_plan *plan, int32_t kernel, uint32_t max_launch
     if (!plan || kernel < PDP_KERNEL_JOIN || kernel > PDP_KERNEL_JOIN_BACKUP || max_launches == 0)
         return fail(PDP_E_INVAL, "pdp_plan_timer_start: bad argument");
     plan->timer_release();
-    for (uint32_t i = 0; i < max_launches; ++i) {
+    for (uint32_t i = 0; kernel != PDP_KERNEL_BUCKET && i < max_launches; ++i) {
         hipEvent_t a, b;
         hipError_t e = hipEventCreate(&a);
         if (e != hipSuccess) return hip_fail(e, "pdp_plan_timer_start");
@@ -1020,13 +1014,14 @@ int32_t pdp_plan_timer_start(pdp_plan *plan, int32_t kernel, uint32_t max_launch
     }
     plan->timer_kernel = kernel;
     plan->timer_used = 0;
+    plan->timer_max = max_launches;
     return ok();
 }
 
 int32_t pdp_plan_timer_read(pdp_plan *plan, double *total_ms, uint32_t *launches) {
     if (!plan || !total_ms || !launches) return fail(PDP_E_INVAL, "pdp_plan_timer_read: null pointer");
     double sum = 0;
-    for (uint32_t i = 0; i < plan->timer_used; ++i) {
+    for (uint32_t i = 0; i < std::min<size_t>(plan->timer_used, plan->timer_events.size()); ++i) {
         hipError_t e = hipEventSynchronize(plan->timer_events[i].second);
         if (e != hipSuccess) return hip_fail(e, "pdp_plan_timer_read");
         float ms = 0;

@@ -738,7 +738,7 @@ __device__ __forceinline__ uint32_t find_genome_by_bin(const DevBuild *t, uint32
     return lo;
 }
 
-// Entries [j*kIxBlock, ...) of genome t: genome-local range, clipped to the genome's entry count.
+// Block j's entries [j * blk, ...) of a genome: genome-local range, clipped to the genome's entry count.
 __device__ __forceinline__ void block_range(const DevBuild &B, const uint32_t *gptr, uint32_t j, uint32_t *e0,
                                             uint32_t *e1, uint32_t *gbase) {
     const uint32_t base = gptr[B.gene_base];
@@ -831,7 +831,7 @@ __device__ __forceinline__ uint64_t rec_code5(const DevBuild &B, const uint2 &r)
     return base20_keys(B) ? base20_to_code(r.x, B.k) : static_cast<uint64_t>(r.x);
 }
 
-constexpr uint32_t kIxPlaceThreads = 1024;  // a placement work-group: its block of entries in registers, 16 per thread
+constexpr uint32_t kIxPlaceThreads = 1024;  // a placement work-group: its block of entries in registers, 16 per thread (2 in small builds)
 
 // Same blocks: each entry goes to its bin's range.  The block counts its entries per bin in
 // LDS (every entry's rank among the block's entries of its bin comes back from the LDS

@@ -259,7 +259,7 @@ struct PairWs {
     uint32_t *big_rows;           // rows with more than kSlab hits from the candidates
     uint32_t *n_big;              // counters word 17
     uint32_t *join_done;          // counters word 16: ended work-groups of the join's count pass
-    uint32_t *partials2;          // scan scratch of more than 1024 row groups
+    uint32_t *partials2;          // scan scratch of more than kRowGroups row groups
     uint4 *cands;
     uint32_t *cand_count;         // counters word 6
     DevLongSeg *long_segs;        // long-gene path, by first row

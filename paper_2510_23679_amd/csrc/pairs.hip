@@ -1712,7 +1712,7 @@ struct BbhArgs {
     uint32_t *__restrict__ partials;
     pdp_status *st;
 };
-// A row's pairs, counted (pos null) or written from *pos on.
+// A row's pairs, counted (from pos on) or written from place pos on; returns the place after the last one.
 template <bool WRITE>
 __device__ __forceinline__ uint32_t bbh_plan_row(const BbhArgs &A, uint32_t grow, uint32_t pos) {
     const DevTask &T = A.tasks[find_bbh_task(A.tasks, A.order, A.n_tasks, grow)];
@@ -2245,8 +2245,6 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
             hipLaunchKernelGGL(k_join<false>, g2, dim3(kJoinThreads), 0, s, w.tasks, p.n_tasks, w.cells, w.tile_tot,
                                w.tile_off, w.counters, w.recs, p.rec_cap, st, rg);
         PDP_TRY(hipGetLastError());
-        PDP_TRY(mark(PDP_KERNEL_BUCKET, true));
-        PDP_TRY(mark(PDP_KERNEL_BUCKET, false));
         if (two_pers)
             hipLaunchKernelGGL(k_join_persistent<true>, g2, dim3(kJoinThreads), 0, s, w.tasks, p.n_tasks, p.total_chunks,
                                w.cells, w.tile_tot, w.tile_off, w.counters, w.recs, p.rec_cap, st, w.next_join_write, gate, rg);
@@ -2261,8 +2259,6 @@ hipError_t launch_pairs(const PlanShape &p, const PairWs &w, pdp_bh_out *bh, pdp
     } else {  // no join items (every task on the long-gene or the group path)
         if (!p.n_gdicts) PDP_TRY(mark(PDP_KERNEL_JOIN, true));
         PDP_TRY(mark(PDP_KERNEL_JOIN, false));
-        PDP_TRY(mark(PDP_KERNEL_BUCKET, true));
-        PDP_TRY(mark(PDP_KERNEL_BUCKET, false));
         PDP_TRY(mark(PDP_KERNEL_JOIN_BACKUP, true));
     }
     PDP_TRY(mark(PDP_KERNEL_JOIN_BACKUP, false));
