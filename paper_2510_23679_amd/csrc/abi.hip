@@ -5,6 +5,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
+#include <memory>
 #include <new>
 #include <unordered_map>
 #include <utility>
@@ -503,7 +505,7 @@ static uint64_t plan_groups(pdp_plan *P, const pdp_task *tasks, uint32_t n_tasks
     return entries;
 }
 
-int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *params, pdp_plan **out) {
+static int32_t plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *params, pdp_plan **out) {
     if (!out || (n_tasks && !tasks)) return fail(PDP_E_INVAL, "pdp_plan_create: null pointer");
     *out = nullptr;
     if (n_tasks == 0) return fail(PDP_E_INVAL, "pdp_plan_create: no tasks");
@@ -525,12 +527,8 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
     if (prm.theta_den && prm.theta_num > prm.theta_den) return fail(PDP_E_INVAL, "theta above 1");
     const bool filt = prm.theta_den || prm.tau_den;
 
-    pdp_plan *P = new (std::nothrow) pdp_plan();
-    if (!P) return fail(PDP_E_INVAL, "out of host memory");
-    auto bail = [&](int32_t rc) {
-        delete P;
-        return rc;
-    };
+    std::unique_ptr<pdp_plan> owner(new pdp_plan());
+    pdp_plan *P = owner.get();
     // Rows of all tasks and directions: short plans take lower tiles, to fill the chip.
     uint64_t all_rows = 0;
     for (uint32_t t = 0; t < n_tasks; ++t)
@@ -551,14 +549,14 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
     std::vector<uint8_t> is_long(n_tasks, 0);  // the task takes the long-gene path
     for (uint32_t t = 0; t < n_tasks; ++t) {
         const pdp_task &tk = tasks[t];
-        if (!tk.a || !tk.b) return bail(fail(PDP_E_INVAL, "task %u: null dictionary", t));
+        if (!tk.a || !tk.b) return fail(PDP_E_INVAL, "task %u: null dictionary", t);
         if (tk.a->k != tk.b->k || tk.a->alphabet != tk.b->alphabet || tk.a->lead != tk.b->lead ||
             tk.a->n_buckets != tk.b->n_buckets)
-            return bail(fail(PDP_E_INVAL, "task %u: dictionaries built with different k or alphabet (k %u/%u, alphabet %u/%u)",
-                             t, tk.a->k, tk.b->k, tk.a->alphabet, tk.b->alphabet));
+            return fail(PDP_E_INVAL, "task %u: dictionaries built with different k or alphabet (k %u/%u, alphabet %u/%u)",
+                        t, tk.a->k, tk.b->k, tk.a->alphabet, tk.b->alphabet);
         uint32_t flags = tk.flags & (PDP_TASK_AB | PDP_TASK_BA | PDP_TASK_BBH);
         if (flags & PDP_TASK_BBH) flags |= PDP_TASK_AB | PDP_TASK_BA;
-        if (!flags) return bail(fail(PDP_E_INVAL, "task %u: no output selected", t));
+        if (!flags) return fail(PDP_E_INVAL, "task %u: no output selected", t);
         DevTask &d = caller[t];
         std::memset(&d, 0, sizeof(d));
         const bool long_task = ((tk.a->flags | tk.b->flags) & PDP_DICT_LONG_GENES) != 0;
@@ -616,7 +614,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
             const uint64_t W = (uint64_t(C->n_genes) + 1) / 2;
             const uint64_t dense = 4 * (((W + 3) & ~3ull) + (filt ? 3 : 1) * W + (W + 31) / 32);
             if (dense > kMaxTileLds)
-                return bail(fail(PDP_E_LIMIT, "task %u: %u target genes do not fit an LDS tile", t, C->n_genes));
+                return fail(PDP_E_LIMIT, "task %u: %u target genes do not fit an LDS tile", t, C->n_genes);
             tile_lds = std::max<uint32_t>(tile_lds, static_cast<uint32_t>(dense));
             // Unless the caller fixed the height: to fill the chip a plan with under 256 tiles takes
             // lower ones, or under 512 where a tile's records (a row meets columns by chance, `met`) then
@@ -643,8 +641,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         while (d.tiles_n[0] + d.tiles_n[1] > kJoinTileCap) {
             const bool can0 = d.tiles_n[0] && d.tile_shift[0] < 8, can1 = d.tiles_n[1] && d.tile_shift[1] < 8;
             if (!can0 && !can1)
-                return bail(fail(PDP_E_LIMIT, "task %u: too many genes for %u tiles of %u rows", t, kJoinTileCap,
-                                 kTileMaxRows));
+                return fail(PDP_E_LIMIT, "task %u: too many genes for %u tiles of %u rows", t, kJoinTileCap, kTileMaxRows);
             const uint32_t dir = can0 && (!can1 || d.tiles_n[0] >= d.tiles_n[1]) ? 0 : 1;
             ++d.tile_shift[dir];
             const uint32_t nrows = dir == 0 ? qa->n_genes : qb->n_genes;
@@ -656,7 +653,7 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         P->ab_row.push_back(orow[0]);
         P->ba_row.push_back(orow[1]);
         P->bbh_row.push_back((flags & PDP_TASK_BBH) ? d.bbh_row_base : UINT32_MAX);
-        if (bh_rows >= UINT32_MAX) return bail(fail(PDP_E_LIMIT, "plan too large for 32-bit indices"));
+        if (bh_rows >= UINT32_MAX) return fail(PDP_E_LIMIT, "plan too large for 32-bit indices");
     }
     // Tasks of a group leave the pair path: no join items and no tiles of their own.
     std::memset(&P->shape, 0, sizeof(P->shape));
@@ -743,10 +740,10 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
         }
         join_tiles = std::max(join_tiles, tile_local);
         cells += uint64_t(tile_local) * d.n_chunks;
-        if (cells >= UINT32_MAX) return bail(fail(PDP_E_LIMIT, "plan too large for 32-bit record counts"));
+        if (cells >= UINT32_MAX) return fail(PDP_E_LIMIT, "plan too large for 32-bit record counts");
         P->tasks.push_back(d);
         if (chunks > UINT32_MAX || P->tiles.size() >= UINT32_MAX)
-            return bail(fail(PDP_E_LIMIT, "plan too large for 32-bit indices"));
+            return fail(PDP_E_LIMIT, "plan too large for 32-bit indices");
     }
     {  // the one-pass join's items: each task's bucket ranges of bpw * subs buckets, ordered by range
        // across tasks (a range's first bucket as a fraction of its task's buckets, in kSteps steps),
@@ -835,8 +832,16 @@ int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_param
     P->shape.long_lds = (filt ? 3u : 1u) * kLongCols * 4u;
     P->persistent = (prm.flags & PDP_PARAM_PERSISTENT) != 0;
     P->ws_bytes = pair_ws_bytes(P->shape);
-    *out = P;
+    *out = owner.release();
     return ok();
+}
+
+int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *params, pdp_plan **out) {
+    try {
+        return plan_create(tasks, n_tasks, params, out);
+    } catch (const std::exception &) {  // the plan's host tables
+        return fail(PDP_E_INVAL, "out of host memory");
+    }
 }
 
 }  // extern "C"

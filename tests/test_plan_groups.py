@@ -2,6 +2,9 @@
 whatever the k-mer length, so that plan tables, launches and host time stay in proportion; and a plan takes
 the path where the measurements say that it pays."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import pytest
 
@@ -55,3 +58,27 @@ def test_a_group_is_taken_where_it_pays(n, genes, filters, grouped):
     prm = {"theta": (1, 2), "tau": (1, 6)} if filters else {}
     dicts = _dicts(n, genes, 340, 6, "aa")
     assert (_items(dicts, **prm) != _items(dicts, persistent=True, **prm)) == grouped
+
+
+def test_a_plan_past_the_host_memory_is_an_error():
+    # 150,000 tasks of two genomes of 3000 genes: some 2 GB of join items, in a process that may have 1 GB
+    code = """
+import ctypes as C, resource, sys
+sys.path.insert(0, %r)
+import test_plan_groups as T
+import paper_2510_23679_amd as pdp
+from paper_2510_23679_amd import binding as B
+a, b = T._dicts(2, 3000, 300, 6, "aa")
+tasks = (B.pdp_task * 150000)()
+for t in tasks:
+    t.a, t.b, t.flags = C.pointer(a), C.pointer(b), pdp.PDP_TASK_AB
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (1 << 30),) * 2)
+h = B.vp()
+rc = pdp.lib().pdp_plan_create(tasks, len(tasks), None, C.byref(h))
+assert rc == pdp.PDP_E_INVAL and not h.value, rc
+print(pdp.lib().pdp_last_error().decode())
+""" % os.path.dirname(os.path.abspath(__file__))
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), timeout=120)
+    assert r.returncode == 0 and "out of host memory" in r.stdout, (r.returncode, r.stderr[-500:])
