@@ -317,7 +317,8 @@ typedef struct pdp_plan_info {
  * names a dictionary bound with PDP_DICT_LONG_GENES has no join items and no
  * tiles: its rows take the long-gene path (and PDP_PARAM_COLMAX does not apply
  * to it), with the same output layout.  Tasks that compare most pairs of a set
- * of dictionaries (a group, e.g. all pairs of eight genomes or more) are joined
+ * of dictionaries (a group, e.g. all pairs of a dozen genomes, at most 255 of
+ * them; tile_rows, join_entries and lds_budget do not apply to it) are joined
  * together: their shared k-mers are found in one pass over the group's indexes
  * and kept with bounds known from the dictionaries, both directions of a task
  * come from one (column maxima), and join_groups and tiles count the group's
@@ -325,9 +326,9 @@ typedef struct pdp_plan_info {
  * hits from column maxima and from rows of more than four ties, at most its
  * shared k-mers' records (with PDP_PARAM_COLMAX: twice the capacity, since a
  * record then stands for a hit each way); their number, and needed, is the
- * same in every launch.  A plan with
- * PDP_PARAM_PERSISTENT or PDP_PARAM_TWO_PASS joins every pair on its own.
- * Results are identical either way.  Host only.
+ * same in every launch.  A plan with PDP_PARAM_PERSISTENT or
+ * PDP_PARAM_TWO_PASS joins every pair on its own.  Results are identical
+ * either way.  Host only.
  * Errors: PDP_E_INVAL (null, k or alphabet mismatch, BBH without AB|BA), PDP_E_LIMIT. */
 int32_t pdp_plan_create(const pdp_task *tasks, uint32_t n_tasks, const pdp_params *params, pdp_plan **out);
 int32_t pdp_plan_info_get(const pdp_plan *plan, pdp_plan_info *info);

@@ -19,7 +19,9 @@
 //     maximum and ties as in the pair path (Eq. best_hit), and the targets' best hits come from
 //     the column maxima (Alg. 3) of the same sums.
 // Rows with more than kSlab ties leave through the column candidates' list, which counts and
-// orders them (k_colmax_rows, k_colmax_big, k_colmax_sort).
+// orders them (k_group_rows, k_group_big; k_colmax_sort).
+// Letters are not used evenly, and some k-mers are in many genes: items past the LDS arrays or with a hot
+// k-mer go to k_group_join_big, tiles past their hash table to k_group_tile_big.
 #include <algorithm>
 
 #include "common.hpp"
@@ -1078,9 +1080,11 @@ __device__ __forceinline__ void gt_replay(const GtArgs &A, uint32_t tile, uint32
     }
 }
 
-// One tile.  50 genomes of 3000 to 5000 genes: 0.71 ms, half of it the walk (random runs of
-// postings; 1.15 ms with eight lanes per descriptor and 8-byte postings) and half the table's LDS
-// atomics; 26 KiB of LDS, six work-groups per CU.
+// One tile.  50 genomes of 3000 to 5000 genes: 0.71 ms, of which the walk takes 0.38 (random runs of
+// postings; 1.15 ms in all with eight lanes per descriptor and 8-byte postings), the table's keys 0.07, sums,
+// values and ties 0.08, and the column keys' device atomics with the candidates 0.18 (timed by leaving each
+// out).  Bound by latency: its waves wait 77% of their cycles, VALU issues in 36% and LDS is busy in 23% of
+// the kernel's; 26 KiB of LDS, six work-groups per CU.
 template <bool FILT>
 __global__ __launch_bounds__(kGtThreads) void k_group_tile(GtArgs A) {
     using SH = GtSmall<FILT>;
