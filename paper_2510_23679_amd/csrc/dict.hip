@@ -1039,7 +1039,7 @@ struct BinSort {
 };
 
 // Counting-sort slot of a code inside the bin starting at bucket b0: the bucket, then the
-// next xb bits of the code (whole letters), so slots ascend like codes.
+// next xb bits of the code, so slots ascend like codes.
 __device__ __forceinline__ uint32_t bin_slot(const DevBuild &B, uint64_t code, uint32_t b0) {
     const uint32_t b = bucket_of(code, B.k, B.lead, B.bits) - b0;
     if (!B.xb) return b;
@@ -1054,7 +1054,7 @@ __device__ __forceinline__ uint32_t rec_slot(const DevBuild &B, const uint4 &r, 
 __device__ __forceinline__ uint32_t rec_slot(const DevBuild &B, const uint2 &r, uint32_t b0) {
     if (!base20_keys(B)) return bin_slot(B, r.x, b0);
     const uint32_t b = r.x / 8000u - b0;  // 20^3: the last three letters
-    return B.xb ? (b << B.xb) | ((r.x / 400u) % 20u) : b;
+    return B.xb ? (b << B.xb) | (((r.x / 400u) % 20u) >> (5u - B.xb)) : b;
 }
 
 __device__ __forceinline__ uint32_t slot16(const uint32_t *w, uint32_t s) { return (w[s >> 1] >> ((s & 1u) * 16u)) & 0xFFFFu; }
@@ -1330,23 +1330,19 @@ static uint32_t bin_shift(uint32_t nb, uint64_t cap, uint32_t target) {
     return s;
 }
 
-// Bin shift s and sub-slot bits xb of one genome: a bin's counting sort goes by bucket and,
-// where the slots still fit, the next letter (amino acids, 5 bits) or two (nucleotides, 4 bits), so
-// that a slot holds about one entry.  Bins above kIxBinTargetWide entries are halved for these slots to fit
-// where buckets alone hold over two entries on average, and far more of the frequent letters (2000 genes
-// with the letters of proteins: 221 us by buckets, 113 so, even letters 117 and 109; six genomes of 1000
-// genes: 185 and 169, even letters 152 and 167; below, of 700 genes: 144 and 157, 141 and 157).
+// Bin shift s and sub-slot bits xb of one genome: a bin's counting sort goes by bucket and the leading bits
+// of the next letter (amino acids, 5 bits) or two (nucleotides, 4 bits), all of them or as many as the
+// slots hold, so that a slot holds few entries also where letters are frequent (2000 genes with the letters
+// of proteins: 221 us by buckets alone, 138 so).
 struct BinPlan {
     uint32_t s, xb;
 };
 static BinPlan bin_plan(uint32_t nb, uint64_t cap, uint32_t k, uint32_t alphabet, uint32_t target, uint32_t slots) {
     const AlphaSpec a = alpha_spec(alphabet);
-    uint32_t s = bin_shift(nb, cap, target);
-    const uint32_t least = bin_shift(nb, cap, kIxBinTargetWide);  // the most bins the workspace holds
+    const uint32_t s = bin_shift(nb, cap, target);
     const uint32_t rest = k - lead_letters(k, alphabet);
     uint32_t xb = a.bits * std::min<uint32_t>(rest, a.bits == 2 ? 2u : 1u);
-    while (xb && s > least && cap > 2ull * nb && (1ull << (s + xb)) > slots) --s;
-    while (xb && (1ull << (s + xb)) > slots) xb -= a.bits;
+    while (xb && (1ull << (s + xb)) > slots) --xb;
     return {s, xb};
 }
 

@@ -206,7 +206,7 @@ struct DevBuild {
     uint32_t n_genes, k, nb, lead, gene_base;
     uint32_t hshift, nh, nblk;            // coarse bins of 2^hshift buckets; entry blocks for the histogram
     uint32_t blk;                         // entries per block
-    uint32_t xb;                          // sub-slot bits per bucket of a bin's counting sort (next letters)
+    uint32_t xb;                          // sub-slot bits per bucket of a bin's counting sort (of the next letters)
     uint32_t blk_base, bin_base;          // first block and bin of the genome
     uint32_t *nwin, *mv_ptr;
     uint64_t *mv_code;

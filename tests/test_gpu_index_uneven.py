@@ -93,19 +93,28 @@ def test_around_the_small_builds(letters, k):
     check_dictionary(d.host(), oracle.OracleGenome(genome, k))
 
 
-def test_around_two_entries_a_bucket():
-    # 160000 buckets: genomes of 319,998 to 320,004 letters beside one that makes the build large
-    genomes = [_genome(32 + i, 2, 159999 + i, "ACDEFGHIKL") for i in range(4)]
-    for g in genomes:  # genes of ordinary length
-        n = g.n_residues
-        g.offsets = np.append(np.arange(0, n, 400, dtype=np.uint64), np.uint64(n))
-    genomes.append(_genome(40, 1000, 700, AA))
-    print("[case] two entries a bucket", [g.n_residues for g in genomes], flush=True)
-    batch = pdp.DictionaryBatch([pdp.DeviceGenome.of(g) for g in genomes], 6)
+@pytest.mark.parametrize("k,letters", [(k, n) for k in (6, 7) for n in (20, 60, 130, 250, 500)])
+def test_sub_slots_of_part_of_a_letter(k, letters):
+    # genomes of 20,000 to 500,000 letters beside one that makes the build large: bins of 16384 to 512 buckets,
+    # whose slots take none to four bits of the next letter
+    genomes = [_genome(32 + i, letters, 1000 + i, AA, PROTEIN) for i in range(3)] + [_genome(40, 1000, 700, AA)]
+    print("[case] sub-slots, k", k, [g.n_residues for g in genomes], flush=True)
+    batch = pdp.DictionaryBatch([pdp.DeviceGenome.of(g) for g in genomes], k)
     batch.build()
     batch.check_status()
     for d, g in zip(batch.dicts, genomes):
-        check_dictionary(d.host(), oracle.OracleGenome(g, 6))
+        check_dictionary(d.host(), oracle.OracleGenome(g, k))
+
+
+@pytest.mark.parametrize("k", [11, 13, 17])
+def test_sub_slots_of_part_of_a_letter_nucleotides(k):
+    genomes = [_genome(60 + n, n, 1001, "ACGT", alphabet="nt") for n in (50, 200, 400, 900)]
+    print("[case] nucleotide sub-slots, k", k, [g.n_residues for g in genomes], flush=True)
+    batch = pdp.DictionaryBatch([pdp.DeviceGenome.of(g) for g in genomes], k)
+    batch.build()
+    batch.check_status()
+    for d, g in zip(batch.dicts, genomes):
+        check_dictionary(d.host(), oracle.OracleGenome(g, k))
 
 
 def test_a_genome_of_ordinary_size_takes_the_large_forms():
